@@ -81,7 +81,8 @@ typedef enum {
  * Supported shapes (SA_ERR_UNSUPPORTED otherwise): 1 <= H, 1 <= M <= 4096,
  * d in {64, 128}, T < 2^31, B >= 0.  bf16 with d = 64 and M a multiple of 128
  * up to 1024, or d = 128 and M a multiple of 128 up to 512, runs the fused
- * matrix-core kernels; other supported shapes and SA_FP32 run a plain fp32
+ * matrix-core kernels; the forward of other bf16 shapes runs in two matrix-core
+ * passes with fp32 weights; other supported shapes and SA_FP32 run a plain fp32
  * path with the same ABI and the same results up to rounding.
  */
 

@@ -96,7 +96,8 @@ sa_status validate_offsets(const int64_t* offsets, int64_t B, int64_t T, hipStre
 
 // ---------------------------------------------------------------- forward plan
 struct FwdPlan {
-    bool fused = false;
+    bool fused = false;    // one-pass matrix-core forward on the work list
+    bool split = false;    // two-pass matrix-core forward (bf16 shapes without a fused instance)
     int64_t C = 0;         // tokens per workgroup range
     int64_t n_ranges = 0;  // workgroups
     int64_t max_items = 0;
@@ -120,12 +121,24 @@ FwdPlan plan_fwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype
                  bool need_lse_scratch) {
     FwdPlan p;
     p.fused = dtype == SA_BF16 && sa::fused_fwd_supported(M, d);
+    p.split = dtype == SA_BF16 && !p.fused;
     size_t off = 0;
     auto carve = [&](size_t bytes) {
         const size_t o = off;
         off = align_up(off + bytes, 256);
         return o;
     };
+    if (p.split) {
+        const int64_t target = sa::split_fwd_ranges(M), HT = (int64_t)H * T;
+        p.C = std::max<int64_t>(1, ((HT + target - 1) / target + sa::kTileTokens - 1) / sa::kTileTokens) * sa::kTileTokens;
+        p.n_ranges = (HT + p.C - 1) / p.C;
+        // a pair split over ranges has at most one slot per range it touches, two
+        // ranges' worth of slots cover them all (segments.h)
+        p.off_partials = carve(sizeof(float) * 2 * (size_t)p.n_ranges * M * d);
+        if (need_lse_scratch) p.off_lse = carve(sizeof(float) * (size_t)T * H);
+        p.total = off;
+        return p;
+    }
     // both paths cut the head-major token space into equal ranges (a work list
     // of (user, head) segments, split pairs merged in segment order): the fused
     // kernel runs one range per workgroup slot, the plain aggregation one range
@@ -612,6 +625,31 @@ sa_status run_fwd(const void* K, const void* V, const void* P, const int64_t* of
                   float* sketch, float* lse, uint8_t* ws, const FwdPlan& plan, hipStream_t stream,
                   bool p_user) {
     hipError_t e;
+    if (plan.split) {
+        sa::SplitFwdArgs f;
+        f.K = reinterpret_cast<const uint16_t*>(K);
+        f.V = reinterpret_cast<const uint16_t*>(V);
+        f.P = reinterpret_cast<const uint16_t*>(P);
+        f.offsets = offsets;
+        f.B = B;
+        f.T = T;
+        f.C = plan.C;
+        f.n_ranges = plan.n_ranges;
+        f.H = H;
+        f.M = M;
+        f.d = d;
+        f.scale = scale;
+        f.p_user = p_user;
+        f.sketch = sketch;
+        f.lse = lse ? lse : reinterpret_cast<float*>(ws + plan.off_lse);
+        f.partials = reinterpret_cast<float*>(ws + plan.off_partials);
+        e = sa::launch_split_fwd(f, stream);
+        if (e != hipSuccess) return hip_fail(e, "two-pass forward launch");
+        sa::ProfScope ps("splitL_merge", stream);
+        e = sa::launch_merge_ranges(offsets, B, T, H, plan.C, plan.n_ranges, f.partials, (int64_t)M * d, sketch, stream);
+        if (e != hipSuccess) return hip_fail(e, "split-L merge launch");
+        return SA_OK;
+    }
     int32_t* items = reinterpret_cast<int32_t*>(ws + plan.off_items);
     int32_t* wg_start = reinterpret_cast<int32_t*>(ws + plan.off_wgstart);
     int32_t* pair_start = reinterpret_cast<int32_t*>(ws + plan.off_pairstart);

@@ -1,0 +1,525 @@
+// Forward of the SA sketching step on bf16 inputs for the shapes the one-pass
+// fused kernel (fwd_fused.hip) has no instance for: M x d too large for one
+// workgroup's registers (d = 128 above 512 prototypes, d = 64 above 1024), or M
+// not a multiple of 128.  The weights keep their fp32 precision.
+//
+// Two passes over the keys:
+//
+//   lse_tokens_kernel  lse_t = log sum_m exp(scale <K_t, P_m>)
+//   agg_split_kernel   A = exp(scale <K_t, P_m> - lse_t);  sketch_m += A V_t
+//
+// so that a workgroup of the second pass needs only its own prototypes (section
+// 3.1: the softmax of a token couples all M prototypes through lse_t alone) and
+// the M x d accumulator is spread over workgroups.
+//
+// Products of bf16 inputs are exact in the matrix cores' fp32 accumulation, so
+// the logits are single-precision sums.  The weights A are fp32: each is cut into
+// three bf16 parts of eight mantissa bits, A = hi + mid + lo exactly (truncation,
+// each remainder is exact), and the three products with the bf16 V accumulate in
+// fp32.  Against float64 the sketch is then as close as a plain fp32 evaluation
+// (measured 6e-7 relative, 2-norm, at M = 1024, d = 128).
+//
+// Executed matrix work is (2 + 2 + 6) M d per token against 4 M d algorithmic;
+// the aggregation is bound by its matrix instructions (32 of them per 32 x 32
+// logits tile at d = 128) beside about 11 VALU instructions per weight.
+// Measured on 100K tokens, H = 1, M = 1024, d = 128: lse 57 us, aggregation 106 us
+// (990 TFLOP/s executed, against 1200 for a large library product), merge 7 us; the
+// fp32 VALU path took 2.8 ms, 3.2 ms and 86 us.
+#include "reduce_ops.h"
+#include "sa_internal.h"
+#include "segments.h"
+#include "tile_ops.h"
+
+namespace sa {
+
+namespace {
+
+using namespace tile;
+
+constexpr float kLn2 = 0.6931471805599453f;
+
+// ---------------------------------------------------------------- log-sum-exp
+// Workgroup = 4 waves, each holding 32 TT tokens of one head as B operands; the
+// prototypes stream through LDS 64 at a time (double-buffered, the next tile in
+// registers), so the logits tile has prototypes as rows and a token per lane and
+// the running maximum and sum of a token live in one lane per half-wave: no
+// cross-lane work until the end.
+template <int D, int TT>
+struct LseCfg {
+    static constexpr int KS = D / 16;
+    static constexpr int KCH = D / 8;
+    static constexpr int ROWS = 64;                       // prototypes per LDS tile
+    static constexpr int NLD = ROWS * KCH / 256;          // 16-byte chunks per thread
+    static constexpr int TILE = ROWS * D * 2;
+    static constexpr int TOKENS = 4 * 32 * TT;            // tokens per workgroup
+};
+
+template <int D, int TT>
+__global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __restrict__ K,
+                                                            const uint16_t* __restrict__ P,
+                                                            const int64_t* __restrict__ off, int64_t B, int64_t T,
+                                                            int32_t H, int32_t M, float scale, bool p_user,
+                                                            float* __restrict__ lse) {
+    using C = LseCfg<D, TT>;
+    constexpr int KS = C::KS;
+    __shared__ __attribute__((aligned(16))) uint8_t smem[2 * C::TILE];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int l32 = lane & 31, hl = lane >> 5;
+    const int64_t nblk = (T + C::TOKENS - 1) / C::TOKENS;
+    const int32_t h = (int32_t)(blockIdx.x / nblk);
+    const int64_t blk0 = (blockIdx.x % nblk) * C::TOKENS;          // the workgroup's first token
+    const int64_t blk1 = blk0 + C::TOKENS < T ? blk0 + C::TOKENS : T;
+
+    int64_t tok[TT];
+    bf16x8 kop[TT][KS];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+        tok[tt] = blk0 + (w * TT + tt) * 32 + l32;
+        const int64_t row = tok[tt] < T ? tok[tt] : T - 1;
+        const uint16_t* src = K + (row * H + h) * D + 8 * hl;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk)
+            kop[tt][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src + 16 * kk));
+    }
+    const float ks2 = scale * kLog2e;
+    const int ntiles = (M + C::ROWS - 1) / C::ROWS;
+
+    // with one prototype block per user, one round per user that has tokens here
+    int64_t b = 0, lo = 0, hi = T;
+    if (p_user) {   // first user whose tokens end after blk0
+        int64_t a = 0, z = B;
+        while (a < z) {
+            const int64_t mid = (a + z) >> 1;
+            if (seg_clamp(off[mid + 1], T) > blk0) z = mid; else a = mid + 1;
+        }
+        b = a;
+    }
+    for (; p_user ? b < B : b < 1; ++b) {
+        if (p_user) {
+            lo = seg_clamp(off[b], T);
+            hi = seg_clamp(off[b + 1], T);
+            if (lo >= blk1) break;
+            if (hi <= lo || hi <= blk0) continue;
+        }
+        const uint16_t* Pg = P + (p_user ? b * H + h : (int64_t)h) * M * D;
+        u32x4 reg[C::NLD];
+        auto fetch = [&](int tile) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < C::NLD; ++i) {
+                const int idx = tid + i * 256;
+                const int row = min(tile * C::ROWS + idx / C::KCH, M - 1);
+                reg[i] = *reinterpret_cast<const u32x4*>(Pg + (uint32_t)(row * D + (idx % C::KCH) * 8));
+            }
+        };
+        auto store = [&](int buf) __attribute__((always_inline)) {
+            uint16_t* dst = reinterpret_cast<uint16_t*>(smem + buf * C::TILE);
+#pragma unroll
+            for (int i = 0; i < C::NLD; ++i) {
+                const int idx = tid + i * 256;
+                *reinterpret_cast<u32x4*>(dst + swz<D>(idx / C::KCH, idx % C::KCH)) = reg[i];
+            }
+        };
+        float mu[TT], z[TT];   // log2 units
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+            mu[tt] = -INFINITY;
+            z[tt] = 0.f;
+        }
+        fetch(0);
+        __syncthreads();   // the previous round is done with the tiles
+        store(0);
+        __syncthreads();
+        for (int tile = 0; tile < ntiles; ++tile) {
+            const bool more = tile + 1 < ntiles;
+            if (more) fetch(tile + 1);
+            const uint16_t* Ps = reinterpret_cast<const uint16_t*>(smem + (tile & 1) * C::TILE);
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const int row0 = tile * C::ROWS + half * 32;
+                if (row0 >= M) break;
+                f32x16 s[TT];
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) s[tt][r] = 0.f;
+#pragma unroll
+                for (int kk = 0; kk < KS; ++kk) {
+                    const bf16x8 pop = lds_b128(Ps, swz<D>(half * 32 + l32, 2 * kk + hl));
+#pragma unroll
+                    for (int tt = 0; tt < TT; ++tt)
+                        s[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pop, kop[tt][kk], s[tt], 0, 0, 0);
+                }
+                const bool ragged = row0 + 32 > M;   // rows past M: no part in the maximum or the sum
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt) {
+                    float x[16];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) x[r] = s[tt][r];
+                    if (ragged) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if (row0 + srow(r, hl) >= M) x[r] = -3.4028234664e38f;
+                    }
+                    float t = x[0];
+#pragma unroll
+                    for (int r = 1; r < 16; ++r) t = fmaxf(t, x[r]);
+                    const float mn = fmaxf(mu[tt], t * ks2);
+                    z[tt] *= __builtin_amdgcn_exp2f(mu[tt] - mn);   // 0 on the first tile
+                    float sum[2] = {0.f, 0.f};
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], ks2, -mn));
+                        if (ragged && row0 + srow(r, hl) >= M) e = 0.f;
+                        sum[r & 1] += e;
+                    }
+                    z[tt] += sum[0] + sum[1];
+                    mu[tt] = mn;
+                }
+            }
+            if (more) store((tile + 1) & 1);
+            __syncthreads();
+        }
+        // the two half-waves hold the token's other prototype rows
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+            const auto m2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(mu[tt]), __float_as_uint(mu[tt]), false, false);
+            const auto z2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(z[tt]), __float_as_uint(z[tt]), false, false);
+            const float ma = __uint_as_float(m2[0]), mb = __uint_as_float(m2[1]);
+            const float mx = fmaxf(ma, mb);
+            const float zz = __uint_as_float(z2[0]) * __builtin_amdgcn_exp2f(ma - mx) +
+                             __uint_as_float(z2[1]) * __builtin_amdgcn_exp2f(mb - mx);
+            if (hl == 0 && tok[tt] >= lo && tok[tt] < hi)
+                lse[tok[tt] * H + h] = __builtin_fmaf(mx, kLn2, __builtin_amdgcn_logf(zz) * kLn2);
+        }
+    }
+}
+
+// ---------------------------------------------------------------- aggregation
+// Workgroup = (token range, 32 NW prototypes), a wave = 32 prototypes held in
+// registers as B operands for the whole segment; token tiles of 32 double-buffered
+// in LDS, fetched two tiles ahead into alternating register sets.  The logits tile
+// has tokens as rows and a prototype per lane, which is the A operand layout of the
+// aggregation (V read with the transposing LDS load).
+template <int D, int NW>
+struct AggCfg {
+    static constexpr int THREADS = NW * 64;
+    static constexpr int MP = 32 * NW;
+    static constexpr int KS = D / 16;
+    static constexpr int JT = D / 32;
+    static constexpr int KCH = D / 8;
+    static constexpr int LD_CHUNKS = 32 * KCH;
+    static constexpr int NCH = (LD_CHUNKS + THREADS - 1) / THREADS;
+    static constexpr int TILE = 32 * D * 2;
+    static constexpr int OFF_K = 0;                    // 2 x [32][D] K tiles
+    static constexpr int OFF_V = OFF_K + 2 * TILE;     // 2 x [32][D] V tiles
+    static constexpr int OFF_L = OFF_V + 2 * TILE;     // 2 x [32] token shifts, -lse / ln 2
+    static constexpr int OFF_F = OFF_L + 2 * 32 * 4;   // [2] first token + 1 of a tile with infinite or NaN V
+    static constexpr int LDS = OFF_F + 16;
+};
+
+struct AggArgs {
+    const uint16_t* K;
+    const uint16_t* V;
+    const uint16_t* P;
+    const int64_t* off;
+    const float* lse;
+    int64_t B, T, C, n_ranges;
+    int32_t H, M, parts;
+    float scale;
+    bool p_user;
+    float* sketch;
+    float* partials;
+};
+
+// whether any of eight bf16 values is infinite or NaN
+__device__ inline bool nonfinite8(u32x4 v) {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    u16x2 m = __builtin_bit_cast(u16x2, v[0] & 0x7fff7fffu);
+#pragma unroll
+    for (int i = 1; i < 4; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, v[i] & 0x7fff7fffu));
+    return m[0] >= 0x7f80 || m[1] >= 0x7f80;
+}
+__device__ inline uint32_t finite_or_zero(uint32_t w) {
+    if ((w & 0x7f80u) == 0x7f80u) w &= 0xffff0000u;
+    if ((w & 0x7f800000u) == 0x7f800000u) w &= 0xffffu;
+    return w;
+}
+
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void agg_split_kernel(AggArgs a) {
+    using C = AggCfg<D, NW>;
+    constexpr int KS = C::KS, JT = C::JT;
+    __shared__ __attribute__((aligned(16))) uint8_t smem[C::LDS];
+    float* shift = reinterpret_cast<float*>(smem + C::OFF_L);
+    volatile int* flag = reinterpret_cast<volatile int*>(smem + C::OFF_F);
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int l32 = lane & 31, hl = lane >> 5;
+
+    // workgroup -> (range, part): the parts of a range read the same tokens, so
+    // they sit back to back on one XCD
+    const int64_t xcd = blockIdx.x % 8, jx = blockIdx.x / 8;
+    const int part = (int)(jx % a.parts);
+    const int64_t ix = jx / a.parts;
+    const int64_t q8 = a.n_ranges / 8, r8 = a.n_ranges % 8;
+    if (ix >= q8 + (xcd < r8 ? 1 : 0)) return;
+    const int64_t range = xcd * q8 + (xcd < r8 ? xcd : r8) + ix;
+
+    const float ks2 = a.scale * kLog2e;
+    const int64_t MD = (int64_t)a.M * D;
+    const uint32_t row_stride = (uint32_t)a.H * D;
+    const int m0 = part * C::MP + w * 32;            // the wave's first prototype
+    const int prow = min(m0 + l32, a.M - 1);         // this lane's (rows past M repeat the last)
+
+    SegmentWalk walk(a.off, a.B, a.T, a.H, a.C, range);
+    Segment sg;
+    while (walk.next(sg)) {
+        const int b = sg.b, h = sg.h, t0 = sg.t0, t1 = sg.t1;
+        bf16x8 pop[KS];
+        {
+            const uint16_t* Pg = a.P + (a.p_user ? (int64_t)b * a.H + h : (int64_t)h) * MD + (int64_t)prow * D;
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk)
+                pop[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(Pg + 16 * kk + 8 * hl));
+        }
+        // Every fetch issues the same loads (rows past the segment read its last
+        // token), so the wait before a store counts exactly the newer set's loads.
+        struct Regs { u32x4 k[C::NCH], v[C::NCH]; float l; };
+        Regs ra, rb;
+        const char* Kb = reinterpret_cast<const char*>(a.K + ((int64_t)t0 * a.H + h) * D);
+        const char* Vb = reinterpret_cast<const char*>(a.V + ((int64_t)t0 * a.H + h) * D);
+        const float* Lb = a.lse + (int64_t)t0 * a.H + h;
+        auto fetch = [&](int ts, Regs& r) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < C::NCH; ++c) {
+                const int idx = (tid + c * C::THREADS) % C::LD_CHUNKS;
+                const int row = min(ts + idx / C::KCH, t1 - 1) - t0;
+                const uint32_t o = ((uint32_t)row * row_stride + (uint32_t)((idx % C::KCH) * 8)) * 2;
+                r.k[c] = *reinterpret_cast<const u32x4*>(Kb + o);
+                r.v[c] = *reinterpret_cast<const u32x4*>(Vb + o);
+            }
+            r.l = Lb[(uint32_t)(min(ts + l32, t1 - 1) - t0) * (uint32_t)a.H];
+        };
+        auto store = [&](int ts, int buf, const Regs& r) __attribute__((always_inline)) {
+            uint16_t* Kd = reinterpret_cast<uint16_t*>(smem + C::OFF_K + buf * C::TILE);
+            uint16_t* Vd = reinterpret_cast<uint16_t*>(smem + C::OFF_V + buf * C::TILE);
+            bool bad = false;
+#pragma unroll
+            for (int c = 0; c < C::NCH; ++c) {
+                const int idx = tid + c * C::THREADS;
+                if (C::LD_CHUNKS % C::THREADS == 0 || idx < C::LD_CHUNKS) {
+                    u32x4 v = r.v[c];
+                    if (ts + idx / C::KCH >= t1) v = (u32x4){0, 0, 0, 0};   // V of rows past the segment
+                    *reinterpret_cast<u32x4*>(Kd + swz<D>(idx / C::KCH, idx % C::KCH)) = r.k[c];
+                    *reinterpret_cast<u32x4*>(Vd + swz<D>(idx / C::KCH, idx % C::KCH)) = v;
+                    bad |= nonfinite8(v);
+                }
+            }
+            if (w == 0 && hl == 0) shift[buf * 32 + l32] = -r.l * kLog2e;
+            if (bad) flag[buf] = ts + 1;
+        };
+        fetch(t0, ra);
+        fetch(t0 + 32, rb);
+        __syncthreads();   // the previous segment is done with every LDS buffer
+        store(t0, 0, ra);
+        __syncthreads();
+
+        f32x16 acc[JT];
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[jt][r] = 0.f;
+        // wait for the held operands here, so that the waits inside the loop count
+        // the token fetches alone
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(pop[kk]));
+
+        auto step = [&](int ts, int buf, Regs& far, const Regs& nxt) __attribute__((always_inline)) {
+            const bool more = ts + 32 < t1;
+            fetch(ts + 64, far);
+            const uint16_t* Ks = reinterpret_cast<const uint16_t*>(smem + C::OFF_K + buf * C::TILE);
+            uint16_t* Vs = reinterpret_cast<uint16_t*>(smem + C::OFF_V + buf * C::TILE);
+            f32x16 s;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk)
+                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_b128(Ks, swz<D>(l32, 2 * kk + hl)), pop[kk], s, 0, 0, 0);
+            float sh[16];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 q = *reinterpret_cast<const float4*>(shift + buf * 32 + 8 * g + 4 * hl);
+                sh[4 * g] = q.x;
+                sh[4 * g + 1] = q.y;
+                sh[4 * g + 2] = q.z;
+                sh[4 * g + 3] = q.w;
+            }
+            // weights and their three bf16 parts (parts[p][i]: two tokens' values)
+            uint32_t parts[3][8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                float e[2], r1[2], r2[2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    e[q] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * i + q], ks2, sh[2 * i + q]));
+                    r1[q] = e[q] - bf16_hi(__float_as_uint(e[q]));
+                    r2[q] = r1[q] - bf16_hi(__float_as_uint(r1[q]));
+                }
+                // the upper halves of two values, the first in the low half
+                parts[0][i] = __builtin_amdgcn_perm(__float_as_uint(e[1]), __float_as_uint(e[0]), 0x07060302u);
+                parts[1][i] = __builtin_amdgcn_perm(__float_as_uint(r1[1]), __float_as_uint(r1[0]), 0x07060302u);
+                parts[2][i] = __builtin_amdgcn_perm(__float_as_uint(r2[1]), __float_as_uint(r2[0]), 0x07060302u);
+            }
+            auto op = [&](int p, int h2) __attribute__((always_inline)) {
+                return __builtin_bit_cast(bf16x8, (u32x4){parts[p][4 * h2], parts[p][4 * h2 + 1], parts[p][4 * h2 + 2],
+                                                          parts[p][4 * h2 + 3]});
+            };
+            if (__builtin_expect(flag[buf] != ts + 1, 1)) {
+#pragma unroll
+                for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+                    for (int h2 = 0; h2 < 2; ++h2) {
+                        const bf16x8 v = lds_tr_tokens<D>(Vs, lane, jt, h2);
+#pragma unroll
+                        for (int p = 2; p >= 0; --p)
+                            acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(p, h2), v, acc[jt], 0, 0, 0);
+                    }
+            } else {
+                // an infinite V times a weight's zero lower part would be NaN: the
+                // upper parts see V as it is, the others its finite values only
+                // (uniform over the workgroup: every thread reads the same flag)
+                auto add = [&](int p) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+                        for (int h2 = 0; h2 < 2; ++h2)
+                            acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(p, h2), lds_tr_tokens<D>(Vs, lane, jt, h2),
+                                                                              acc[jt], 0, 0, 0);
+                };
+                add(0);
+                __syncthreads();
+                for (int idx = tid; idx < C::LD_CHUNKS * 4; idx += C::THREADS) {
+                    uint32_t* q = reinterpret_cast<uint32_t*>(Vs) + idx;
+                    *q = finite_or_zero(*q);
+                }
+                __syncthreads();
+                add(1);
+                add(2);
+            }
+            if (more) store(ts + 32, buf ^ 1, nxt);
+            __syncthreads();
+        };
+        for (int ts = t0;; ts += 64) {
+            step(ts, 0, ra, rb);
+            if (ts + 32 >= t1) break;
+            step(ts + 32, 1, rb, ra);
+            if (ts + 64 >= t1) break;
+        }
+        // rows of this wave: prototypes m0 + srow(r, hl), columns jt*32 + l32
+        float* out = sg.split ? a.partials + sg.slot * MD : a.sketch + ((int64_t)b * a.H + h) * MD;
+        uint32_t lane_off = (uint32_t)((m0 + 4 * hl) * D + l32);
+        asm volatile("" : "+v"(lane_off));
+        if (m0 + 32 <= a.M) {
+#pragma unroll
+            for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    out[lane_off + (uint32_t)((8 * (r >> 2) + (r & 3)) * D + jt * 32)] = acc[jt][r];
+        } else {
+#pragma unroll
+            for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (m0 + srow(r, hl) < a.M)
+                        out[lane_off + (uint32_t)((8 * (r >> 2) + (r & 3)) * D + jt * 32)] = acc[jt][r];
+        }
+    }
+}
+
+// ---------------------------------------------------------------- split-L merge
+// sketch[b,h] = the partials of a split pair added in token order; zero for an
+// empty one; a pair held by one range is written by the aggregation itself.
+__global__ __launch_bounds__(256) void merge_ranges_kernel(const int64_t* __restrict__ off, int64_t B, int64_t T,
+                                                           int32_t H, int64_t C, int64_t n_ranges,
+                                                           const float* __restrict__ partials, int64_t MD,
+                                                           float* __restrict__ sketch) {
+    const int64_t h = blockIdx.x / B, b = blockIdx.x % B;
+    const PairSlots ps(seg_clamp(off[b], T), seg_clamp(off[b + 1], T), h, T, C);
+    if (ps.count == 1) return;
+    const int64_t idx = ((int64_t)blockIdx.y * 256 + threadIdx.x) * 4;
+    if (idx >= MD) return;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 16   // several segments' loads in flight; the sum keeps segment order
+    for (int64_t i = 0; i < ps.count; ++i) {
+        const float4 v = *reinterpret_cast<const float4*>(partials + ps.slot(i) * MD + idx);
+        acc.x += v.x;
+        acc.y += v.y;
+        acc.z += v.z;
+        acc.w += v.w;
+    }
+    *reinterpret_cast<float4*>(sketch + (b * H + h) * MD + idx) = acc;
+}
+
+template <int D, int NW>
+hipError_t launch_agg(AggArgs a, hipStream_t stream) {
+    a.parts = (a.M + 32 * NW - 1) / (32 * NW);
+    const int64_t per_xcd = (a.n_ranges + 7) / 8;
+    hipLaunchKernelGGL((agg_split_kernel<D, NW>), dim3((unsigned)(8 * per_xcd * a.parts)), dim3(NW * 64), 0, stream, a);
+    return hipGetLastError();
+}
+
+template <int D, int TT>
+hipError_t launch_lse(const SplitFwdArgs& f, hipStream_t stream) {
+    const int64_t nblk = (f.T + LseCfg<D, TT>::TOKENS - 1) / LseCfg<D, TT>::TOKENS;
+    if (nblk * f.H > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((lse_tokens_kernel<D, TT>), dim3((unsigned)(nblk * f.H)), dim3(256), 0, stream, f.K, f.P,
+                       f.offsets, f.B, f.T, f.H, f.M, f.scale, f.p_user, f.lse);
+    return hipGetLastError();
+}
+
+// Waves (of 32 prototypes) per aggregation workgroup: eight, or four where eight
+// would leave at least half a workgroup without prototypes, two for M <= 64.
+int agg_waves(int32_t M) {
+    if (M <= 64) return 2;
+    const int rest = M % 256;
+    return rest > 0 && rest <= 128 ? 4 : 8;
+}
+
+}  // namespace
+
+int64_t split_fwd_ranges(int32_t M) {
+    // two waves per SIMD of every CU in one round of workgroups; at most two
+    // workgroups per CU, which bounds the partials by 2 x 512 slots
+    const int nw = agg_waves(M);
+    const int64_t parts = (M + 32 * nw - 1) / (32 * nw);
+    const int64_t r = (int64_t)device_cus() * (nw == 8 ? 1 : 2) / parts;
+    return r < 1 ? 1 : r;
+}
+
+hipError_t launch_split_fwd(const SplitFwdArgs& f, hipStream_t stream) {
+    if (f.T == 0) return hipSuccess;
+    hipError_t e;
+    {
+        ProfScope ps("split_lse", stream);
+        e = f.d == 64 ? launch_lse<64, 2>(f, stream) : launch_lse<128, 2>(f, stream);
+    }
+    if (e != hipSuccess) return e;
+    AggArgs a{f.K, f.V, f.P, f.offsets, f.lse, f.B, f.T, f.C, f.n_ranges, f.H, f.M, 1, f.scale, f.p_user, f.sketch,
+              f.partials};
+    ProfScope ps("split_agg", stream);
+    switch (agg_waves(f.M)) {
+        case 2: return f.d == 64 ? launch_agg<64, 2>(a, stream) : launch_agg<128, 2>(a, stream);
+        case 4: return f.d == 64 ? launch_agg<64, 4>(a, stream) : launch_agg<128, 4>(a, stream);
+        default: return f.d == 64 ? launch_agg<64, 8>(a, stream) : launch_agg<128, 8>(a, stream);
+    }
+}
+
+hipError_t launch_merge_ranges(const int64_t* offsets, int64_t B, int64_t T, int32_t H, int64_t C, int64_t n_ranges,
+                               const float* partials, int64_t MD, float* sketch, hipStream_t stream) {
+    if ((int64_t)H * B == 0) return hipSuccess;
+    dim3 grid((unsigned)((int64_t)H * B), (unsigned)((MD + 1023) / 1024));   // MD is a multiple of 4
+    hipLaunchKernelGGL(merge_ranges_kernel, grid, dim3(256), 0, stream, offsets, B, T, H, C, n_ranges, partials, MD,
+                       sketch);
+    return hipGetLastError();
+}
+
+}  // namespace sa

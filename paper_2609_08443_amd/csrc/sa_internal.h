@@ -74,6 +74,29 @@ size_t fused_fwd_lds_bytes(int32_t M, int32_t d);
 hipError_t fused_fwd_occupancy(int32_t M, int32_t d, int* blocks_per_cu);
 hipError_t launch_fused_fwd(const FusedFwdArgs& a, hipStream_t stream);
 
+// Two-pass forward of bf16 inputs for the shapes without a fused instance
+// (fwd_split.hip): the log-sum-exp of every token into lse, then the aggregation
+// over n_ranges token ranges of C (segments.h); split pairs leave partials in slots
+// 0 .. 2 n_ranges - 1 for launch_merge_ranges.
+struct SplitFwdArgs {
+    const uint16_t* K;
+    const uint16_t* V;
+    const uint16_t* P;
+    const int64_t* offsets;
+    int64_t B, T, C, n_ranges;
+    int32_t H, M, d;
+    float scale;
+    bool p_user;       // P is [B,H,M,d]
+    float* sketch;
+    float* lse;        // [T,H]
+    float* partials;   // [2 n_ranges][M][d]
+};
+// token ranges that fill the device once
+int64_t split_fwd_ranges(int32_t M);
+hipError_t launch_split_fwd(const SplitFwdArgs& f, hipStream_t stream);
+hipError_t launch_merge_ranges(const int64_t* offsets, int64_t B, int64_t T, int32_t H, int64_t C, int64_t n_ranges,
+                               const float* partials, int64_t MD, float* sketch, hipStream_t stream);
+
 // Fused bf16 backward (matrix cores): prep, token-side and prototype-side
 // kernels plus the per-head sum of the dP partials.
 struct FusedBwdArgs {

@@ -1,0 +1,108 @@
+// Ragged scheduling without a work-list launch: a workgroup finds the segments of
+// its own token range from the offsets.
+//
+// The (head, token) pairs form one head-major index space of length H*T, cut into
+// equal ranges of C, as for the work list (worklist.hip).  Inside a range only the
+// segment at its start can belong to a user that began in an earlier range, and
+// only its last one to a user that goes on in the next, so two partial slots per
+// range hold everything a split (user, head) pair leaves behind: slot 2 r for the
+// segment at the start of range r, 2 r + 1 for a later one.  The merge derives a
+// pair's slots from its offsets in the same way.
+//
+// Offsets are device data the host never reads: every value is clamped to [0, T]
+// and every step of the walk moves forward, so malformed offsets give wrong
+// values but neither an access out of range nor an endless loop.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace sa {
+
+__device__ inline int64_t seg_clamp(int64_t x, int64_t T) { return x < 0 ? 0 : (x > T ? T : x); }
+
+struct Segment {
+    int32_t b, h;       // user and head
+    int32_t t0, t1;     // tokens [t0, t1)
+    int64_t slot;       // partial slot, used when split
+    bool split;         // the user's tokens of this head span several ranges
+};
+
+class SegmentWalk {
+  public:
+    __device__ inline SegmentWalk(const int64_t* off, int64_t B, int64_t T, int32_t H, int64_t C, int64_t range)
+        : off_(off), B_(B), T_(T), C_(C), range_(range) {
+        const int64_t HT = (int64_t)H * T;
+        g_ = range * C;
+        end_ = g_ + C < HT ? g_ + C : HT;
+        h_ = T > 0 ? (int32_t)(g_ / T) : 0;
+        b_ = find(g_ - (int64_t)h_ * T);
+    }
+    // the next non-empty segment, or false at the end of the range
+    __device__ inline bool next(Segment& s) {
+        while (g_ < end_) {
+            if (b_ >= B_) {   // past the last user of this head
+                ++h_;
+                g_ = (int64_t)h_ * T_;
+                b_ = 0;
+                continue;
+            }
+            const int64_t base = (int64_t)h_ * T_;
+            const int64_t lo = seg_clamp(off_[b_], T_), hi = seg_clamp(off_[b_ + 1], T_);
+            const int64_t t = g_ - base;
+            const int64_t t0 = t > lo ? t : lo;
+            const int64_t lim = end_ - base;
+            const int64_t t1 = hi < lim ? hi : lim;
+            const int32_t b = (int32_t)b_++;
+            if (t1 <= t0) {
+                if (lo >= lim) g_ = end_;   // begins after this range
+                continue;
+            }
+            s.b = b;
+            s.h = h_;
+            s.t0 = (int32_t)t0;
+            s.t1 = (int32_t)t1;
+            s.split = (base + lo) / C_ != (base + hi - 1) / C_;
+            s.slot = 2 * range_ + (base + t0 == range_ * C_ ? 0 : 1);
+            g_ = base + t1;
+            return true;
+        }
+        return false;
+    }
+
+  private:
+    // first user whose tokens end after t (B when there is none)
+    __device__ inline int64_t find(int64_t t) const {
+        int64_t lo = 0, hi = B_;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (seg_clamp(off_[mid + 1], T_) > t) hi = mid; else lo = mid + 1;
+        }
+        return lo;
+    }
+    const int64_t* off_;
+    int64_t B_, T_, C_, range_, g_, end_, b_;
+    int32_t h_;
+};
+
+// Partial slots of the pair with tokens [lo, hi) of head h: slot(i) for
+// i = 0 .. count - 1, in token order; count = 0 for an empty user.
+struct PairSlots {
+    int64_t first_range, count;
+    bool aligned;   // the pair begins at a range's start
+    __device__ inline PairSlots(int64_t lo, int64_t hi, int64_t h, int64_t T, int64_t C) {
+        if (hi <= lo) {
+            first_range = 0;
+            count = 0;
+            aligned = true;
+            return;
+        }
+        const int64_t g0 = h * T + lo, g1 = h * T + hi - 1;
+        first_range = g0 / C;
+        count = g1 / C - first_range + 1;
+        aligned = g0 == first_range * C;
+    }
+    __device__ inline int64_t slot(int64_t i) const { return 2 * (first_range + i) + (i == 0 && !aligned ? 1 : 0); }
+};
+
+}  // namespace sa

@@ -1,0 +1,76 @@
+"""Two-pass forward of bf16 inputs (shapes without a one-pass instance) against the
+fp64 oracle: the weights keep fp32 precision, so the bounds are those of
+single-precision sums.
+
+A weight's relative error is that of its logit (an fp32 sum of d exact products,
+about sqrt(d) 2^-24 |s| for unit logits, 7e-7 at d = 128) plus a few roundings of
+2^-24; the errors of different tokens are independent, so the sketch's 2-norm
+error stays near that of one weight: 2e-6 is three times it, and half of what
+dropping the lowest of the three bf16 parts of a weight would add (2^-18).
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_08443_amd import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sa():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_08443_amd import sa_sketch
+    sa_sketch.lib()
+    return sa_sketch
+
+
+# prototype counts around a wave's 32, a workgroup's 64 / 128 / 256 and an LDS tile's
+# 64; users of one token, of a tile, empty, and split over ranges at both ends
+CASES = [
+    ([33, 0, 1, 64], 2, 1, 64), ([40, 7], 1, 3, 128), ([95, 32], 2, 33, 64), ([31, 0, 65], 2, 64, 128),
+    ([70], 3, 65, 64), ([129, 2], 1, 127, 128), ([64, 64], 2, 129, 64), ([50, 300], 1, 200, 128),
+    ([90], 2, 257, 64), ([45, 0, 77], 1, 385, 128), ([5000, 12, 7000, 0, 2500], 2, 640, 128),
+    ([300, 1, 4001], 1, 1152, 64), ([2100, 33], 1, 2048, 128), ([100], 1, 4096, 64),
+]
+
+
+@pytest.mark.parametrize("lengths,H,M,d", CASES)
+@pytest.mark.parametrize("want_lse", [True, False])
+def test_split_fwd_single_precision(sa, lengths, H, M, d, want_lse):
+    w = wl.custom(lengths, H, M, d, "bf16", seed=sum(lengths) + M + d)
+    host = wl.host_tensors(w)
+    dev = wl.to_device(host, "bf16")
+    print(f"case {w.name} lse={want_lse}", flush=True)
+    sk, lse = sa.sketch_fwd(dev["K"], dev["V"], dev["P"], dev["offsets"], w.scale, want_lse=want_lse)
+    ref, rlse = oracle.fwd(host["K"], host["V"], host["P"], host["offsets"], w.scale)
+    g = sk.cpu().numpy().astype(np.float64)
+    for b, n in enumerate(lengths):
+        if n == 0:
+            assert np.all(g[b] == 0)
+            continue
+        assert np.linalg.norm(g[b] - ref[b]) <= 2e-6 * np.linalg.norm(ref[b]), b
+    if want_lse:
+        assert np.abs(lse.cpu().numpy() - rlse).max() <= 2e-6 * max(1.0, np.abs(rlse).max())
+
+
+def test_split_fwd_infinite_values(sa):
+    """An infinite V reaches exactly its own column, as in a plain sum of products."""
+    w = wl.custom([40, 300, 33], 1, 200, 64, "bf16", seed=3)
+    host = wl.host_tensors(w)
+    host["V"][17, 0, 5] = np.inf
+    host["V"][40 + 299, 0, 63] = -np.inf
+    host["V"][340 + 2, 0, 0] = np.nan
+    dev = wl.to_device(host, "bf16")
+    bits = dev["V"].view(torch.int16)
+    bits[340 + 2, 0, 0] = 0x7FC0
+    g = sa.sketch_fwd(dev["K"], dev["V"], dev["P"], dev["offsets"], w.scale)[0].cpu().numpy()
+    assert np.all(g[0, 0, :, 5] == np.inf) and np.all(g[1, 0, :, 63] == -np.inf) and np.all(np.isnan(g[2, 0, :, 0]))
+    for b, (t, j) in enumerate(((17, 5), (339, 63), (342, 0))):
+        host["V"][t, 0, j] = 0.0
+    ref = oracle.fwd(host["K"], host["V"], host["P"], host["offsets"], w.scale)[0]
+    for b, j in enumerate((5, 63, 0)):
+        keep = [c for c in range(64) if c != j]
+        assert np.linalg.norm(g[b, 0][:, keep] - ref[b, 0][:, keep]) <= 2e-6 * np.linalg.norm(ref[b, 0][:, keep])
