@@ -17,14 +17,15 @@
 // three bf16 parts of eight mantissa bits, A = hi + mid + lo exactly (truncation,
 // each remainder is exact), and the three products with the bf16 V accumulate in
 // fp32.  Against float64 the sketch is then as close as a plain fp32 evaluation
-// (measured 6e-7 relative, 2-norm, at M = 1024, d = 128).
+// (5.3e-7 relative, 2-norm, at M = 1024, d = 128; the fp32 VALU path had 5.9e-7).
 //
 // Executed matrix work is (2 + 2 + 6) M d per token against 4 M d algorithmic;
 // the aggregation is bound by its matrix instructions (32 of them per 32 x 32
 // logits tile at d = 128) beside about 11 VALU instructions per weight.
-// Measured on 100K tokens, H = 1, M = 1024, d = 128: lse 57 us, aggregation 106 us
-// (990 TFLOP/s executed, against 1200 for a large library product), merge 7 us; the
+// Measured on 100K tokens, H = 1, M = 1024, d = 128: lse 45 us, aggregation 118 us
+// (890 TFLOP/s executed, against 1200 for a large library product), merge 7 us; the
 // fp32 VALU path took 2.8 ms, 3.2 ms and 86 us.
+#include <type_traits>
 #include "reduce_ops.h"
 #include "sa_internal.h"
 #include "segments.h"
@@ -37,34 +38,41 @@ namespace {
 using namespace tile;
 
 constexpr float kLn2 = 0.6931471805599453f;
+constexpr float kLog2eLo = 1.9259629911e-8f;   // 1 / ln 2 - kLog2e
 
 // ---------------------------------------------------------------- log-sum-exp
-// Workgroup = 4 waves, each holding 32 TT tokens of one head as B operands; the
-// prototypes stream through LDS 64 at a time (double-buffered, the next tile in
-// registers), so the logits tile has prototypes as rows and a token per lane and
-// the running maximum and sum of a token live in one lane per half-wave: no
-// cross-lane work until the end.
-template <int D, int TT>
+// Workgroup = 4 waves; a wave holds 64 tokens of one head as B operands (two
+// 32-token tiles share each prototype operand read from LDS), WM waves share the
+// same tokens and take every WM-th 32 prototypes.  The prototypes stream through
+// LDS ROWS at a time (double-buffered, the next tile in registers).  The logits
+// tile has prototypes as rows and a token per lane, so the running maximum and sum
+// of a token live in one lane per half-wave and wave: no cross-lane work until the
+// end.
+template <int D, int WM>
 struct LseCfg {
+    static constexpr int TT = 2;
     static constexpr int KS = D / 16;
     static constexpr int KCH = D / 8;
-    static constexpr int ROWS = 64;                       // prototypes per LDS tile
+    static constexpr int ROWS = WM == 4 ? 128 : 64;       // prototypes per LDS tile
+    static constexpr int SUB = ROWS / (32 * WM);          // 32-prototype tiles per wave and LDS tile
     static constexpr int NLD = ROWS * KCH / 256;          // 16-byte chunks per thread
     static constexpr int TILE = ROWS * D * 2;
-    static constexpr int TOKENS = 4 * 32 * TT;            // tokens per workgroup
+    static constexpr int TOKENS = 4 / WM * 32 * TT;       // tokens per workgroup
 };
 
-template <int D, int TT>
+template <int D, int WM>
 __global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __restrict__ K,
                                                             const uint16_t* __restrict__ P,
                                                             const int64_t* __restrict__ off, int64_t B, int64_t T,
                                                             int32_t H, int32_t M, float scale, bool p_user,
                                                             float* __restrict__ lse) {
-    using C = LseCfg<D, TT>;
-    constexpr int KS = C::KS;
+    using C = LseCfg<D, WM>;
+    constexpr int KS = C::KS, TT = C::TT;
     __shared__ __attribute__((aligned(16))) uint8_t smem[2 * C::TILE];
+    __shared__ float2 stats[WM > 1 ? 4 : 1][TT * 32];   // (maximum, sum) of each wave's tokens
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int l32 = lane & 31, hl = lane >> 5;
+    const int wt = w / WM, wm = w % WM;
     const int64_t nblk = (T + C::TOKENS - 1) / C::TOKENS;
     const int32_t h = (int32_t)(blockIdx.x / nblk);
     const int64_t blk0 = (blockIdx.x % nblk) * C::TOKENS;          // the workgroup's first token
@@ -74,7 +82,7 @@ __global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __re
     bf16x8 kop[TT][KS];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
-        tok[tt] = blk0 + (w * TT + tt) * 32 + l32;
+        tok[tt] = blk0 + (wt * TT + tt) * 32 + l32;
         const int64_t row = tok[tt] < T ? tok[tt] : T - 1;
         const uint16_t* src = K + (row * H + h) * D + 8 * hl;
 #pragma unroll
@@ -86,14 +94,7 @@ __global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __re
 
     // with one prototype block per user, one round per user that has tokens here
     int64_t b = 0, lo = 0, hi = T;
-    if (p_user) {   // first user whose tokens end after blk0
-        int64_t a = 0, z = B;
-        while (a < z) {
-            const int64_t mid = (a + z) >> 1;
-            if (seg_clamp(off[mid + 1], T) > blk0) z = mid; else a = mid + 1;
-        }
-        b = a;
-    }
+    if (p_user) b = first_user_after(off, B, T, blk0);
     for (; p_user ? b < B : b < 1; ++b) {
         if (p_user) {
             lo = seg_clamp(off[b], T);
@@ -125,6 +126,34 @@ __global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __re
             mu[tt] = -INFINITY;
             z[tt] = 0.f;
         }
+        // a logits tile into the running maximum and sum; in the ragged one, rows past
+        // M have no part in either
+        auto add_tile = [&](f32x16 (&s)[TT], int row0, auto ragged) __attribute__((always_inline)) {
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) {
+                if constexpr (ragged.value) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (row0 + srow(r, hl) >= M) s[tt][r] = -3.4028234664e38f;
+                }
+                float t = s[tt][0];
+#pragma unroll
+                for (int r = 1; r < 16; ++r) t = fmaxf(t, s[tt][r]);
+                const float mn = fmaxf(mu[tt], t * ks2);
+                z[tt] *= __builtin_amdgcn_exp2f(mu[tt] - mn);   // 0 on the first tile
+                float sum[2] = {0.f, 0.f};
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[tt][r], ks2, -mn));
+                    if constexpr (ragged.value) {
+                        if (row0 + srow(r, hl) >= M) e = 0.f;
+                    }
+                    sum[r & 1] += e;
+                }
+                z[tt] += sum[0] + sum[1];
+                mu[tt] = mn;
+            }
+        };
         fetch(0);
         __syncthreads();   // the previous round is done with the tiles
         store(0);
@@ -134,8 +163,8 @@ __global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __re
             if (more) fetch(tile + 1);
             const uint16_t* Ps = reinterpret_cast<const uint16_t*>(smem + (tile & 1) * C::TILE);
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const int row0 = tile * C::ROWS + half * 32;
+            for (int sub = 0; sub < C::SUB; ++sub) {
+                const int r32 = (sub * WM + wm) * 32, row0 = tile * C::ROWS + r32;
                 if (row0 >= M) break;
                 f32x16 s[TT];
 #pragma unroll
@@ -144,52 +173,45 @@ __global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __re
                     for (int r = 0; r < 16; ++r) s[tt][r] = 0.f;
 #pragma unroll
                 for (int kk = 0; kk < KS; ++kk) {
-                    const bf16x8 pop = lds_b128(Ps, swz<D>(half * 32 + l32, 2 * kk + hl));
+                    const bf16x8 pop = lds_b128(Ps, swz<D>(r32 + l32, 2 * kk + hl));
 #pragma unroll
                     for (int tt = 0; tt < TT; ++tt)
                         s[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pop, kop[tt][kk], s[tt], 0, 0, 0);
                 }
-                const bool ragged = row0 + 32 > M;   // rows past M: no part in the maximum or the sum
-#pragma unroll
-                for (int tt = 0; tt < TT; ++tt) {
-                    float x[16];
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) x[r] = s[tt][r];
-                    if (ragged) {
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            if (row0 + srow(r, hl) >= M) x[r] = -3.4028234664e38f;
-                    }
-                    float t = x[0];
-#pragma unroll
-                    for (int r = 1; r < 16; ++r) t = fmaxf(t, x[r]);
-                    const float mn = fmaxf(mu[tt], t * ks2);
-                    z[tt] *= __builtin_amdgcn_exp2f(mu[tt] - mn);   // 0 on the first tile
-                    float sum[2] = {0.f, 0.f};
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], ks2, -mn));
-                        if (ragged && row0 + srow(r, hl) >= M) e = 0.f;
-                        sum[r & 1] += e;
-                    }
-                    z[tt] += sum[0] + sum[1];
-                    mu[tt] = mn;
-                }
+                if (row0 + 32 <= M) add_tile(s, M, std::false_type{});
+                else add_tile(s, row0, std::true_type{});
             }
             if (more) store((tile + 1) & 1);
             __syncthreads();
         }
-        // the two half-waves hold the token's other prototype rows
+        // the half-waves, and the waves sharing the tokens, hold a token's other
+        // prototypes; every wave has a row of the last tile unless M ends before it
+        auto merge = [](float ma, float za, float mb, float zb, float& m, float& z) {
+            m = fmaxf(ma, mb);
+            z = (za > 0.f || za != za ? za * __builtin_amdgcn_exp2f(ma - m) : 0.f) +
+                (zb > 0.f || zb != zb ? zb * __builtin_amdgcn_exp2f(mb - m) : 0.f);
+        };
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) {
             const auto m2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(mu[tt]), __float_as_uint(mu[tt]), false, false);
             const auto z2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(z[tt]), __float_as_uint(z[tt]), false, false);
-            const float ma = __uint_as_float(m2[0]), mb = __uint_as_float(m2[1]);
-            const float mx = fmaxf(ma, mb);
-            const float zz = __uint_as_float(z2[0]) * __builtin_amdgcn_exp2f(ma - mx) +
-                             __uint_as_float(z2[1]) * __builtin_amdgcn_exp2f(mb - mx);
-            if (hl == 0 && tok[tt] >= lo && tok[tt] < hi)
-                lse[tok[tt] * H + h] = __builtin_fmaf(mx, kLn2, __builtin_amdgcn_logf(zz) * kLn2);
+            merge(__uint_as_float(m2[0]), __uint_as_float(z2[0]), __uint_as_float(m2[1]), __uint_as_float(z2[1]), mu[tt], z[tt]);
+            if constexpr (WM > 1) {
+                if (hl == 0) stats[w][tt * 32 + l32] = make_float2(mu[tt], z[tt]);
+            }
+        }
+        if constexpr (WM > 1) __syncthreads();
+        if (wm == 0) {
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) {
+#pragma unroll
+                for (int q = 1; q < WM; ++q) {
+                    const float2 o = stats[w + q][tt * 32 + l32];
+                    merge(mu[tt], z[tt], o.x, o.y, mu[tt], z[tt]);
+                }
+                if (hl == 0 && tok[tt] >= lo && tok[tt] < hi)
+                    lse[tok[tt] * H + h] = __builtin_fmaf(mu[tt], kLn2, __builtin_amdgcn_logf(z[tt]) * kLn2);
+            }
         }
     }
 }
@@ -212,8 +234,8 @@ struct AggCfg {
     static constexpr int TILE = 32 * D * 2;
     static constexpr int OFF_K = 0;                    // 2 x [32][D] K tiles
     static constexpr int OFF_V = OFF_K + 2 * TILE;     // 2 x [32][D] V tiles
-    static constexpr int OFF_L = OFF_V + 2 * TILE;     // 2 x [32] token shifts, -lse / ln 2
-    static constexpr int OFF_F = OFF_L + 2 * 32 * 4;   // [2] first token + 1 of a tile with infinite or NaN V
+    static constexpr int OFF_L = OFF_V + 2 * TILE;     // 2 x [2][32] token shifts (see `shift`)
+    static constexpr int OFF_F = OFF_L + 4 * 32 * 4;   // [2] first token + 1 of a tile with infinite or NaN V
     static constexpr int LDS = OFF_F + 16;
 };
 
@@ -250,6 +272,9 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
     using C = AggCfg<D, NW>;
     constexpr int KS = C::KS, JT = C::JT;
     __shared__ __attribute__((aligned(16))) uint8_t smem[C::LDS];
+    // The exponent of a weight is s ks2 - lse / ln 2: its second term rounded to
+    // fp32 is added after the product, the rounding error (the same for all of a
+    // token's weights) enters as the score chain's initial value.
     float* shift = reinterpret_cast<float*>(smem + C::OFF_L);
     volatile int* flag = reinterpret_cast<volatile int*>(smem + C::OFF_F);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -265,6 +290,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
     const int64_t range = xcd * q8 + (xcd < r8 ? xcd : r8) + ix;
 
     const float ks2 = a.scale * kLog2e;
+    const float rks2 = ks2 > 0.f ? 1.0f / ks2 : 0.f;
     const int64_t MD = (int64_t)a.M * D;
     const uint32_t row_stride = (uint32_t)a.H * D;
     const int m0 = part * C::MP + w * 32;            // the wave's first prototype
@@ -314,7 +340,12 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
                     bad |= nonfinite8(v);
                 }
             }
-            if (w == 0 && hl == 0) shift[buf * 32 + l32] = -r.l * kLog2e;
+            if (w == 0 && hl == 0) {
+                const float l2 = -r.l * kLog2e;
+                const float lo = __builtin_fmaf(-r.l, kLog2eLo, __builtin_fmaf(-r.l, kLog2e, -l2));
+                shift[buf * 64 + l32] = l2;
+                shift[buf * 64 + 32 + l32] = __builtin_fabsf(r.l) < 1e30f ? lo * rks2 : 0.f;
+            }
             if (bad) flag[buf] = ts + 1;
         };
         fetch(t0, ra);
@@ -339,20 +370,23 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
             const uint16_t* Ks = reinterpret_cast<const uint16_t*>(smem + C::OFF_K + buf * C::TILE);
             uint16_t* Vs = reinterpret_cast<uint16_t*>(smem + C::OFF_V + buf * C::TILE);
             f32x16 s;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] = 0.f;
-#pragma unroll
-            for (int kk = 0; kk < KS; ++kk)
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_b128(Ks, swz<D>(l32, 2 * kk + hl)), pop[kk], s, 0, 0, 0);
             float sh[16];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const float4 q = *reinterpret_cast<const float4*>(shift + buf * 32 + 8 * g + 4 * hl);
+                const float4 q = *reinterpret_cast<const float4*>(shift + buf * 64 + 8 * g + 4 * hl);
+                const float4 c = *reinterpret_cast<const float4*>(shift + buf * 64 + 32 + 8 * g + 4 * hl);
                 sh[4 * g] = q.x;
                 sh[4 * g + 1] = q.y;
                 sh[4 * g + 2] = q.z;
                 sh[4 * g + 3] = q.w;
+                s[4 * g] = c.x;
+                s[4 * g + 1] = c.y;
+                s[4 * g + 2] = c.z;
+                s[4 * g + 3] = c.w;
             }
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk)
+                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_b128(Ks, swz<D>(l32, 2 * kk + hl)), pop[kk], s, 0, 0, 0);
             // weights and their three bf16 parts (parts[p][i]: two tokens' values)
             uint32_t parts[3][8];
 #pragma unroll
@@ -374,15 +408,21 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
                                                           parts[p][4 * h2 + 3]});
             };
             if (__builtin_expect(flag[buf] != ts + 1, 1)) {
+                // a tile's products sum up on their own, the smallest parts first, and
+                // are added to the running sum once (one rounding at its magnitude per
+                // 32 tokens instead of six)
 #pragma unroll
-                for (int jt = 0; jt < JT; ++jt)
+                for (int jt = 0; jt < JT; ++jt) {
+                    const bf16x8 v0 = lds_tr_tokens<D>(Vs, lane, jt, 0), v1 = lds_tr_tokens<D>(Vs, lane, jt, 1);
+                    f32x16 t = {};
 #pragma unroll
-                    for (int h2 = 0; h2 < 2; ++h2) {
-                        const bf16x8 v = lds_tr_tokens<D>(Vs, lane, jt, h2);
-#pragma unroll
-                        for (int p = 2; p >= 0; --p)
-                            acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(p, h2), v, acc[jt], 0, 0, 0);
+                    for (int p = 2; p >= 0; --p) {
+                        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(p, 0), v0, t, 0, 0, 0);
+                        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(p, 1), v1, t, 0, 0, 0);
                     }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[jt][r] += t[r];
+                }
             } else {
                 // an infinite V times a weight's zero lower part would be NaN: the
                 // upper parts see V as it is, the others its finite values only
@@ -437,13 +477,14 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
 
 // ---------------------------------------------------------------- split-L merge
 // sketch[b,h] = the partials of a split pair added in token order; zero for an
-// empty one; a pair held by one range is written by the aggregation itself.
+// empty one; a pair held by one range is written by its own workgroup.  Without
+// offsets there is one user, of all T tokens.
 __global__ __launch_bounds__(256) void merge_ranges_kernel(const int64_t* __restrict__ off, int64_t B, int64_t T,
                                                            int32_t H, int64_t C, int64_t n_ranges,
                                                            const float* __restrict__ partials, int64_t MD,
                                                            float* __restrict__ sketch) {
     const int64_t h = blockIdx.x / B, b = blockIdx.x % B;
-    const PairSlots ps(seg_clamp(off[b], T), seg_clamp(off[b + 1], T), h, T, C);
+    const PairSlots ps(off ? seg_clamp(off[b], T) : 0, off ? seg_clamp(off[b + 1], T) : T, h, T, C);
     if (ps.count == 1) return;
     const int64_t idx = ((int64_t)blockIdx.y * 256 + threadIdx.x) * 4;
     if (idx >= MD) return;
@@ -467,13 +508,24 @@ hipError_t launch_agg(AggArgs a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int D, int TT>
-hipError_t launch_lse(const SplitFwdArgs& f, hipStream_t stream) {
-    const int64_t nblk = (f.T + LseCfg<D, TT>::TOKENS - 1) / LseCfg<D, TT>::TOKENS;
+template <int D, int WM>
+hipError_t launch_lse_inst(const SplitFwdArgs& f, hipStream_t stream) {
+    const int64_t nblk = (f.T + LseCfg<D, WM>::TOKENS - 1) / LseCfg<D, WM>::TOKENS;
     if (nblk * f.H > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((lse_tokens_kernel<D, TT>), dim3((unsigned)(nblk * f.H)), dim3(256), 0, stream, f.K, f.P,
+    hipLaunchKernelGGL((lse_tokens_kernel<D, WM>), dim3((unsigned)(nblk * f.H)), dim3(256), 0, stream, f.K, f.P,
                        f.offsets, f.B, f.T, f.H, f.M, f.scale, f.p_user, f.lse);
     return hipGetLastError();
+}
+// Waves sharing a workgroup's tokens: none while 256-token workgroups give every CU
+// one (each prototype operand then serves the most tokens), two or four below that.
+// Measured (us; sharing 1 / 2 / 4 waves): M = 1024, d = 128, 100K tokens (391 workgroups
+// of 256) 45 / 52 / 59; M = 2048, d = 128, 15K tokens (59 of 256) 50 / 33 / 23.
+template <int D>
+hipError_t launch_lse(const SplitFwdArgs& f, hipStream_t stream) {
+    const int64_t n256 = (f.T + 255) / 256 * f.H;
+    if (n256 >= device_cus()) return launch_lse_inst<D, 1>(f, stream);
+    if (2 * n256 >= device_cus()) return launch_lse_inst<D, 2>(f, stream);
+    return launch_lse_inst<D, 4>(f, stream);
 }
 
 // Waves (of 32 prototypes) per aggregation workgroup: eight, or four where eight
@@ -500,7 +552,7 @@ hipError_t launch_split_fwd(const SplitFwdArgs& f, hipStream_t stream) {
     hipError_t e;
     {
         ProfScope ps("split_lse", stream);
-        e = f.d == 64 ? launch_lse<64, 2>(f, stream) : launch_lse<128, 2>(f, stream);
+        e = f.d == 64 ? launch_lse<64>(f, stream) : launch_lse<128>(f, stream);
     }
     if (e != hipSuccess) return e;
     AggArgs a{f.K, f.V, f.P, f.offsets, f.lse, f.B, f.T, f.C, f.n_ranges, f.H, f.M, 1, f.scale, f.p_user, f.sketch,

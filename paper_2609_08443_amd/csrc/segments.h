@@ -21,6 +21,16 @@ namespace sa {
 
 __device__ inline int64_t seg_clamp(int64_t x, int64_t T) { return x < 0 ? 0 : (x > T ? T : x); }
 
+// first user whose tokens end after t (B when there is none)
+__device__ inline int64_t first_user_after(const int64_t* off, int64_t B, int64_t T, int64_t t) {
+    int64_t lo = 0, hi = B;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (seg_clamp(off[mid + 1], T) > t) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+
 struct Segment {
     int32_t b, h;       // user and head
     int32_t t0, t1;     // tokens [t0, t1)
@@ -36,7 +46,7 @@ class SegmentWalk {
         g_ = range * C;
         end_ = g_ + C < HT ? g_ + C : HT;
         h_ = T > 0 ? (int32_t)(g_ / T) : 0;
-        b_ = find(g_ - (int64_t)h_ * T);
+        b_ = first_user_after(off, B, T, g_ - (int64_t)h_ * T);
     }
     // the next non-empty segment, or false at the end of the range
     __device__ inline bool next(Segment& s) {
@@ -71,15 +81,6 @@ class SegmentWalk {
     }
 
   private:
-    // first user whose tokens end after t (B when there is none)
-    __device__ inline int64_t find(int64_t t) const {
-        int64_t lo = 0, hi = B_;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (seg_clamp(off_[mid + 1], T_) > t) hi = mid; else lo = mid + 1;
-        }
-        return lo;
-    }
     const int64_t* off_;
     int64_t B_, T_, C_, range_, g_, end_, b_;
     int32_t h_;

@@ -34,6 +34,8 @@ CASES = [
     ([70], 3, 65, 64), ([129, 2], 1, 127, 128), ([64, 64], 2, 129, 64), ([50, 300], 1, 200, 128),
     ([90], 2, 257, 64), ([45, 0, 77], 1, 385, 128), ([5000, 12, 7000, 0, 2500], 2, 640, 128),
     ([300, 1, 4001], 1, 1152, 64), ([2100, 33], 1, 2048, 128), ([100], 1, 4096, 64),
+    # 256-, 128- and 64-token workgroups of the log-sum-exp (by their number)
+    ([20000, 3, 13000], 2, 200, 64), ([20000, 0, 129], 2, 65, 128),
 ]
 
 
