@@ -96,8 +96,7 @@ sa_status validate_offsets(const int64_t* offsets, int64_t B, int64_t T, hipStre
 
 // ---------------------------------------------------------------- forward plan
 struct FwdPlan {
-    bool fused = false;    // one-pass matrix-core forward on the work list
-    bool split = false;    // two-pass matrix-core forward (bf16 shapes without a fused instance)
+    bool fused = false;    // one-pass matrix-core forward on the work list, else two passes
     int64_t C = 0;         // tokens per workgroup range
     int64_t n_ranges = 0;  // workgroups
     int64_t max_items = 0;
@@ -117,41 +116,37 @@ int64_t fused_chunk_tokens(int64_t T, int32_t H, int32_t M, int32_t d) {
     return C;
 }
 
+// at most `target` ranges of whole token tiles
+void set_ranges(int64_t HT, int64_t target, int64_t* C, int64_t* n) {
+    const int64_t per = (HT + target - 1) / target;
+    *C = std::max<int64_t>(1, (per + sa::kTileTokens - 1) / sa::kTileTokens) * sa::kTileTokens;
+    *n = (HT + *C - 1) / *C;
+}
+
 FwdPlan plan_fwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype dtype,
                  bool need_lse_scratch) {
     FwdPlan p;
     p.fused = dtype == SA_BF16 && sa::fused_fwd_supported(M, d);
-    p.split = dtype == SA_BF16 && !p.fused;
     size_t off = 0;
     auto carve = [&](size_t bytes) {
         const size_t o = off;
         off = align_up(off + bytes, 256);
         return o;
     };
-    if (p.split) {
-        const int64_t target = sa::split_fwd_ranges(M), HT = (int64_t)H * T;
-        p.C = std::max<int64_t>(1, ((HT + target - 1) / target + sa::kTileTokens - 1) / sa::kTileTokens) * sa::kTileTokens;
-        p.n_ranges = (HT + p.C - 1) / p.C;
-        // a pair split over ranges has at most one slot per range it touches, two
-        // ranges' worth of slots cover them all (segments.h)
+    const int64_t HT = (int64_t)H * T;
+    if (!p.fused) {
+        // two passes over the keys (fwd_split.hip in bf16, fp32_path.hip in fp32): the
+        // head-major token space cut into equal ranges, two partial slots a range
+        const int64_t target = dtype == SA_BF16 ? sa::split_fwd_ranges(M) : sa::plain_fwd_ranges(M);
+        set_ranges(HT, target, &p.C, &p.n_ranges);
         p.off_partials = carve(sizeof(float) * 2 * (size_t)p.n_ranges * M * d);
         if (need_lse_scratch) p.off_lse = carve(sizeof(float) * (size_t)T * H);
         p.total = off;
         return p;
     }
-    // both paths cut the head-major token space into equal ranges (a work list
-    // of (user, head) segments, split pairs merged in segment order): the fused
-    // kernel runs one range per workgroup slot, the plain aggregation one range
-    // per 64 prototypes and about four workgroups per CU
-    const int64_t HT = (int64_t)H * T;
-    if (p.fused) {
-        p.C = fused_chunk_tokens(T, H, M, d);
-    } else {
-        const int64_t target = 4 * (int64_t)device_cus();
-        int64_t C = (HT + target - 1) / target;
-        C = (C + sa::kTileTokens - 1) / sa::kTileTokens * sa::kTileTokens;
-        p.C = C < sa::kTileTokens ? sa::kTileTokens : C;
-    }
+    // equal ranges of the head-major token space, one per workgroup slot (a work
+    // list of (user, head) segments, split pairs merged in segment order)
+    p.C = fused_chunk_tokens(T, H, M, d);
     p.n_ranges = (HT + p.C - 1) / p.C;
     p.max_items = p.n_ranges + (int64_t)H * B;
     p.off_nitems = carve(sizeof(int64_t));
@@ -159,7 +154,6 @@ FwdPlan plan_fwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype
     p.off_pairstart = carve(sizeof(int32_t) * ((int64_t)H * B + 1));
     p.off_items = carve(sizeof(int32_t) * sa::IT_WORDS * p.max_items);
     p.off_partials = carve(sizeof(float) * (size_t)p.max_items * M * d);
-    if (!p.fused && need_lse_scratch) p.off_lse = carve(sizeof(float) * (size_t)T * H);
     p.total = off;
     return p;
 }
@@ -205,7 +199,6 @@ TwPlan plan_tokenwise(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_
 // ---------------------------------------------------------------- backward plan
 struct BwdPlan {
     bool fused = false;
-    int32_t n_chunks = 1;
     int64_t C = 0, n_ranges = 0, max_items = 0;
     size_t off_dY = 0, off_D = 0, off_part = 0;
     size_t off_nitems = 0, off_wgstart = 0, off_pairstart = 0, off_items = 0, off_ymj = 0,
@@ -243,10 +236,10 @@ BwdPlan plan_bwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype
         p.off_D = carve(sizeof(float) * (size_t)T * H);
         p.off_part = carve(sizeof(float) * (size_t)p.max_items * M * d);
     } else {
-        p.n_chunks = sa::generic_dp_chunks(T, H, M);
+        set_ranges((int64_t)H * T, sa::plain_bwd_ranges(M, d), &p.C, &p.n_ranges);
         p.off_dY = carve(sizeof(float) * (size_t)B * H * M * d);
         p.off_D = carve(sizeof(float) * (size_t)T * H);
-        p.off_part = carve(sizeof(float) * (size_t)p.n_chunks * H * M * d);
+        p.off_part = carve(sizeof(float) * 2 * (size_t)p.n_ranges * M * d);
     }
     p.total = off;
     return p;
@@ -254,14 +247,14 @@ BwdPlan plan_bwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype
 
 // ---------------------------------------------------------------- SA layer plan
 // [Q fp32 | P' = Q W_K^T in the input dtype | (bwd) dP' fp32 | dQ fp32 |
-//  (bwd, plain path) dK, dV fp32 | workspace of the sketching call]
+//  workspace of the sketching call]
 struct LayerPlan {
-    size_t off_q = 0, off_pp = 0, off_dpp = 0, off_dq = 0, off_dk = 0, off_dv = 0, off_base = 0;
+    size_t off_q = 0, off_pp = 0, off_dpp = 0, off_dq = 0, off_base = 0;
     size_t total = 0;
 };
 
-LayerPlan plan_layer(int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype dtype, bool bwd,
-                     bool plain_bwd, size_t base_bytes) {
+LayerPlan plan_layer(int32_t H, int32_t M, int32_t d, sa_dtype dtype, bool bwd,
+                     size_t base_bytes) {
     LayerPlan p;
     size_t off = 0;
     auto carve = [&](size_t bytes) {
@@ -275,10 +268,6 @@ LayerPlan plan_layer(int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype dtype,
     if (bwd) {
         p.off_dpp = carve(sizeof(float) * hmd);
         p.off_dq = carve(sizeof(float) * hmd);
-        if (plain_bwd) {
-            p.off_dk = carve(sizeof(float) * (size_t)T * H * d);
-            p.off_dv = carve(sizeof(float) * (size_t)T * H * d);
-        }
     }
     p.off_base = carve(base_bytes);
     p.total = off;
@@ -371,7 +360,7 @@ struct BlockBwdPlan : BlockSaved {
     FwdPlan fwd;
     BwdPlan bshared, buser;
     size_t off_layers = 0, off_xhat = 0, off_z = 0, off_du = 0, off_dy2 = 0, off_dy1 = 0, off_dpp = 0,
-           off_dq = 0, off_stats = 0, off_colpart = 0, off_wpart = 0, off_dk = 0, off_dv = 0,
+           off_dq = 0, off_stats = 0, off_colpart = 0, off_wpart = 0,
            off_out = 0, off_base = 0, total = 0;
     int64_t nch = 1;
 };
@@ -403,10 +392,6 @@ BlockBwdPlan plan_block_bwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t 
     p.nch = std::max<int64_t>(1, std::min<int64_t>(B * M, (1024 + H - 1) / H));
     p.off_colpart = carve(f * (size_t)p.nch * H * 2 * d);
     p.off_wpart = carve(f * (size_t)B * H * 2 * d * d);
-    if (!p.bshared.fused) {
-        p.off_dk = carve(f * (size_t)T * H * d);
-        p.off_dv = carve(f * (size_t)T * H * d);
-    }
     p.off_out = carve(f * rd);
     p.off_base = carve(std::max({p.fwd.total, p.bshared.total, p.buser.total}));
     p.total = off;
@@ -625,7 +610,7 @@ sa_status run_fwd(const void* K, const void* V, const void* P, const int64_t* of
                   float* sketch, float* lse, uint8_t* ws, const FwdPlan& plan, hipStream_t stream,
                   bool p_user) {
     hipError_t e;
-    if (plan.split) {
+    if (!plan.fused) {
         sa::SplitFwdArgs f;
         f.K = reinterpret_cast<const uint16_t*>(K);
         f.V = reinterpret_cast<const uint16_t*>(V);
@@ -643,7 +628,7 @@ sa_status run_fwd(const void* K, const void* V, const void* P, const int64_t* of
         f.sketch = sketch;
         f.lse = lse ? lse : reinterpret_cast<float*>(ws + plan.off_lse);
         f.partials = reinterpret_cast<float*>(ws + plan.off_partials);
-        e = sa::launch_split_fwd(f, stream);
+        e = dtype == SA_BF16 ? sa::launch_split_fwd(f, stream) : sa::launch_plain_fwd(f, stream);
         if (e != hipSuccess) return hip_fail(e, "two-pass forward launch");
         sa::ProfScope ps("splitL_merge", stream);
         e = sa::launch_merge_ranges(offsets, B, T, H, plan.C, plan.n_ranges, f.partials, (int64_t)M * d, sketch, stream);
@@ -661,54 +646,33 @@ sa_status run_fwd(const void* K, const void* V, const void* P, const int64_t* of
                                 pair_start, n_items, stream);
     }
     if (e != hipSuccess) return hip_fail(e, "work list launch");
-    if (plan.fused) {
-        sa::FusedFwdArgs a;
-        a.K = reinterpret_cast<const uint16_t*>(K);
-        a.V = reinterpret_cast<const uint16_t*>(V);
-        a.P = reinterpret_cast<const uint16_t*>(P);
-        a.items = items;
-        a.wg_start = wg_start;
-        a.n_ranges = plan.n_ranges;
-        a.max_items = plan.max_items;
-        a.T = T;
-        a.B = (int32_t)B;
-        a.H = H;
-        a.M = M;
-        a.d = d;
-        a.scale = scale;
-        a.sketch = sketch;
-        a.lse = lse;
-        a.partials = partials;
-        a.p_user = p_user;
-        {
-            sa::ProfScope ps("fused_fwd", stream);
-            e = sa::launch_fused_fwd(a, stream);
-        }
-        if (e != hipSuccess) return hip_fail(e, "fused forward launch");
-        {
-            sa::ProfScope ps("splitL_merge", stream);
-            e = sa::launch_merge(pair_start, B, H, plan.max_items, partials, (int64_t)M * d,
-                                 sketch, stream);
-        }
-        if (e != hipSuccess) return hip_fail(e, "split-L merge launch");
-        return SA_OK;
-    }
-    float* lse_out = lse ? lse : reinterpret_cast<float*>(ws + plan.off_lse);
+    sa::FusedFwdArgs a;
+    a.K = reinterpret_cast<const uint16_t*>(K);
+    a.V = reinterpret_cast<const uint16_t*>(V);
+    a.P = reinterpret_cast<const uint16_t*>(P);
+    a.items = items;
+    a.wg_start = wg_start;
+    a.n_ranges = plan.n_ranges;
+    a.max_items = plan.max_items;
+    a.T = T;
+    a.B = (int32_t)B;
+    a.H = H;
+    a.M = M;
+    a.d = d;
+    a.scale = scale;
+    a.sketch = sketch;
+    a.lse = lse;
+    a.partials = partials;
+    a.p_user = p_user;
     {
-        sa::ProfScope ps("plain_fwd", stream);
-        sa::GenericFwdItems wi;
-        wi.items = items;
-        wi.wg_start = wg_start;
-        wi.n_ranges = plan.n_ranges;
-        wi.max_items = plan.max_items;
-        wi.partials = partials;
-        e = sa::launch_generic_fwd(K, V, P, offsets, B, T, H, M, d, scale, dtype == SA_BF16, sketch, lse_out, wi,
-                                   stream, p_user);
+        sa::ProfScope ps("fused_fwd", stream);
+        e = sa::launch_fused_fwd(a, stream);
     }
-    if (e != hipSuccess) return hip_fail(e, "fp32 forward launch");
+    if (e != hipSuccess) return hip_fail(e, "fused forward launch");
     {
         sa::ProfScope ps("splitL_merge", stream);
-        e = sa::launch_merge(pair_start, B, H, plan.max_items, partials, (int64_t)M * d, sketch, stream);
+        e = sa::launch_merge(pair_start, B, H, plan.max_items, partials, (int64_t)M * d,
+                             sketch, stream);
     }
     if (e != hipSuccess) return hip_fail(e, "split-L merge launch");
     return SA_OK;
@@ -717,8 +681,7 @@ sa_status run_fwd(const void* K, const void* V, const void* P, const int64_t* of
 
 // backward on a checked plan and workspace.  With dX non-null, K and V are the
 // same tensor X and the gradient w.r.t. it, dX = dK + dV, is written (added to dX
-// with dx_add) instead of dK and dV (the plain path still needs dK and dV as
-// scratch).
+// with dx_add) instead of dK and dV.
 sa_status run_bwd(const void* K, const void* V, const void* P, const int64_t* offsets, int64_t B,
                   int64_t T, int32_t H, int32_t M, int32_t d, float scale, sa_dtype dtype,
                   const float* dsketch, int32_t R, const float* lse, float* dK, float* dV,
@@ -771,23 +734,36 @@ sa_status run_bwd(const void* K, const void* V, const void* P, const int64_t* of
         if (e != hipSuccess) return hip_fail(e, "fused backward launch");
         return SA_OK;
     }
-    {
+    if (R > 1) {
         sa::ProfScope ps("dY_reduce", stream);
         e = sa::launch_dy_reduce(dsketch, B, R, H, (int64_t)M * d, dY, stream);
+        if (e != hipSuccess) return hip_fail(e, "dY reduce launch");
     }
-    if (e != hipSuccess) return hip_fail(e, "dY reduce launch");
-    {
-        sa::ProfScope ps("plain_bwd", stream);
-        e = sa::launch_generic_bwd(K, V, P, offsets, B, T, H, M, d, scale, dtype == SA_BF16, dY,
-                                   lse, Dbuf, dK, dV, dP, part, plan.n_chunks, stream, p_user);
-    }
+    sa::PlainBwdArgs f;
+    f.K = K;
+    f.V = V;
+    f.P = P;
+    f.offsets = offsets;
+    f.dY = R > 1 ? dY : dsketch;
+    f.lse = lse;
+    f.B = B;
+    f.T = T;
+    f.C = plan.C;
+    f.n_ranges = plan.n_ranges;
+    f.H = H;
+    f.M = M;
+    f.d = d;
+    f.scale = scale;
+    f.p_user = p_user;
+    f.dx_add = dx_add;
+    f.Dbuf = Dbuf;
+    f.dK = dK;
+    f.dV = dV;
+    f.dX = dX;
+    f.dP = dP;
+    f.partials = part;
+    e = sa::launch_plain_bwd(f, dtype == SA_BF16, stream);
     if (e != hipSuccess) return hip_fail(e, "backward launch");
-    if (dX) {
-        sa::ProfScope ps("dX_sum", stream);
-        e = sa::launch_add(dK, dV, dx_add ? dK : dX, T * H * d, stream);
-        if (e == hipSuccess && dx_add) e = sa::launch_add(dX, dK, dX, T * H * d, stream);
-        if (e != hipSuccess) return hip_fail(e, "dX sum launch");
-    }
     return SA_OK;
 }
 
@@ -1055,7 +1031,7 @@ sa_status sa_sketch_bwd(const void* K, const void* V, const void* P, const int64
 size_t sa_layer_fwd_workspace_size(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d,
                                    sa_dtype dtype) {
     if (check_common(B, T, H, M, d, 1.0f, dtype) != SA_OK) return 0;
-    return plan_layer(T, H, M, d, dtype, false, false, plan_fwd(B, T, H, M, d, dtype, true).total)
+    return plan_layer(H, M, d, dtype, false, plan_fwd(B, T, H, M, d, dtype, true).total)
         .total;
 }
 
@@ -1074,7 +1050,7 @@ sa_status sa_layer_fwd(const void* X, const void* P, const void* Wq, const void*
         return fail(SA_ERR_INVALID_ARG, "X, P, W_Q, W_K, sketch and lse must be 16-byte aligned");
     hipStream_t stream = reinterpret_cast<hipStream_t>(stream_);
     const FwdPlan base = plan_fwd(B, T, H, M, d, dtype, lse == nullptr);
-    const LayerPlan plan = plan_layer(T, H, M, d, dtype, false, false, base.total);
+    const LayerPlan plan = plan_layer(H, M, d, dtype, false, base.total);
     if (!workspace || workspace_bytes < plan.total)
         return fail(SA_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", plan.total,
                     workspace ? workspace_bytes : (size_t)0);
@@ -1095,7 +1071,7 @@ size_t sa_layer_bwd_workspace_size(int64_t B, int64_t T, int32_t H, int32_t M, i
                                    sa_dtype dtype, int32_t R) {
     if (check_common(B, T, H, M, d, 1.0f, dtype) != SA_OK || R < 1) return 0;
     const BwdPlan base = plan_bwd(B, T, H, M, d, dtype);
-    return plan_layer(T, H, M, d, dtype, true, !base.fused, base.total).total;
+    return plan_layer(H, M, d, dtype, true, base.total).total;
 }
 
 sa_status sa_layer_bwd(const void* X, const void* P, const void* Wq, const void* Wk,
@@ -1115,7 +1091,7 @@ sa_status sa_layer_bwd(const void* X, const void* P, const void* Wq, const void*
         return fail(SA_ERR_INVALID_ARG, "tensor arguments must be 16-byte aligned");
     hipStream_t stream = reinterpret_cast<hipStream_t>(stream_);
     const BwdPlan base = plan_bwd(B, T, H, M, d, dtype);
-    const LayerPlan plan = plan_layer(T, H, M, d, dtype, true, !base.fused, base.total);
+    const LayerPlan plan = plan_layer(H, M, d, dtype, true, base.total);
     if (!workspace || workspace_bytes < plan.total)
         return fail(SA_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", plan.total,
                     workspace ? workspace_bytes : (size_t)0);
@@ -1130,9 +1106,7 @@ sa_status sa_layer_bwd(const void* X, const void* P, const void* Wq, const void*
     float* dQ = reinterpret_cast<float*>(ws + plan.off_dq);
     st = layer_prototypes(P, Wq, Wk, H, M, d, dtype, Q, Pp, stream);
     if (st != SA_OK) return st;
-    float* dKs = base.fused ? nullptr : reinterpret_cast<float*>(ws + plan.off_dk);
-    float* dVs = base.fused ? nullptr : reinterpret_cast<float*>(ws + plan.off_dv);
-    st = run_bwd(X, X, Pp, offsets, B, T, H, M, d, scale, dtype, dsketch, R, lse, dKs, dVs, dPp, dX,
+    st = run_bwd(X, X, Pp, offsets, B, T, H, M, d, scale, dtype, dsketch, R, lse, nullptr, nullptr, dPp, dX,
                  ws + plan.off_base, base, stream);
     if (st != SA_OK) return st;
     // dW_K = dP'^T Q, dQ = dP' W_K, dW_Q = P^T dQ, dP = dQ W_Q^T
@@ -1369,9 +1343,7 @@ sa_status sa_block_bwd(const void* X, const void* P, const void* Wq, const void*
         // the sketch (dsketch = dY1, one target instance): dX of this layer (the
         // last layer writes dX, the others add to it) and dP'
         if (T > 0) {
-            float* dKs = plan.bshared.fused ? nullptr : F(plan.off_dk);
-            float* dVs = plan.bshared.fused ? nullptr : F(plan.off_dv);
-            st = run_bwd(X, X, io.Pp, offsets, B, T, H, M, d, scale, dtype, dY1, 1, io.lse, dKs, dVs, dPp, dX,
+            st = run_bwd(X, X, io.Pp, offsets, B, T, H, M, d, scale, dtype, dY1, 1, io.lse, nullptr, nullptr, dPp, dX,
                          ws + plan.off_base, io.first ? plan.bshared : plan.buser, stream, !io.first,
                          l != n_layers - 1);
             if (st != SA_OK) return st;

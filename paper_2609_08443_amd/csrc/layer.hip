@@ -16,8 +16,7 @@
 // backward and dX = dV + scale dS P' from its token side.
 //
 // This file holds the small batched product used for those six [M|d] x d
-// matrices (fp32 accumulation, strided operands so that transposes are free)
-// and the elementwise sum of the plain path's dK and dV.
+// matrices (fp32 accumulation, strided operands so that transposes are free).
 #include "sa_internal.h"
 #include "tile_ops.h"
 
@@ -124,15 +123,6 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(const TA* __restrict__ 
     }
 }
 
-__global__ __launch_bounds__(256) void add_kernel(const float* __restrict__ a, const float* __restrict__ b,
-                                                  float* __restrict__ out, int64_t n4) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n4) return;
-    const float4 x = reinterpret_cast<const float4*>(a)[i];
-    const float4 y = reinterpret_cast<const float4*>(b)[i];
-    reinterpret_cast<float4*>(out)[i] = make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
-}
-
 template <typename TA, typename TB, typename TC>
 hipError_t gemm_t(const MatView& a, const MatView& b, int32_t b_mod, void* c, int64_t c_h, int64_t c_r, int32_t H,
                   int32_t R, int32_t N, int32_t Kd, float alpha, bool accumulate, hipStream_t stream) {
@@ -171,13 +161,6 @@ hipError_t launch_small_gemm_general(const GemmDesc& d, hipStream_t stream) {
     return small_gemm_dispatch({d.A, d.a_bf16, d.a_z, d.a_m, d.a_k}, {d.B, d.b_bf16, d.b_z, d.b_k, d.b_n}, d.C,
                                d.c_bf16, d.c_z, d.c_m, d.batch, d.M, d.N, d.K, d.b_mod > 0 ? (int32_t)d.b_mod : d.batch,
                                d.alpha, d.accumulate, stream);
-}
-
-hipError_t launch_add(const float* a, const float* b, float* out, int64_t n, hipStream_t stream) {
-    if (n <= 0) return hipSuccess;
-    const int64_t n4 = n / 4;   // n is a multiple of d (64 or 128)
-    hipLaunchKernelGGL(add_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream, a, b, out, n4);
-    return hipGetLastError();
 }
 
 }  // namespace sa

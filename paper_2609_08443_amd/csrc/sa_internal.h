@@ -95,7 +95,7 @@ struct SplitFwdArgs {
 int64_t split_fwd_ranges(int32_t M);
 hipError_t launch_split_fwd(const SplitFwdArgs& f, hipStream_t stream);
 hipError_t launch_merge_ranges(const int64_t* offsets, int64_t B, int64_t T, int32_t H, int64_t C, int64_t n_ranges,
-                               const float* partials, int64_t MD, float* sketch, hipStream_t stream);
+                               const float* partials, int64_t MD, float* sketch, hipStream_t stream);  // offsets null: one user of T tokens
 
 // Fused bf16 backward (matrix cores): prep, token-side and prototype-side
 // kernels plus the per-head sum of the dP partials.
@@ -236,35 +236,31 @@ hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t stream);
 // out[h][i] = sum over b, in order, of part[b * H + h][i], i < n (fp32)
 hipError_t launch_sum_users(const float* part, int64_t B, int32_t H, int64_t n, float* out, hipStream_t stream);
 
-// out = a + b elementwise (n fp32 values, n a multiple of 4, 16-byte aligned)
-hipError_t launch_add(const float* a, const float* b, float* out, int64_t n, hipStream_t stream);
-
-// Plain fp32-arithmetic path (fp32 or bf16 inputs).
-// Work list of the plain forward's aggregation (the fused forward's format:
-// items and per-range starts from launch_worklist) and the partial sketches of
-// (user, head) pairs split across ranges, merged by launch_merge.
-struct GenericFwdItems {
-    const int32_t* items = nullptr;
-    const int32_t* wg_start = nullptr;
-    int64_t n_ranges = 0, max_items = 0;
-    float* partials = nullptr;
-};
-hipError_t launch_generic_fwd(const void* K, const void* V, const void* P, const int64_t* off, int64_t B,
-                              int64_t T, int32_t H, int32_t M, int32_t d, float scale, bool bf16, float* sketch,
-                              float* lse_out, const GenericFwdItems& w, hipStream_t stream, bool p_user);
+// Single-precision path on the fp32 matrix cores (fp32_path.hip): the forward of
+// fp32 inputs (K, V, P of SplitFwdArgs point to fp32 values), and the backward of
+// fp32 inputs and of the bf16 shapes without a fused instance.
+// token ranges that fill the device once (forward; backward, prototype side)
+int64_t plain_fwd_ranges(int32_t M);
+int64_t plain_bwd_ranges(int32_t M, int32_t d);
+hipError_t launch_plain_fwd(const SplitFwdArgs& f, hipStream_t stream);
 
 // dY[b,h] = sum_r dsketch[b,r,h]  (fp32, [B,H,M,d])
 hipError_t launch_dy_reduce(const float* dsketch, int64_t B, int32_t R, int32_t H, int64_t MD,
                             float* dY, hipStream_t stream);
 
-hipError_t launch_generic_bwd(const void* K, const void* V, const void* P,
-                              const int64_t* offsets, int64_t B, int64_t T, int32_t H,
-                              int32_t M, int32_t d, float scale, bool bf16, const float* dY,
-                              const float* lse, float* Dbuf, float* dK, float* dV, float* dP,
-                              float* dp_partials, int32_t n_chunks, hipStream_t stream,
-                              bool p_user = false);
-
-// number of token chunks the generic dP kernel uses (sizes its partial buffer)
-int32_t generic_dp_chunks(int64_t T, int32_t H, int32_t M);
+struct PlainBwdArgs {
+    const void *K, *V, *P;
+    const int64_t* offsets;
+    const float *dY, *lse;   // [B,H,M,d], [T,H]
+    int64_t B, T, C, n_ranges;   // token ranges of the prototype side (segments.h)
+    int32_t H, M, d;
+    float scale;
+    bool p_user;             // P is [B,H,M,d] and dP each pair's gradient
+    bool dx_add;             // with dX: add to it
+    float* Dbuf;             // [T,H]
+    float *dK, *dV, *dX, *dP;   // dX non-null: K = V, its gradient goes there (dK, dV unused)
+    float* partials;         // [2 n_ranges][M][d]
+};
+hipError_t launch_plain_bwd(const PlainBwdArgs& f, bool bf16, hipStream_t stream);
 
 }  // namespace sa
