@@ -96,13 +96,11 @@ sa_status validate_offsets(const int64_t* offsets, int64_t B, int64_t T, hipStre
 
 // ---------------------------------------------------------------- forward plan
 struct FwdPlan {
-    bool fused = false;    // one-pass matrix-core forward on the work list, else two passes
+    bool fused = false;    // one-pass matrix-core forward, else two passes over the keys
     int64_t C = 0;         // tokens per workgroup range
     int64_t n_ranges = 0;  // workgroups
-    int64_t max_items = 0;
     // workspace offsets (bytes)
-    size_t off_nitems = 0, off_wgstart = 0, off_pairstart = 0, off_items = 0, off_partials = 0,
-           off_lse = 0, total = 0;
+    size_t off_partials = 0, off_lse = 0, total = 0;
 };
 
 int64_t fused_chunk_tokens(int64_t T, int32_t H, int32_t M, int32_t d) {
@@ -134,26 +132,17 @@ FwdPlan plan_fwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype
         return o;
     };
     const int64_t HT = (int64_t)H * T;
-    if (!p.fused) {
-        // two passes over the keys (fwd_split.hip in bf16, fp32_path.hip in fp32): the
-        // head-major token space cut into equal ranges, two partial slots a range
-        const int64_t target = dtype == SA_BF16 ? sa::split_fwd_ranges(M) : sa::plain_fwd_ranges(M);
-        set_ranges(HT, target, &p.C, &p.n_ranges);
-        p.off_partials = carve(sizeof(float) * 2 * (size_t)p.n_ranges * M * d);
-        if (need_lse_scratch) p.off_lse = carve(sizeof(float) * (size_t)T * H);
-        p.total = off;
-        return p;
+    // the head-major token space in equal ranges: one per workgroup slot of the
+    // one-pass kernel, or as many as fill the device with the aggregation's
+    // prototype parts; partial slots as in segments.h
+    if (p.fused) {
+        p.C = fused_chunk_tokens(T, H, M, d);
+        p.n_ranges = (HT + p.C - 1) / p.C;
+    } else {
+        set_ranges(HT, dtype == SA_BF16 ? sa::split_fwd_ranges(M) : sa::plain_fwd_ranges(M), &p.C, &p.n_ranges);
     }
-    // equal ranges of the head-major token space, one per workgroup slot (a work
-    // list of (user, head) segments, split pairs merged in segment order)
-    p.C = fused_chunk_tokens(T, H, M, d);
-    p.n_ranges = (HT + p.C - 1) / p.C;
-    p.max_items = p.n_ranges + (int64_t)H * B;
-    p.off_nitems = carve(sizeof(int64_t));
-    p.off_wgstart = carve(sizeof(int32_t) * (p.n_ranges + 1));
-    p.off_pairstart = carve(sizeof(int32_t) * ((int64_t)H * B + 1));
-    p.off_items = carve(sizeof(int32_t) * sa::IT_WORDS * p.max_items);
-    p.off_partials = carve(sizeof(float) * (size_t)p.max_items * M * d);
+    p.off_partials = carve(sizeof(float) * (size_t)(p.n_ranges + H * B) * M * d);
+    if (!p.fused && need_lse_scratch) p.off_lse = carve(sizeof(float) * (size_t)T * H);
     p.total = off;
     return p;
 }
@@ -161,9 +150,8 @@ FwdPlan plan_fwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype
 // ---------------------------------------------------------------- token-wise plan
 struct TwPlan {
     bool fused = false;
-    int64_t C = 0, n_ranges = 0, max_items = 0;
-    size_t off_nitems = 0, off_wgstart = 0, off_pairstart = 0, off_items = 0, off_partials = 0,
-           off_stats = 0, total = 0;
+    int64_t C = 0, n_ranges = 0;
+    size_t off_partials = 0, off_stats = 0, total = 0;
 };
 
 TwPlan plan_tokenwise(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype dtype) {
@@ -177,20 +165,9 @@ TwPlan plan_tokenwise(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_
     };
     if (p.fused) {
         // one range per CU; each range runs M / (prototypes per workgroup) workgroups
-        const int64_t HT = (int64_t)H * T;
-        const int64_t target = device_cus();
-        int64_t C = (HT + target - 1) / target;
-        C = (C + sa::kTileTokens - 1) / sa::kTileTokens * sa::kTileTokens;
-        if (C < sa::kTileTokens) C = sa::kTileTokens;
-        p.C = C;
-        p.n_ranges = (HT + C - 1) / C;
-        p.max_items = p.n_ranges + (int64_t)H * B;
-        p.off_nitems = carve(sizeof(int64_t));
-        p.off_wgstart = carve(sizeof(int32_t) * (p.n_ranges + 1));
-        p.off_pairstart = carve(sizeof(int32_t) * ((int64_t)H * B + 1));
-        p.off_items = carve(sizeof(int32_t) * sa::IT_WORDS * p.max_items);
-        p.off_partials = carve(sizeof(float) * (size_t)p.max_items * M * d);
-        p.off_stats = carve(sizeof(float) * (size_t)p.max_items * M * 2);
+        set_ranges((int64_t)H * T, device_cus(), &p.C, &p.n_ranges);
+        p.off_partials = carve(sizeof(float) * (size_t)(p.n_ranges + H * B) * M * d);
+        p.off_stats = carve(sizeof(float) * 2 * (size_t)(p.n_ranges + H * B) * M);
     }
     p.total = off;
     return p;
@@ -239,7 +216,7 @@ BwdPlan plan_bwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype
         set_ranges((int64_t)H * T, sa::plain_bwd_ranges(M, d), &p.C, &p.n_ranges);
         p.off_dY = carve(sizeof(float) * (size_t)B * H * M * d);
         p.off_D = carve(sizeof(float) * (size_t)T * H);
-        p.off_part = carve(sizeof(float) * 2 * (size_t)p.n_ranges * M * d);
+        p.off_part = carve(sizeof(float) * (size_t)(p.n_ranges + H * B) * M * d);
     }
     p.total = off;
     return p;
@@ -610,6 +587,7 @@ sa_status run_fwd(const void* K, const void* V, const void* P, const int64_t* of
                   float* sketch, float* lse, uint8_t* ws, const FwdPlan& plan, hipStream_t stream,
                   bool p_user) {
     hipError_t e;
+    float* partials = reinterpret_cast<float*>(ws + plan.off_partials);
     if (!plan.fused) {
         sa::SplitFwdArgs f;
         f.K = reinterpret_cast<const uint16_t*>(K);
@@ -627,35 +605,23 @@ sa_status run_fwd(const void* K, const void* V, const void* P, const int64_t* of
         f.p_user = p_user;
         f.sketch = sketch;
         f.lse = lse ? lse : reinterpret_cast<float*>(ws + plan.off_lse);
-        f.partials = reinterpret_cast<float*>(ws + plan.off_partials);
+        f.partials = partials;
         e = dtype == SA_BF16 ? sa::launch_split_fwd(f, stream) : sa::launch_plain_fwd(f, stream);
         if (e != hipSuccess) return hip_fail(e, "two-pass forward launch");
         sa::ProfScope ps("splitL_merge", stream);
-        e = sa::launch_merge_ranges(offsets, B, T, H, plan.C, plan.n_ranges, f.partials, (int64_t)M * d, sketch, stream);
+        e = sa::launch_merge_ranges(offsets, B, T, H, plan.C, plan.n_ranges, partials, (int64_t)M * d, sketch, stream);
         if (e != hipSuccess) return hip_fail(e, "split-L merge launch");
         return SA_OK;
     }
-    int32_t* items = reinterpret_cast<int32_t*>(ws + plan.off_items);
-    int32_t* wg_start = reinterpret_cast<int32_t*>(ws + plan.off_wgstart);
-    int32_t* pair_start = reinterpret_cast<int32_t*>(ws + plan.off_pairstart);
-    int64_t* n_items = reinterpret_cast<int64_t*>(ws + plan.off_nitems);
-    float* partials = reinterpret_cast<float*>(ws + plan.off_partials);
-    {
-        sa::ProfScope ps("worklist", stream);
-        e = sa::launch_worklist(offsets, B, T, H, plan.C, plan.n_ranges, items, plan.max_items, wg_start,
-                                pair_start, n_items, stream);
-    }
-    if (e != hipSuccess) return hip_fail(e, "work list launch");
     sa::FusedFwdArgs a;
     a.K = reinterpret_cast<const uint16_t*>(K);
     a.V = reinterpret_cast<const uint16_t*>(V);
     a.P = reinterpret_cast<const uint16_t*>(P);
-    a.items = items;
-    a.wg_start = wg_start;
-    a.n_ranges = plan.n_ranges;
-    a.max_items = plan.max_items;
+    a.offsets = offsets;
+    a.B = B;
     a.T = T;
-    a.B = (int32_t)B;
+    a.C = plan.C;
+    a.n_ranges = plan.n_ranges;
     a.H = H;
     a.M = M;
     a.d = d;
@@ -669,11 +635,8 @@ sa_status run_fwd(const void* K, const void* V, const void* P, const int64_t* of
         e = sa::launch_fused_fwd(a, stream);
     }
     if (e != hipSuccess) return hip_fail(e, "fused forward launch");
-    {
-        sa::ProfScope ps("splitL_merge", stream);
-        e = sa::launch_merge(pair_start, B, H, plan.max_items, partials, (int64_t)M * d,
-                             sketch, stream);
-    }
+    sa::ProfScope ps("splitL_merge", stream);
+    e = sa::launch_merge_ranges(offsets, B, T, H, plan.C, plan.n_ranges, partials, (int64_t)M * d, sketch, stream);
     if (e != hipSuccess) return hip_fail(e, "split-L merge launch");
     return SA_OK;
 }
@@ -958,29 +921,31 @@ sa_status sa_sketch_fwd_tokenwise(const void* K, const void* V, const void* P,
     hipError_t e;
     if (plan.fused) {
         uint8_t* ws = reinterpret_cast<uint8_t*>(workspace);
-        int32_t* items = reinterpret_cast<int32_t*>(ws + plan.off_items);
-        int32_t* wg_start = reinterpret_cast<int32_t*>(ws + plan.off_wgstart);
-        int32_t* pair_start = reinterpret_cast<int32_t*>(ws + plan.off_pairstart);
-        int64_t* n_items = reinterpret_cast<int64_t*>(ws + plan.off_nitems);
-        float* partials = reinterpret_cast<float*>(ws + plan.off_partials);
-        float* stats = reinterpret_cast<float*>(ws + plan.off_stats);
-        {
-            sa::ProfScope ps("worklist", stream);
-            e = sa::launch_worklist(offsets, B, T, H, plan.C, plan.n_ranges, items,
-                                    plan.max_items, wg_start, pair_start, n_items, stream);
-        }
-        if (e != hipSuccess) return hip_fail(e, "work list launch");
+        sa::TokenwiseArgs f;
+        f.K = K;
+        f.V = V;
+        f.P = P;
+        f.offsets = offsets;
+        f.B = B;
+        f.T = T;
+        f.C = plan.C;
+        f.n_ranges = plan.n_ranges;
+        f.H = H;
+        f.M = M;
+        f.d = d;
+        f.scale = scale;
+        f.sketch = sketch;
+        f.lse_m = lse_m;
+        f.partials = reinterpret_cast<float*>(ws + plan.off_partials);
+        f.stats = reinterpret_cast<float*>(ws + plan.off_stats);
         {
             sa::ProfScope ps("tokenwise_fwd", stream);
-            e = sa::launch_tokenwise_fused(items, wg_start, plan.n_ranges, plan.max_items, K, V, P,
-                                           B, T, H, M, d, scale, sketch, lse_m, partials, stats,
-                                           stream);
+            e = sa::launch_tokenwise_fused(f, stream);
         }
         if (e != hipSuccess) return hip_fail(e, "token-wise forward launch");
         {
             sa::ProfScope ps("tokenwise_merge", stream);
-            e = sa::launch_tokenwise_merge(pair_start, B, H, M, d, plan.max_items, partials, stats,
-                                           sketch, lse_m, stream);
+            e = sa::launch_tokenwise_merge(f, stream);
         }
         if (e != hipSuccess) return hip_fail(e, "token-wise merge launch");
         return SA_OK;

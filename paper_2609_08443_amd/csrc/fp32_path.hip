@@ -264,7 +264,7 @@ __global__ __launch_bounds__(NW * 64) void agg_f32_kernel(AggF32Args a) {
     if (!range_part(a.n_ranges, a.parts, range, part)) return;
     const int64_t MD = (int64_t)a.M * D;
     const int m0 = (part * NW + w) * 32;
-    SegmentWalk walk(a.off, a.B, a.T, a.H, a.C, range);
+    SegmentWalk walk(a.off, a.B, a.T, a.H, a.C, a.n_ranges, range);
     Segment sg;
     while (walk.next(sg)) {
         const int t0 = sg.t0, t1 = sg.t1, h = sg.h;
@@ -324,7 +324,7 @@ struct BwdF32Args {
     float* Dbuf;
     float *dK, *dV, *dX;   // dX: K and V are one tensor, its gradient is written there
     float* dP;             // [H,M,d], or [B,H,M,d] with p_user
-    float* partials;       // [2 n_ranges][M][d]
+    float* partials;       // [n_ranges + H B][M][d]
 };
 
 // Workgroup = 4 waves of 32 tokens of one (user, head) segment of a 128-token range;
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(256) void bwd_token_f32_kernel(BwdF32Args a) {
             if (i % D == 0) a.Dbuf[row] = 0.f;
         }
     };
-    SegmentWalk walk(a.off, a.B, a.T, a.H, a.C, blockIdx.x);
+    SegmentWalk walk(a.off, a.B, a.T, a.H, a.C, 0, blockIdx.x);
     Segment sg;
     while (walk.next(sg)) {
         const int h = sg.h;
@@ -511,13 +511,13 @@ __global__ __launch_bounds__(NW * 64) void bwd_proto_f32_kernel(BwdF32Args a) {
     auto flush_to = [&](int h1) {
         for (; cur_h < h1; ++cur_h) {
             const int64_t g0 = (int64_t)cur_h * a.T, g1 = g0 + a.T - 1;
-            const int64_t slot = 2 * range + (g0 <= range * a.C ? 0 : 1);
+            const int64_t slot = g0 <= range * a.C ? range : a.n_ranges + cur_h;
             store_rows<D>(g0 / a.C != g1 / a.C ? a.partials + slot * MD : a.dP + cur_h * MD, acc, m0, a.M, l32, hl, a.scale);
 #pragma unroll
             for (int jt = 0; jt < JT; ++jt) acc[jt] = zero16();
         }
     };
-    SegmentWalk walk(a.off, a.B, a.T, a.H, a.C, range);
+    SegmentWalk walk(a.off, a.B, a.T, a.H, a.C, a.n_ranges, range);
     Segment sg;
     while (walk.next(sg)) {
         const int t0 = sg.t0, t1 = sg.t1, h = sg.h;

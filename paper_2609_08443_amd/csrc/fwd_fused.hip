@@ -54,6 +54,7 @@
 // runs the same code.
 #include "reduce_ops.h"
 #include "sa_internal.h"
+#include "segments.h"
 #include "tile_ops.h"
 
 namespace sa {
@@ -188,26 +189,19 @@ __global__ __launch_bounds__(NW * 64, 1) void fwd_fused_kernel(FusedFwdArgs a) {
     const int l32 = lane & 31;
     const int hl = lane >> 5;  // half of the wave
 
-    const int64_t range = xcd_range(blockIdx.x, gridDim.x);
-    const int64_t k0 = a.wg_start[range];
-    const int64_t k1 = a.wg_start[range + 1];
-    if (k0 < 0 || k1 < k0 || k1 > a.max_items) return;  // malformed offsets: nothing safe to do
-
+    SegmentWalk walk(a.offsets, a.B, a.T, a.H, a.C, a.n_ranges, xcd_range(blockIdx.x, gridDim.x));
     const float ks2 = a.scale * kLog2e;
     const int64_t MD = (int64_t)C::M * D;
     const uint32_t row_stride = (uint32_t)a.H * D;
     int64_t cur_p = -1;   // prototype block in LDS: head, or (user, head) with per-user P
     float pmax = 0.f;  // max_m |P[h, m]| of the loaded head
 
-    for (int64_t k = k0; k < k1; ++k) {
-        const int32_t* it = a.items + k * IT_WORDS;
-        const int b = it[IT_B];
-        const int h = it[IT_H];
-        const int t0 = it[IT_T0];
-        const int t1 = it[IT_T1];
-        const int split = it[IT_SPLIT];
-        // (segments of the work list are never empty)
-        if (b < 0 || b >= a.B || h < 0 || h >= a.H || t0 < 0 || t1 <= t0 || t1 > a.T) continue;
+    Segment sg;
+    while (walk.next(sg)) {
+        const int b = sg.b;
+        const int h = sg.h;
+        const int t0 = sg.t0;
+        const int t1 = sg.t1;
 
         // ---- prototypes of head h into LDS, with max_m |P_m|
         const int64_t pkey = a.p_user ? (int64_t)b * a.H + h : h;
@@ -547,7 +541,7 @@ __global__ __launch_bounds__(NW * 64, 1) void fwd_fused_kernel(FusedFwdArgs a) {
         }
 
         // ---- flush: the whole sketch of the pair, or this segment's partial
-        float* out = split ? a.partials + k * MD : a.sketch + ((int64_t)b * a.H + h) * MD;
+        float* out = sg.split ? a.partials + sg.slot * MD : a.sketch + ((int64_t)b * a.H + h) * MD;
         uint32_t lane_off = (uint32_t)((w * MW + 4 * hl) * D + l32);
         // keep the per-store addresses from being hoisted out of the loops (they
         // would stay live in registers through the whole tile loop)

@@ -296,7 +296,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
     const int m0 = part * C::MP + w * 32;            // the wave's first prototype
     const int prow = min(m0 + l32, a.M - 1);         // this lane's (rows past M repeat the last)
 
-    SegmentWalk walk(a.off, a.B, a.T, a.H, a.C, range);
+    SegmentWalk walk(a.off, a.B, a.T, a.H, a.C, a.n_ranges, range);
     Segment sg;
     while (walk.next(sg)) {
         const int b = sg.b, h = sg.h, t0 = sg.t0, t1 = sg.t1;
@@ -475,31 +475,6 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 }
 
-// ---------------------------------------------------------------- split-L merge
-// sketch[b,h] = the partials of a split pair added in token order; zero for an
-// empty one; a pair held by one range is written by its own workgroup.  Without
-// offsets there is one user, of all T tokens.
-__global__ __launch_bounds__(256) void merge_ranges_kernel(const int64_t* __restrict__ off, int64_t B, int64_t T,
-                                                           int32_t H, int64_t C, int64_t n_ranges,
-                                                           const float* __restrict__ partials, int64_t MD,
-                                                           float* __restrict__ sketch) {
-    const int64_t h = blockIdx.x / B, b = blockIdx.x % B;
-    const PairSlots ps(off ? seg_clamp(off[b], T) : 0, off ? seg_clamp(off[b + 1], T) : T, h, T, C);
-    if (ps.count == 1) return;
-    const int64_t idx = ((int64_t)blockIdx.y * 256 + threadIdx.x) * 4;
-    if (idx >= MD) return;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 16   // several segments' loads in flight; the sum keeps segment order
-    for (int64_t i = 0; i < ps.count; ++i) {
-        const float4 v = *reinterpret_cast<const float4*>(partials + ps.slot(i) * MD + idx);
-        acc.x += v.x;
-        acc.y += v.y;
-        acc.z += v.z;
-        acc.w += v.w;
-    }
-    *reinterpret_cast<float4*>(sketch + (b * H + h) * MD + idx) = acc;
-}
-
 template <int D, int NW>
 hipError_t launch_agg(AggArgs a, hipStream_t stream) {
     a.parts = (a.M + 32 * NW - 1) / (32 * NW);
@@ -563,15 +538,6 @@ hipError_t launch_split_fwd(const SplitFwdArgs& f, hipStream_t stream) {
         case 4: return f.d == 64 ? launch_agg<64, 4>(a, stream) : launch_agg<128, 4>(a, stream);
         default: return f.d == 64 ? launch_agg<64, 8>(a, stream) : launch_agg<128, 8>(a, stream);
     }
-}
-
-hipError_t launch_merge_ranges(const int64_t* offsets, int64_t B, int64_t T, int32_t H, int64_t C, int64_t n_ranges,
-                               const float* partials, int64_t MD, float* sketch, hipStream_t stream) {
-    if ((int64_t)H * B == 0) return hipSuccess;
-    dim3 grid((unsigned)((int64_t)H * B), (unsigned)((MD + 1023) / 1024));   // MD is a multiple of 4
-    hipLaunchKernelGGL(merge_ranges_kernel, grid, dim3(256), 0, stream, offsets, B, T, H, C, n_ranges, partials, MD,
-                       sketch);
-    return hipGetLastError();
 }
 
 }  // namespace sa

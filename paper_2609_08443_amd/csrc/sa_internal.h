@@ -46,27 +46,19 @@ hipError_t launch_worklist(const int64_t* offsets, int64_t B, int64_t T, int32_t
                            int32_t* wg_start, int32_t* pair_start, int64_t* n_items,
                            hipStream_t stream);
 
-// sketch[b,h] = sum of the partial sketches of a split (user, head) pair, in
-// segment order; zero for empty pairs; untouched for single-segment pairs.
-hipError_t launch_merge(const int32_t* pair_start, int64_t B, int32_t H, int64_t max_items,
-                        const float* partials, int64_t MD, float* sketch, hipStream_t stream);
-
 // Fused bf16 forward (matrix cores).  Returns hipErrorInvalidValue for a
 // (d, M) it has no instance for.
 struct FusedFwdArgs {
     const uint16_t* K;
     const uint16_t* V;
     const uint16_t* P;
-    const int32_t* items;
-    const int32_t* wg_start;
-    int64_t n_ranges;
-    int64_t max_items;
-    int64_t T;
-    int32_t B, H, M, d;
+    const int64_t* offsets;
+    int64_t B, T, C, n_ranges;   // token ranges of C, one per workgroup (segments.h)
+    int32_t H, M, d;
     float scale;
     float* sketch;
     float* lse;
-    float* partials;
+    float* partials;             // [n_ranges + H B][M][d]
     bool p_user;   // P is [B,H,M,d], one prototype block per user (stacked layers)
 };
 bool fused_fwd_supported(int32_t M, int32_t d);
@@ -76,8 +68,8 @@ hipError_t launch_fused_fwd(const FusedFwdArgs& a, hipStream_t stream);
 
 // Two-pass forward of bf16 inputs for the shapes without a fused instance
 // (fwd_split.hip): the log-sum-exp of every token into lse, then the aggregation
-// over n_ranges token ranges of C (segments.h); split pairs leave partials in slots
-// 0 .. 2 n_ranges - 1 for launch_merge_ranges.
+// over n_ranges token ranges of C (segments.h); split pairs leave partials for
+// launch_merge_ranges.
 struct SplitFwdArgs {
     const uint16_t* K;
     const uint16_t* V;
@@ -89,13 +81,16 @@ struct SplitFwdArgs {
     bool p_user;       // P is [B,H,M,d]
     float* sketch;
     float* lse;        // [T,H]
-    float* partials;   // [2 n_ranges][M][d]
+    float* partials;   // [n_ranges + H B][M][d]
 };
 // token ranges that fill the device once
 int64_t split_fwd_ranges(int32_t M);
 hipError_t launch_split_fwd(const SplitFwdArgs& f, hipStream_t stream);
+// sketch[b,h] = sum of the partial sketches of a split (user, head) pair, in
+// segment order; zero for empty pairs; untouched for single-segment pairs.  Without
+// offsets there is one user, of all T tokens.
 hipError_t launch_merge_ranges(const int64_t* offsets, int64_t B, int64_t T, int32_t H, int64_t C, int64_t n_ranges,
-                               const float* partials, int64_t MD, float* sketch, hipStream_t stream);  // offsets null: one user of T tokens
+                               const float* partials, int64_t MD, float* sketch, hipStream_t stream);
 
 // Fused bf16 backward (matrix cores): prep, token-side and prototype-side
 // kernels plus the per-head sum of the dP partials.
@@ -139,14 +134,18 @@ hipError_t launch_fused_bwd(const FusedBwdArgs& a, hipStream_t stream);
 
 // Token-wise normalised forward (sa_sketch_fwd_tokenwise).
 bool tokenwise_fused_supported(int32_t M, int32_t d);
-hipError_t launch_tokenwise_fused(const int32_t* items, const int32_t* wg_start, int64_t n_ranges,
-                                  int64_t max_items, const void* K, const void* V, const void* P,
-                                  int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, float scale,
-                                  float* sketch, float* lse_m, float* partials, float* stats,
-                                  hipStream_t stream);
-hipError_t launch_tokenwise_merge(const int32_t* pair_start, int64_t B, int32_t H, int32_t M, int32_t d,
-                                  int64_t max_items, const float* partials, const float* stats,
-                                  float* sketch, float* lse_m, hipStream_t stream);
+struct TokenwiseArgs {
+    const void *K, *V, *P;
+    const int64_t* offsets;
+    int64_t B, T, C, n_ranges;
+    int32_t H, M, d;
+    float scale;
+    float *sketch, *lse_m;   // lse_m may be null
+    float* partials;         // [n_ranges + H B][M][d], unnormalised
+    float* stats;            // [n_ranges + H B][M][2]
+};
+hipError_t launch_tokenwise_fused(const TokenwiseArgs& f, hipStream_t stream);
+hipError_t launch_tokenwise_merge(const TokenwiseArgs& f, hipStream_t stream);
 hipError_t launch_tokenwise_generic(const void* K, const void* V, const void* P, const int64_t* offsets,
                                     int64_t B, int32_t H, int32_t M, int32_t d, float scale, bool bf16,
                                     float* sketch, float* lse_m, hipStream_t stream);
@@ -259,7 +258,7 @@ struct PlainBwdArgs {
     bool dx_add;             // with dX: add to it
     float* Dbuf;             // [T,H]
     float *dK, *dV, *dX, *dP;   // dX non-null: K = V, its gradient goes there (dK, dV unused)
-    float* partials;         // [2 n_ranges][M][d]
+    float* partials;         // [n_ranges + H B][M][d]
 };
 hipError_t launch_plain_bwd(const PlainBwdArgs& f, bool bf16, hipStream_t stream);
 

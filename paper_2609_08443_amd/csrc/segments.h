@@ -2,12 +2,11 @@
 // its own token range from the offsets.
 //
 // The (head, token) pairs form one head-major index space of length H*T, cut into
-// equal ranges of C, as for the work list (worklist.hip).  Inside a range only the
-// segment at its start can belong to a user that began in an earlier range, and
-// only its last one to a user that goes on in the next, so two partial slots per
-// range hold everything a split (user, head) pair leaves behind: slot 2 r for the
-// segment at the start of range r, 2 r + 1 for a later one.  The merge derives a
-// pair's slots from its offsets in the same way.
+// equal ranges of C, as for the work list (worklist.hip).  A (user, head) pair whose
+// tokens span several ranges leaves one partial a range: slot r from the segment
+// that begins with range r (only one does), slot n_ranges + h B + b from the pair's
+// first segment when it begins inside a range.  The merge derives a pair's slots
+// from its offsets in the same way; there are n_ranges + H B of them.
 //
 // Offsets are device data the host never reads: every value is clamped to [0, T]
 // and every step of the walk moves forward, so malformed offsets give wrong
@@ -40,8 +39,8 @@ struct Segment {
 
 class SegmentWalk {
   public:
-    __device__ inline SegmentWalk(const int64_t* off, int64_t B, int64_t T, int32_t H, int64_t C, int64_t range)
-        : off_(off), B_(B), T_(T), C_(C), range_(range) {
+    __device__ inline SegmentWalk(const int64_t* off, int64_t B, int64_t T, int32_t H, int64_t C, int64_t n_ranges, int64_t range)
+        : off_(off), B_(B), T_(T), C_(C), n_ranges_(n_ranges), range_(range) {
         const int64_t HT = (int64_t)H * T;
         g_ = range * C;
         end_ = g_ + C < HT ? g_ + C : HT;
@@ -73,7 +72,7 @@ class SegmentWalk {
             s.t0 = (int32_t)t0;
             s.t1 = (int32_t)t1;
             s.split = (base + lo) / C_ != (base + hi - 1) / C_;
-            s.slot = 2 * range_ + (base + t0 == range_ * C_ ? 0 : 1);
+            s.slot = base + t0 == range_ * C_ ? range_ : n_ranges_ + h_ * B_ + b;
             g_ = base + t1;
             return true;
         }
@@ -82,28 +81,24 @@ class SegmentWalk {
 
   private:
     const int64_t* off_;
-    int64_t B_, T_, C_, range_, g_, end_, b_;
+    int64_t B_, T_, C_, n_ranges_, range_, g_, end_, b_;
     int32_t h_;
 };
 
-// Partial slots of the pair with tokens [lo, hi) of head h: slot(i) for
+// Partial slots of user b of B, head h, with tokens [lo, hi): slot(i) for
 // i = 0 .. count - 1, in token order; count = 0 for an empty user.
 struct PairSlots {
-    int64_t first_range, count;
-    bool aligned;   // the pair begins at a range's start
-    __device__ inline PairSlots(int64_t lo, int64_t hi, int64_t h, int64_t T, int64_t C) {
-        if (hi <= lo) {
-            first_range = 0;
-            count = 0;
-            aligned = true;
-            return;
-        }
+    int64_t count, first, rest;   // slot(0), and slot(i) = rest + i from there on
+    __device__ inline PairSlots(int64_t lo, int64_t hi, int64_t b, int64_t h, int64_t B, int64_t T, int64_t C,
+                                int64_t n_ranges)
+        : count(0), first(0), rest(0) {
+        if (hi <= lo) return;
         const int64_t g0 = h * T + lo, g1 = h * T + hi - 1;
-        first_range = g0 / C;
-        count = g1 / C - first_range + 1;
-        aligned = g0 == first_range * C;
+        rest = g0 / C;
+        count = g1 / C - rest + 1;
+        first = g0 == rest * C ? rest : n_ranges + h * B + b;
     }
-    __device__ inline int64_t slot(int64_t i) const { return 2 * (first_range + i) + (i == 0 && !aligned ? 1 : 0); }
+    __device__ inline int64_t slot(int64_t i) const { return i == 0 ? first : rest + i; }
 };
 
 }  // namespace sa

@@ -22,10 +22,10 @@
 //                       token tiles of 32 double-buffered in LDS; S = K P^T and the
 //                       aggregation E^T V on v_mfma_f32_32x32x16_bf16 (V^T read
 //                       with the transposing LDS load).
-//   tw_merge_kernel     one wave per (user, head, prototype) row: rescale-and-add
-//                       of the partials of a split user, or zero / -inf for an
-//                       empty one.
+//   tw_merge_kernel     rescale-and-add of the partials of a split user, or zero /
+//                       -inf for an empty one.
 #include "sa_internal.h"
+#include "segments.h"
 #include "tile_ops.h"
 
 namespace sa {
@@ -119,18 +119,15 @@ struct TwArgs {
     const uint16_t* K;
     const uint16_t* V;
     const uint16_t* P;
-    const int32_t* items;
-    const int32_t* wg_start;
-    int64_t n_ranges;
-    int64_t max_items;
-    int64_t T;
-    int32_t B, H, M;
+    const int64_t* offsets;
+    int64_t B, T, C, n_ranges;
+    int32_t H, M;
     int32_t parts;
     float scale;
     float* sketch;
     float* lse_m;       // may be null
-    float* partials;    // [max_items][M][D]: unnormalised partial of a split user
-    float* stats;       // [max_items][M][2]: (max in log2 units, sum)
+    float* partials;    // [n_ranges + H B][M][D]: unnormalised partial of a split user
+    float* stats;       // [n_ranges + H B][M][2]: (max in log2 units, sum)
 };
 
 template <int D, int NW>
@@ -149,8 +146,6 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
     const int64_t q8 = a.n_ranges / 8, r8 = a.n_ranges % 8;
     if (ix >= q8 + (xcd < r8 ? 1 : 0)) return;
     const int64_t range = xcd * q8 + (xcd < r8 ? xcd : r8) + ix;
-    const int64_t k0 = a.wg_start[range], k1 = a.wg_start[range + 1];
-    if (k0 < 0 || k1 < k0 || k1 > a.max_items) return;
 
     const float ks2 = a.scale * kLog2e;
     const int64_t MD = (int64_t)a.M * D;
@@ -173,11 +168,12 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
         wave_lds_order();
     };
 
-    for (int64_t k = k0; k < k1; ++k) {
-        const int32_t* it = a.items + k * IT_WORDS;
-        const int b = it[IT_B], h = it[IT_H], t0 = it[IT_T0], t1 = it[IT_T1];
-        const int split = it[IT_SPLIT];
-        if (b < 0 || b >= a.B || h < 0 || h >= a.H || t0 < 0 || t1 < t0 || t1 > a.T) continue;
+    SegmentWalk walk(a.offsets, a.B, a.T, a.H, a.C, a.n_ranges, range);
+    Segment sg;
+    while (walk.next(sg)) {
+        const int b = sg.b, h = sg.h, t0 = sg.t0, t1 = sg.t1;
+        const int64_t k = sg.slot;
+        const bool split = sg.split;
 
         // this wave's 32 prototypes as B operands, for the whole segment
         bf16x8 pop[KS];
@@ -221,13 +217,10 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
                 }
             }
         };
-        const bool any = t1 > t0;   // (an empty segment still writes its zero output)
-        if (any) {
-            fetch(t0, ra);
-            fetch(t0 + 32, rb);
-        }
+        fetch(t0, ra);
+        fetch(t0 + 32, rb);
         __syncthreads();  // the previous segment is done with every LDS buffer
-        if (any) store(0, ra);
+        store(0, ra);
         __syncthreads();
 
         f32x16 acc[JT];
@@ -300,13 +293,11 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
         // two tiles per trip; the exits sit after each step, so that the path back
         // to the top always comes from the second step (whose pending loads fill
         // the other register set)
-        if (any) {
-            for (int ts = t0;; ts += 64) {
-                step(ts, 0, ra, rb);
-                if (ts + 32 >= t1) break;
-                step(ts + 32, 1, rb, ra);
-                if (ts + 64 >= t1) break;
-            }
+        for (int ts = t0;; ts += 64) {
+            step(ts, 0, ra, rb);
+            if (ts + 32 >= t1) break;
+            step(ts + 32, 1, rb, ra);
+            if (ts + 64 >= t1) break;
         }
         const float ltot = xhalf_add(lsum);   // both halves hold the same prototype
         // rows of this wave: prototypes part*MP + w*32 + srow(r, hl), columns jt*32 + l32
@@ -338,42 +329,45 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
     }
 }
 
-// One wave per (user, head, prototype) row: the (max, sum) of the row's segments
-// are read once, then lane j rescales and adds columns j and j + 64.
-__global__ __launch_bounds__(256) void tw_merge_kernel(const int32_t* __restrict__ pair_start, int64_t B,
-                                                       int32_t H, int32_t M, int32_t d, int64_t max_items,
+// A workgroup merges ROWS = 256 / (D / 4) prototype rows of a split pair, D / 4
+// threads (four columns each) a row: the (max, sum) of the row's segments are read
+// once by the row's threads in turn, then every thread rescales and adds its columns,
+// several segments' loads in flight; the sums keep segment order.
+template <int D>
+__global__ __launch_bounds__(256) void tw_merge_kernel(const int64_t* __restrict__ off, int64_t B, int64_t T,
+                                                       int32_t H, int32_t M, int64_t C, int64_t n_ranges,
                                                        const float* __restrict__ partials,
-                                                       const float* __restrict__ stats,
+                                                       const float2* __restrict__ stats,
                                                        float* __restrict__ sketch, float* __restrict__ lse_m) {
-    const int64_t p = blockIdx.x;   // head-major pair h*B + b
-    int64_t s0 = pair_start[p], s1 = pair_start[p + 1];
-    s0 = s0 < 0 ? 0 : (s0 > max_items ? max_items : s0);
-    s1 = s1 < s0 ? s0 : (s1 > max_items ? max_items : s1);
-    if (s1 - s0 == 1) return;       // written directly by the fused kernel
-    const int64_t m = (int64_t)blockIdx.y * 4 + (threadIdx.x >> 6);
+    constexpr int TPR = D / 4, ROWS = 256 / TPR;
+    const int64_t h = blockIdx.x / B, b = blockIdx.x % B;
+    const PairSlots ps(seg_clamp(off[b], T), seg_clamp(off[b + 1], T), b, h, B, T, C, n_ranges);
+    if (ps.count == 1) return;       // written directly by the fused kernel
+    const int64_t m = (int64_t)blockIdx.y * ROWS + threadIdx.x / TPR;
     if (m >= M) return;
-    const int lane = threadIdx.x & 63;
-    const int64_t h = p / B, b = p % B;
-    const int64_t MD = (int64_t)M * d;
-    // (unrolled so that the loads of several segments are in flight at once; the
-    // sums keep segment order)
+    const int j = (threadIdx.x % TPR) * 4;
+    const int64_t MD = (int64_t)M * D;
     float mx = -INFINITY;
+    for (int64_t i = threadIdx.x % TPR; i < ps.count; i += TPR) mx = fmaxf(mx, stats[ps.slot(i) * M + m].x);
+#pragma unroll
+    for (int o = 1; o < TPR; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    float l = 0.f;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 8
-    for (int64_t k = s0; k < s1; ++k) mx = fmaxf(mx, stats[(k * M + m) * 2]);
-    float l = 0.f, v0 = 0.f, v1 = 0.f;
-#pragma unroll 4
-    for (int64_t k = s0; k < s1; ++k) {
-        const float f = exp2f(stats[(k * M + m) * 2] - mx);
-        l += f * stats[(k * M + m) * 2 + 1];
-        const float* row = partials + k * MD + m * d;
-        v0 += f * row[lane];
-        if (lane + 64 < d) v1 += f * row[lane + 64];
+    for (int64_t i = 0; i < ps.count; ++i) {
+        const int64_t k = ps.slot(i);
+        const float2 st = stats[k * M + m];
+        const float4 x = *reinterpret_cast<const float4*>(partials + k * MD + m * D + j);
+        const float f = exp2f(st.x - mx);
+        l += f * st.y;
+        v.x += f * x.x;
+        v.y += f * x.y;
+        v.z += f * x.z;
+        v.w += f * x.w;
     }
-    float* out = sketch + (b * H + h) * MD + m * d;
     const float rl = l > 0.f ? 1.0f / l : 0.f;
-    out[lane] = v0 * rl;
-    if (lane + 64 < d) out[lane + 64] = v1 * rl;
-    if (lse_m && lane == 0) lse_m[(b * H + h) * M + m] = l > 0.f ? mx * kLn2 + __logf(l) : -INFINITY;
+    *reinterpret_cast<float4*>(sketch + (b * H + h) * MD + m * D + j) = make_float4(v.x * rl, v.y * rl, v.z * rl, v.w * rl);
+    if (lse_m && j == 0) lse_m[(b * H + h) * M + m] = l > 0.f ? mx * kLn2 + __logf(l) : -INFINITY;
 }
 
 template <int D, int NW>
@@ -396,43 +390,43 @@ bool tokenwise_fused_supported(int32_t M, int32_t d) {
     return (d == 64 || d == 128) && M % 128 == 0 && M <= 4096;
 }
 
-hipError_t launch_tokenwise_fused(const int32_t* items, const int32_t* wg_start, int64_t n_ranges,
-                                  int64_t max_items, const void* K, const void* V, const void* P,
-                                  int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, float scale,
-                                  float* sketch, float* lse_m, float* partials, float* stats,
-                                  hipStream_t stream) {
-    if (n_ranges == 0) return hipSuccess;
+hipError_t launch_tokenwise_fused(const TokenwiseArgs& f, hipStream_t stream) {
+    if (f.n_ranges == 0) return hipSuccess;
     TwArgs a;
-    a.K = reinterpret_cast<const uint16_t*>(K);
-    a.V = reinterpret_cast<const uint16_t*>(V);
-    a.P = reinterpret_cast<const uint16_t*>(P);
-    a.items = items;
-    a.wg_start = wg_start;
-    a.n_ranges = n_ranges;
-    a.max_items = max_items;
-    a.T = T;
-    a.B = (int32_t)B;
-    a.H = H;
-    a.M = M;
+    a.K = reinterpret_cast<const uint16_t*>(f.K);
+    a.V = reinterpret_cast<const uint16_t*>(f.V);
+    a.P = reinterpret_cast<const uint16_t*>(f.P);
+    a.offsets = f.offsets;
+    a.B = f.B;
+    a.T = f.T;
+    a.C = f.C;
+    a.n_ranges = f.n_ranges;
+    a.H = f.H;
+    a.M = f.M;
     a.parts = 1;
-    a.scale = scale;
-    a.sketch = sketch;
-    a.lse_m = lse_m;
-    a.partials = partials;
-    a.stats = stats;
+    a.scale = f.scale;
+    a.sketch = f.sketch;
+    a.lse_m = f.lse_m;
+    a.partials = f.partials;
+    a.stats = f.stats;
     // eight waves (256 prototypes per workgroup) when M allows, else four
-    const bool eight = M % 256 == 0;
-    if (d == 64) return eight ? launch_tw_inst<64, 8>(a, stream) : launch_tw_inst<64, 4>(a, stream);
+    const bool eight = f.M % 256 == 0;
+    if (f.d == 64) return eight ? launch_tw_inst<64, 8>(a, stream) : launch_tw_inst<64, 4>(a, stream);
     return eight ? launch_tw_inst<128, 8>(a, stream) : launch_tw_inst<128, 4>(a, stream);
 }
 
-hipError_t launch_tokenwise_merge(const int32_t* pair_start, int64_t B, int32_t H, int32_t M, int32_t d,
-                                  int64_t max_items, const float* partials, const float* stats,
-                                  float* sketch, float* lse_m, hipStream_t stream) {
-    const int64_t npairs = (int64_t)H * B;
+hipError_t launch_tokenwise_merge(const TokenwiseArgs& f, hipStream_t stream) {
+    const int64_t npairs = (int64_t)f.H * f.B;
     if (npairs == 0) return hipSuccess;
-    hipLaunchKernelGGL(tw_merge_kernel, dim3((unsigned)npairs, (unsigned)((M + 3) / 4)), dim3(256), 0, stream,
-                       pair_start, B, H, M, d, max_items, partials, stats, sketch, lse_m);
+    const int rows = 256 / (f.d / 4);
+    const dim3 grid((unsigned)npairs, (unsigned)((f.M + rows - 1) / rows));
+    const float2* st = reinterpret_cast<const float2*>(f.stats);
+    if (f.d == 64)
+        hipLaunchKernelGGL(tw_merge_kernel<64>, grid, dim3(256), 0, stream, f.offsets, f.B, f.T, f.H, f.M, f.C,
+                           f.n_ranges, f.partials, st, f.sketch, f.lse_m);
+    else
+        hipLaunchKernelGGL(tw_merge_kernel<128>, grid, dim3(256), 0, stream, f.offsets, f.B, f.T, f.H, f.M, f.C,
+                           f.n_ranges, f.partials, st, f.sketch, f.lse_m);
     return hipGetLastError();
 }
 

@@ -11,6 +11,7 @@
 // the partial sketches of a user cut across ranges merge by addition; there is
 // no rescaling step as in a token-wise softmax.
 #include "sa_internal.h"
+#include "segments.h"
 
 namespace sa {
 
@@ -99,22 +100,23 @@ __global__ __launch_bounds__(kWorklistThreads) void worklist_kernel(
     }
 }
 
-__global__ __launch_bounds__(256) void merge_kernel(const int32_t* __restrict__ pair_start,
-                                                    int64_t B, int32_t H, int64_t max_items,
-                                                    const float* __restrict__ partials,
-                                                    int64_t MD, float* __restrict__ sketch) {
-    const int64_t p = blockIdx.x;  // head-major pair index h*B + b
-    int64_t s0 = pair_start[p], s1 = pair_start[p + 1];
-    s0 = s0 < 0 ? 0 : (s0 > max_items ? max_items : s0);
-    s1 = s1 < s0 ? s0 : (s1 > max_items ? max_items : s1);
-    if (s1 - s0 == 1) return;  // written directly by the forward kernel
+// ---------------------------------------------------------------- split-L merge
+// sketch[b,h] = the partials of a split pair added in token order; zero for an
+// empty one; a pair held by one range is written by its own workgroup.  Without
+// offsets there is one user, of all T tokens.
+__global__ __launch_bounds__(256) void merge_ranges_kernel(const int64_t* __restrict__ off, int64_t B, int64_t T,
+                                                           int32_t H, int64_t C, int64_t n_ranges,
+                                                           const float* __restrict__ partials, int64_t MD,
+                                                           float* __restrict__ sketch) {
+    const int64_t h = blockIdx.x / B, b = blockIdx.x % B;
+    const PairSlots ps(off ? seg_clamp(off[b], T) : 0, off ? seg_clamp(off[b + 1], T) : T, b, h, B, T, C, n_ranges);
+    if (ps.count == 1) return;
     const int64_t idx = ((int64_t)blockIdx.y * 256 + threadIdx.x) * 4;
     if (idx >= MD) return;
-    const int64_t h = p / B, b = p % B;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8   // several segments' loads in flight; the sum keeps segment order
-    for (int64_t k = s0; k < s1; ++k) {
-        const float4 v = *reinterpret_cast<const float4*>(partials + k * MD + idx);
+#pragma unroll 16   // several segments' loads in flight; the sum keeps segment order
+    for (int64_t i = 0; i < ps.count; ++i) {
+        const float4 v = *reinterpret_cast<const float4*>(partials + ps.slot(i) * MD + idx);
         acc.x += v.x;
         acc.y += v.y;
         acc.z += v.z;
@@ -134,14 +136,12 @@ hipError_t launch_worklist(const int64_t* offsets, int64_t B, int64_t T, int32_t
     return hipGetLastError();
 }
 
-hipError_t launch_merge(const int32_t* pair_start, int64_t B, int32_t H, int64_t max_items,
-                        const float* partials, int64_t MD, float* sketch, hipStream_t stream) {
-    const int64_t npairs = (int64_t)H * B;
-    if (npairs == 0) return hipSuccess;
-    // MD is a multiple of 4 (d is 64 or 128)
-    dim3 grid((unsigned)npairs, (unsigned)((MD + 1023) / 1024));
-    hipLaunchKernelGGL(merge_kernel, grid, dim3(256), 0, stream, pair_start, B, H, max_items,
-                       partials, MD, sketch);
+hipError_t launch_merge_ranges(const int64_t* offsets, int64_t B, int64_t T, int32_t H, int64_t C, int64_t n_ranges,
+                               const float* partials, int64_t MD, float* sketch, hipStream_t stream) {
+    if ((int64_t)H * B == 0) return hipSuccess;
+    dim3 grid((unsigned)((int64_t)H * B), (unsigned)((MD + 1023) / 1024));   // MD is a multiple of 4
+    hipLaunchKernelGGL(merge_ranges_kernel, grid, dim3(256), 0, stream, offsets, B, T, H, C, n_ranges, partials, MD,
+                       sketch);
     return hipGetLastError();
 }
 
