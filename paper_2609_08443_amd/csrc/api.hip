@@ -97,6 +97,7 @@ sa_status validate_offsets(const int64_t* offsets, int64_t B, int64_t T, hipStre
 // ---------------------------------------------------------------- forward plan
 struct FwdPlan {
     bool fused = false;    // one-pass matrix-core forward, else two passes over the keys
+    bool bf16_weights = false;   // weights rounded to bf16 (the shapes of the one-pass kernel)
     int64_t C = 0;         // tokens per workgroup range
     int64_t n_ranges = 0;  // workgroups
     // workspace offsets (bytes)
@@ -121,10 +122,28 @@ void set_ranges(int64_t HT, int64_t target, int64_t* C, int64_t* n) {
     *n = (HT + *C - 1) / *C;
 }
 
+// Whether a shape of the one-pass forward is faster in two passes (fwd_split.hip).
+// One pass gives every workgroup all M prototypes, so with few tokens a CU it spends
+// its time on the prototype load and the M x d partial of each short range; two
+// passes compute the logits twice but cut the ranges by the prototype parts.
+// Measured, one pass / two (us) at HT (head, token) pairs:
+//   M = 512, d = 128:  2K 49 / 28,  40K 67 / 47,  128K 92 / 76,  512K 227 / 243
+//   M = 256, d = 128:  8K 40 / 27,  40K 43 / 37,  160K 65 / 63,  640K 166 / 176
+//   M = 1024, d = 64:  4K 52 / 28,  40K 56 / 48,  80K 80 / 76,  128K 87 / 94
+//   M = 256, d = 64:   8K 25 / 20,  40K 33 / 27,  128K 37 / 39
+//   M = 128, d = 64:   2K 15 / 18,  8K 18 / 18,  40K 28 / 24,  128K 30 / 29
+//   M = 128, d = 128:  8K 26 / 22,  40K 34 / 31,  128K 39 / 42
+bool two_pass_faster(int64_t HT, int32_t M, int32_t d) {
+    if (M * d <= 8192 && HT < 8192) return false;
+    const int64_t per_cu = d == 128 && M >= 256 ? 512 : 256;
+    return HT <= per_cu * device_cus();
+}
+
 FwdPlan plan_fwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype dtype,
                  bool need_lse_scratch) {
     FwdPlan p;
-    p.fused = dtype == SA_BF16 && sa::fused_fwd_supported(M, d);
+    p.bf16_weights = dtype == SA_BF16 && sa::fused_fwd_supported(M, d);
+    p.fused = p.bf16_weights && !two_pass_faster((int64_t)H * T, M, d);
     size_t off = 0;
     auto carve = [&](size_t bytes) {
         const size_t o = off;
@@ -139,7 +158,7 @@ FwdPlan plan_fwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype
         p.C = fused_chunk_tokens(T, H, M, d);
         p.n_ranges = (HT + p.C - 1) / p.C;
     } else {
-        set_ranges(HT, dtype == SA_BF16 ? sa::split_fwd_ranges(M) : sa::plain_fwd_ranges(M), &p.C, &p.n_ranges);
+        set_ranges(HT, dtype == SA_BF16 ? sa::split_fwd_ranges(M, p.bf16_weights, HT) : sa::plain_fwd_ranges(M), &p.C, &p.n_ranges);
     }
     p.off_partials = carve(sizeof(float) * (size_t)(p.n_ranges + H * B) * M * d);
     if (!p.fused && need_lse_scratch) p.off_lse = carve(sizeof(float) * (size_t)T * H);
@@ -603,6 +622,7 @@ sa_status run_fwd(const void* K, const void* V, const void* P, const int64_t* of
         f.d = d;
         f.scale = scale;
         f.p_user = p_user;
+        f.bf16_weights = plan.bf16_weights;
         f.sketch = sketch;
         f.lse = lse ? lse : reinterpret_cast<float*>(ws + plan.off_lse);
         f.partials = partials;

@@ -1,7 +1,8 @@
-// Forward of the SA sketching step on bf16 inputs for the shapes the one-pass
-// fused kernel (fwd_fused.hip) has no instance for: M x d too large for one
+// Two-pass forward of the SA sketching step on bf16 inputs.  It runs the shapes the
+// one-pass fused kernel (fwd_fused.hip) has no instance for: M x d too large for one
 // workgroup's registers (d = 128 above 512 prototypes, d = 64 above 1024), or M
-// not a multiple of 128.  The weights keep their fp32 precision.
+// not a multiple of 128; there the weights keep their fp32 precision.  And it runs
+// short batches of the one-pass shapes, with that kernel's bf16 weights.
 //
 // Two passes over the keys:
 //
@@ -13,7 +14,7 @@
 // the M x d accumulator is spread over workgroups.
 //
 // Products of bf16 inputs are exact in the matrix cores' fp32 accumulation, so
-// the logits are single-precision sums.  The weights A are fp32: each is cut into
+// the logits are single-precision sums.  fp32 weights A: each is cut into
 // three bf16 parts of eight mantissa bits, A = hi + mid + lo exactly (truncation,
 // each remainder is exact), and the three products with the bf16 V accumulate in
 // fp32.  Against float64 the sketch is then as close as a plain fp32 evaluation
@@ -25,6 +26,7 @@
 // Measured on 100K tokens, H = 1, M = 1024, d = 128: lse 45 us, aggregation 118 us
 // (890 TFLOP/s executed, against 1200 for a large library product), merge 7 us; the
 // fp32 VALU path took 2.8 ms, 3.2 ms and 86 us.
+#include <algorithm>
 #include <type_traits>
 #include "reduce_ops.h"
 #include "sa_internal.h"
@@ -267,7 +269,7 @@ __device__ inline uint32_t finite_or_zero(uint32_t w) {
     return w;
 }
 
-template <int D, int NW>
+template <int D, int NW, int PARTS>
 __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void agg_split_kernel(AggArgs a) {
     using C = AggCfg<D, NW>;
     constexpr int KS = C::KS, JT = C::JT;
@@ -337,7 +339,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
                     if (ts + idx / C::KCH >= t1) v = (u32x4){0, 0, 0, 0};   // V of rows past the segment
                     *reinterpret_cast<u32x4*>(Kd + swz<D>(idx / C::KCH, idx % C::KCH)) = r.k[c];
                     *reinterpret_cast<u32x4*>(Vd + swz<D>(idx / C::KCH, idx % C::KCH)) = v;
-                    bad |= nonfinite8(v);
+                    if constexpr (PARTS == 3) bad |= nonfinite8(v);
                 }
             }
             if (w == 0 && hl == 0) {
@@ -387,63 +389,75 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk)
                 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_b128(Ks, swz<D>(l32, 2 * kk + hl)), pop[kk], s, 0, 0, 0);
-            // weights and their three bf16 parts (parts[p][i]: two tokens' values)
-            uint32_t parts[3][8];
+            if constexpr (PARTS == 1) {
+                float e[16];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float e[2], r1[2], r2[2];
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    e[q] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * i + q], ks2, sh[2 * i + q]));
-                    r1[q] = e[q] - bf16_hi(__float_as_uint(e[q]));
-                    r2[q] = r1[q] - bf16_hi(__float_as_uint(r1[q]));
-                }
-                // the upper halves of two values, the first in the low half
-                parts[0][i] = __builtin_amdgcn_perm(__float_as_uint(e[1]), __float_as_uint(e[0]), 0x07060302u);
-                parts[1][i] = __builtin_amdgcn_perm(__float_as_uint(r1[1]), __float_as_uint(r1[0]), 0x07060302u);
-                parts[2][i] = __builtin_amdgcn_perm(__float_as_uint(r2[1]), __float_as_uint(r2[0]), 0x07060302u);
-            }
-            auto op = [&](int p, int h2) __attribute__((always_inline)) {
-                return __builtin_bit_cast(bf16x8, (u32x4){parts[p][4 * h2], parts[p][4 * h2 + 1], parts[p][4 * h2 + 2],
-                                                          parts[p][4 * h2 + 3]});
-            };
-            if (__builtin_expect(flag[buf] != ts + 1, 1)) {
-                // a tile's products sum up on their own, the smallest parts first, and
-                // are added to the running sum once (one rounding at its magnitude per
-                // 32 tokens instead of six)
+                for (int r = 0; r < 16; ++r) e[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], ks2, sh[r]));
+                const bf16x8 e0 = pack8(e), e1 = pack8(e + 8);
 #pragma unroll
                 for (int jt = 0; jt < JT; ++jt) {
-                    const bf16x8 v0 = lds_tr_tokens<D>(Vs, lane, jt, 0), v1 = lds_tr_tokens<D>(Vs, lane, jt, 1);
-                    f32x16 t = {};
-#pragma unroll
-                    for (int p = 2; p >= 0; --p) {
-                        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(p, 0), v0, t, 0, 0, 0);
-                        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(p, 1), v1, t, 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[jt][r] += t[r];
+                    acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(e0, lds_tr_tokens<D>(Vs, lane, jt, 0), acc[jt], 0, 0, 0);
+                    acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(e1, lds_tr_tokens<D>(Vs, lane, jt, 1), acc[jt], 0, 0, 0);
                 }
             } else {
-                // an infinite V times a weight's zero lower part would be NaN: the
-                // upper parts see V as it is, the others its finite values only
-                // (uniform over the workgroup: every thread reads the same flag)
-                auto add = [&](int p) __attribute__((always_inline)) {
-#pragma unroll
-                    for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-                        for (int h2 = 0; h2 < 2; ++h2)
-                            acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(p, h2), lds_tr_tokens<D>(Vs, lane, jt, h2),
-                                                                              acc[jt], 0, 0, 0);
-                };
-                add(0);
-                __syncthreads();
-                for (int idx = tid; idx < C::LD_CHUNKS * 4; idx += C::THREADS) {
-                    uint32_t* q = reinterpret_cast<uint32_t*>(Vs) + idx;
-                    *q = finite_or_zero(*q);
+                // weights and their three bf16 parts (parts[p][i]: two tokens' values)
+                uint32_t parts[3][8];
+    #pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    float e[2], r1[2], r2[2];
+    #pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        e[q] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * i + q], ks2, sh[2 * i + q]));
+                        r1[q] = e[q] - bf16_hi(__float_as_uint(e[q]));
+                        r2[q] = r1[q] - bf16_hi(__float_as_uint(r1[q]));
+                    }
+                    // the upper halves of two values, the first in the low half
+                    parts[0][i] = __builtin_amdgcn_perm(__float_as_uint(e[1]), __float_as_uint(e[0]), 0x07060302u);
+                    parts[1][i] = __builtin_amdgcn_perm(__float_as_uint(r1[1]), __float_as_uint(r1[0]), 0x07060302u);
+                    parts[2][i] = __builtin_amdgcn_perm(__float_as_uint(r2[1]), __float_as_uint(r2[0]), 0x07060302u);
                 }
-                __syncthreads();
-                add(1);
-                add(2);
+                auto op = [&](int p, int h2) __attribute__((always_inline)) {
+                    return __builtin_bit_cast(bf16x8, (u32x4){parts[p][4 * h2], parts[p][4 * h2 + 1], parts[p][4 * h2 + 2],
+                                                              parts[p][4 * h2 + 3]});
+                };
+                if (__builtin_expect(flag[buf] != ts + 1, 1)) {
+                    // a tile's products sum up on their own, the smallest parts first, and
+                    // are added to the running sum once (one rounding at its magnitude per
+                    // 32 tokens instead of six)
+    #pragma unroll
+                    for (int jt = 0; jt < JT; ++jt) {
+                        const bf16x8 v0 = lds_tr_tokens<D>(Vs, lane, jt, 0), v1 = lds_tr_tokens<D>(Vs, lane, jt, 1);
+                        f32x16 t = {};
+    #pragma unroll
+                        for (int p = 2; p >= 0; --p) {
+                            t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(p, 0), v0, t, 0, 0, 0);
+                            t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(p, 1), v1, t, 0, 0, 0);
+                        }
+    #pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[jt][r] += t[r];
+                    }
+                } else {
+                    // an infinite V times a weight's zero lower part would be NaN: the
+                    // upper parts see V as it is, the others its finite values only
+                    // (uniform over the workgroup: every thread reads the same flag)
+                    auto add = [&](int p) __attribute__((always_inline)) {
+    #pragma unroll
+                        for (int jt = 0; jt < JT; ++jt)
+    #pragma unroll
+                            for (int h2 = 0; h2 < 2; ++h2)
+                                acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(p, h2), lds_tr_tokens<D>(Vs, lane, jt, h2),
+                                                                                  acc[jt], 0, 0, 0);
+                    };
+                    add(0);
+                    __syncthreads();
+                    for (int idx = tid; idx < C::LD_CHUNKS * 4; idx += C::THREADS) {
+                        uint32_t* q = reinterpret_cast<uint32_t*>(Vs) + idx;
+                        *q = finite_or_zero(*q);
+                    }
+                    __syncthreads();
+                    add(1);
+                    add(2);
+                }
             }
             if (more) store(ts + 32, buf ^ 1, nxt);
             __syncthreads();
@@ -475,11 +489,11 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 }
 
-template <int D, int NW>
+template <int D, int NW, int PARTS>
 hipError_t launch_agg(AggArgs a, hipStream_t stream) {
     a.parts = (a.M + 32 * NW - 1) / (32 * NW);
     const int64_t per_xcd = (a.n_ranges + 7) / 8;
-    hipLaunchKernelGGL((agg_split_kernel<D, NW>), dim3((unsigned)(8 * per_xcd * a.parts)), dim3(NW * 64), 0, stream, a);
+    hipLaunchKernelGGL((agg_split_kernel<D, NW, PARTS>), dim3((unsigned)(8 * per_xcd * a.parts)), dim3(NW * 64), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -513,12 +527,14 @@ int agg_waves(int32_t M) {
 
 }  // namespace
 
-int64_t split_fwd_ranges(int32_t M) {
-    // two waves per SIMD of every CU in one round of workgroups; at most two
-    // workgroups per CU, which bounds the partials by 2 x 512 slots
+int64_t split_fwd_ranges(int32_t M, bool bf16_weights, int64_t HT) {
+    // two waves per SIMD of every CU in one round of workgroups, at most two
+    // workgroups per CU; ranges of at least 128 (bf16 weights) or 64 tokens, below
+    // which a range's partial costs more than its tiles (M = 512, d = 128, 2K tokens,
+    // us: 16 ranges 23, 32 25, 63 27)
     const int nw = agg_waves(M);
-    const int64_t parts = (M + 32 * nw - 1) / (32 * nw);
-    const int64_t r = (int64_t)device_cus() * (nw == 8 ? 1 : 2) / parts;
+    const int64_t parts = (M + 32 * nw - 1) / (32 * nw), least = bf16_weights ? 128 : 64;
+    const int64_t r = std::min<int64_t>((int64_t)device_cus() * (nw == 8 ? 1 : 2) / parts, (HT + least - 1) / least);
     return r < 1 ? 1 : r;
 }
 
@@ -533,10 +549,15 @@ hipError_t launch_split_fwd(const SplitFwdArgs& f, hipStream_t stream) {
     AggArgs a{f.K, f.V, f.P, f.offsets, f.lse, f.B, f.T, f.C, f.n_ranges, f.H, f.M, 1, f.scale, f.p_user, f.sketch,
               f.partials};
     ProfScope ps("split_agg", stream);
+    const bool d64 = f.d == 64;
+    if (f.bf16_weights) {
+        if (agg_waves(f.M) == 4) return d64 ? launch_agg<64, 4, 1>(a, stream) : launch_agg<128, 4, 1>(a, stream);
+        return d64 ? launch_agg<64, 8, 1>(a, stream) : launch_agg<128, 8, 1>(a, stream);
+    }
     switch (agg_waves(f.M)) {
-        case 2: return f.d == 64 ? launch_agg<64, 2>(a, stream) : launch_agg<128, 2>(a, stream);
-        case 4: return f.d == 64 ? launch_agg<64, 4>(a, stream) : launch_agg<128, 4>(a, stream);
-        default: return f.d == 64 ? launch_agg<64, 8>(a, stream) : launch_agg<128, 8>(a, stream);
+        case 2: return d64 ? launch_agg<64, 2, 3>(a, stream) : launch_agg<128, 2, 3>(a, stream);
+        case 4: return d64 ? launch_agg<64, 4, 3>(a, stream) : launch_agg<128, 4, 3>(a, stream);
+        default: return d64 ? launch_agg<64, 8, 3>(a, stream) : launch_agg<128, 8, 3>(a, stream);
     }
 }
 

@@ -66,8 +66,8 @@ size_t fused_fwd_lds_bytes(int32_t M, int32_t d);
 hipError_t fused_fwd_occupancy(int32_t M, int32_t d, int* blocks_per_cu);
 hipError_t launch_fused_fwd(const FusedFwdArgs& a, hipStream_t stream);
 
-// Two-pass forward of bf16 inputs for the shapes without a fused instance
-// (fwd_split.hip): the log-sum-exp of every token into lse, then the aggregation
+// Two-pass forward of bf16 inputs: the shapes without a fused instance and short
+// batches (fwd_split.hip): the log-sum-exp of every token into lse, then the aggregation
 // over n_ranges token ranges of C (segments.h); split pairs leave partials for
 // launch_merge_ranges.
 struct SplitFwdArgs {
@@ -79,12 +79,13 @@ struct SplitFwdArgs {
     int32_t H, M, d;
     float scale;
     bool p_user;       // P is [B,H,M,d]
+    bool bf16_weights; // weights rounded to bf16, as in the one-pass kernel (M a multiple of 128)
     float* sketch;
     float* lse;        // [T,H]
     float* partials;   // [n_ranges + H B][M][d]
 };
 // token ranges that fill the device once
-int64_t split_fwd_ranges(int32_t M);
+int64_t split_fwd_ranges(int32_t M, bool bf16_weights, int64_t HT);
 hipError_t launch_split_fwd(const SplitFwdArgs& f, hipStream_t stream);
 // sketch[b,h] = sum of the partial sketches of a split (user, head) pair, in
 // segment order; zero for empty pairs; untouched for single-segment pairs.  Without
