@@ -21,7 +21,7 @@
 // staged.  In both, the tiles of one batch run on one XCD so that its operands
 // share that L2.  Products whose shapes or strides do not fit (k not a multiple of
 // 64, unaligned strides, fp32 operands without that permission) run on the
-// register-tiled fp32 product of layer.hip.
+// fp32 product of layer.hip.
 #include "sa_internal.h"
 #include "tile_ops.h"
 

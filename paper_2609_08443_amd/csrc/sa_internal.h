@@ -170,7 +170,7 @@ hipError_t launch_small_gemm(const MatView& a, const MatView& b, void* c, bool c
 // B[z b_z + k b_k + n b_n], (z, m, n) of C at C[z c_z + m c_m + n]; fp32 accumulation.
 // bf16 operands contiguous along k or along m (n), with k a multiple of 64 and
 // 16-byte aligned pieces, run on the matrix cores (gemm.hip); the rest on the
-// register-tiled fp32 product (layer.hip).
+// fp32 product (layer.hip).
 struct GemmDesc {
     const void* A;
     bool a_bf16;
