@@ -642,11 +642,13 @@ bool lt_offsets_fit(const GemmDesc& d, bool a_kc, bool b_kc) {
     return fits(a_kc, d.M, d.a_m, d.a_k) && fits(b_kc, d.N, d.b_n, d.b_k);
 }
 
-// The shape with the least estimated time: rounds of `occ` tiles per compute unit,
-// each round the tile's work over its speed times the tiles that share a CU (two
-// resident workgroups split its matrix cores); small tiles win where big ones
-// leave compute units idle.  -1 if none applies (byte offsets of a k-contiguous
-// operand beyond 32 bits).
+// The shape with the least estimated time: the most tiles one compute unit gets
+// (resident workgroups split its matrix cores, so `occ` of them take as long as one
+// after the other), each the tile's work over its speed; small tiles win where big
+// ones leave compute units idle.  Counting whole rounds of `occ` tiles instead made
+// 1,200 tiles of 64 x 64 look like six a CU, not five, and 4800 x 1024 x 1024 took
+// 128 x 256 tiles: 21.4 us (23.8 with B n-contiguous) against 18.7 (19.6).  -1 if no
+// shape applies (byte offsets of a k-contiguous operand beyond 32 bits).
 int choose_lt(const GemmDesc& d, bool a_kc, bool b_kc) {
     if (!lt_offsets_fit(d, a_kc, b_kc)) return -1;
     const int64_t cus = device_cus();
@@ -658,9 +660,7 @@ int choose_lt(const GemmDesc& d, bool a_kc, bool b_kc) {
         if ((!a_kc && !t.a_mc_ok) || t.one_slab != (d.K == GBK)) continue;
         const int64_t tiles = (int64_t)((d.M + t.bm - 1) / t.bm) * ((d.N + t.bn - 1) / t.bn) * d.batch;
         if (tiles >= (int64_t(1) << 31)) continue;
-        const int64_t rounds = (tiles + cus * t.occ - 1) / (cus * t.occ);
-        const int64_t share = std::min<int64_t>(t.occ, (tiles + cus - 1) / cus);
-        const double cost = (double)rounds * share * t.bm * t.bn / t.eff;
+        const double cost = (double)((tiles + cus - 1) / cus) * t.bm * t.bn / t.eff;
         if (best < 0 || cost < best_cost) {
             best = i;
             best_cost = cost;
@@ -750,6 +750,15 @@ MgArgs make_args(const GemmDesc& d) {
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t stream) {
     if (d.batch <= 0 || d.M <= 0 || d.N <= 0) return hipSuccess;
     if (!gemm_on_matrix_cores(d)) return launch_small_gemm_general(d, stream);
+    // Products with fp32 operands, when small, stay in fp32: the fp32 matrix cores then
+    // take no longer than the rounding kernel's 128 x 128 tiles, of which there are too
+    // few (64 x 128 outputs, k = 512, 16 of them: 4.7 us against 22).  Measured on
+    // stacked-block training steps, limit 0 / 3e8 / 6e8 / 2.4e9 / 5e9 (us): 8 users,
+    // H = 2, M = 512, d = 64 777 / 530 / 530 / 534 / 533; 32 users, H = 2, M = 512,
+    // d = 128 828 / 777 / 777 / 1010 / 1009.
+    constexpr double kFp32Flops = 6e8;
+    if (!(d.a_bf16 && d.b_bf16) && 2.0 * d.M * d.N * d.K * (double)d.batch <= kFp32Flops)
+        return launch_small_gemm_general(d, stream);
     const MgArgs g = make_args(d);
     const bool a_kc = d.a_k == 1, b_kc = d.b_k == 1;
     if (d.a_bf16 && d.b_bf16) {
