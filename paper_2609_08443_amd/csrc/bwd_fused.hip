@@ -1317,53 +1317,50 @@ __global__ __launch_bounds__(NW * 64, 1) void bwd_proto_kernel(ProtoArgs a) {
     }
 }
 
-// dP[h] = sum of the partials of the segments of head h, in segment order
-__global__ __launch_bounds__(256) void dp_sum_kernel(const int32_t* __restrict__ pair_start,
-                                                     int64_t B, int32_t H, int64_t max_items,
-                                                     const float* __restrict__ partials,
-                                                     int64_t MD, float* __restrict__ dP) {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= (int64_t)H * MD) return;
-    const int64_t h = i / MD, rest = i % MD;
-    int64_t s0 = pair_start[h * B], s1 = pair_start[(h + 1) * B];
+// dP = the partials of a head's segments (or, with per-user prototypes, of a (user,
+// head) pair's) added up; zero where there is none.  A workgroup takes 1024 / G columns of
+// one output: G groups of threads add G consecutive parts of the segments in order,
+// several loads in flight, then the groups' sums are added in order.
+template <int G>
+__global__ __launch_bounds__(256) void dp_sum_kernel(const int32_t* __restrict__ pair_start, int64_t B, int32_t H,
+                                                     bool per_pair, int64_t max_items,
+                                                     const float* __restrict__ partials, int64_t MD,
+                                                     float* __restrict__ dP) {
+    constexpr int COLS = 256 / G;
+    __shared__ float4 part[G > 1 ? 256 : 1];
+    const int64_t o = blockIdx.x;   // output block: head, or b * H + h
+    const int64_t p0 = per_pair ? (o % H) * B + o / H : o * B, p1 = per_pair ? p0 + 1 : p0 + B;
+    int64_t s0 = pair_start[p0], s1 = pair_start[p1];
     s0 = s0 < 0 ? 0 : (s0 > max_items ? max_items : s0);
     s1 = s1 < s0 ? s0 : (s1 > max_items ? max_items : s1);
+    const int g = threadIdx.x / COLS;
+    const int64_t idx = ((int64_t)blockIdx.y * COLS + threadIdx.x % COLS) * 4;
+    const int64_t per = (s1 - s0 + G - 1) / G, k1 = min(s0 + (g + 1) * per, s1);
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8   // several segments' loads in flight; the sum keeps segment order
-    for (int64_t k = s0; k < s1; ++k) {
-        const float4 v = *reinterpret_cast<const float4*>(partials + k * MD + rest);
-        acc.x += v.x;
-        acc.y += v.y;
-        acc.z += v.z;
-        acc.w += v.w;
+    if (idx < MD) {
+#pragma unroll 8
+        for (int64_t k = s0 + g * per; k < k1; ++k) {
+            const float4 v = *reinterpret_cast<const float4*>(partials + k * MD + idx);
+            acc.x += v.x;
+            acc.y += v.y;
+            acc.z += v.z;
+            acc.w += v.w;
+        }
     }
-    *reinterpret_cast<float4*>(dP + i) = acc;
-}
-
-// dP[b,h] = sum of the partials of the segments of pair (b, h), in segment order
-// (per-user prototypes); zero for a pair without tokens
-__global__ __launch_bounds__(256) void dp_pair_sum_kernel(const int32_t* __restrict__ pair_start, int64_t B,
-                                                          int32_t H, int64_t max_items,
-                                                          const float* __restrict__ partials, int64_t MD,
-                                                          float* __restrict__ dP) {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= B * H * MD) return;
-    const int64_t bh = i / MD, rest = i % MD;
-    const int64_t b = bh / H, h = bh % H;
-    const int64_t pr = h * B + b;   // head-major pair order of the work list
-    int64_t s0 = pair_start[pr], s1 = pair_start[pr + 1];
-    s0 = s0 < 0 ? 0 : (s0 > max_items ? max_items : s0);
-    s1 = s1 < s0 ? s0 : (s1 > max_items ? max_items : s1);
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8   // several segments' loads in flight; the sum keeps segment order
-    for (int64_t k = s0; k < s1; ++k) {
-        const float4 v = *reinterpret_cast<const float4*>(partials + k * MD + rest);
-        acc.x += v.x;
-        acc.y += v.y;
-        acc.z += v.z;
-        acc.w += v.w;
+    if constexpr (G > 1) {
+        part[threadIdx.x] = acc;
+        __syncthreads();
+        if (g > 0) return;
+#pragma unroll
+        for (int q = 1; q < G; ++q) {
+            const float4 v = part[q * COLS + threadIdx.x];
+            acc.x += v.x;
+            acc.y += v.y;
+            acc.z += v.z;
+            acc.w += v.w;
+        }
     }
-    *reinterpret_cast<float4*>(dP + i) = acc;
+    if (idx < MD) *reinterpret_cast<float4*>(dP + o * MD + idx) = acc;
 }
 
 template <int D, int NW, bool XV>
@@ -1487,15 +1484,19 @@ hipError_t launch_fused_bwd(const FusedBwdArgs& f, hipStream_t stream) {
         if (e != hipSuccess) return e;
     }
     ProfScope ps("bwd_dp_sum", stream);
-    if (f.p_user) {
-        const int64_t n = f.B * f.H * MD / 4;
-        hipLaunchKernelGGL(dp_pair_sum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                           f.pair_start, f.B, f.H, f.max_items, f.partials, MD, f.dP);
-    } else {
-        const int64_t n = (int64_t)f.H * MD / 4;
-        hipLaunchKernelGGL(dp_sum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                           f.pair_start, f.B, f.H, f.max_items, f.partials, MD, f.dP);
-    }
+    // eight groups where an output has many segments (shared prototypes: those of all
+    // users), one where it has a few
+    const int64_t outs = f.p_user ? f.B * f.H : f.H;
+    if (outs == 0) return hipSuccess;
+    const bool many = f.max_items >= 24 * outs;
+    const int64_t cols = many ? 128 : 1024;
+    const dim3 grid((unsigned)outs, (unsigned)((MD + cols - 1) / cols));
+    if (many)
+        hipLaunchKernelGGL(dp_sum_kernel<8>, grid, dim3(256), 0, stream, f.pair_start, f.B, f.H, f.p_user, f.max_items,
+                           f.partials, MD, f.dP);
+    else
+        hipLaunchKernelGGL(dp_sum_kernel<1>, grid, dim3(256), 0, stream, f.pair_start, f.B, f.H, f.p_user, f.max_items,
+                           f.partials, MD, f.dP);
     return hipGetLastError();
 }
 

@@ -21,82 +21,80 @@ __device__ inline int64_t clamp64(int64_t x, int64_t lo, int64_t hi) {
     return x < lo ? lo : (x > hi ? hi : x);
 }
 
-// Inclusive scan of one int64 per thread over a block of kWorklistThreads.
-__device__ int64_t block_inclusive_scan(int64_t v, int64_t* buf) {
-    const int tid = threadIdx.x;
-    buf[tid] = v;
-    __syncthreads();
-    for (int off = 1; off < kWorklistThreads; off <<= 1) {
-        int64_t add = tid >= off ? buf[tid - off] : 0;
-        __syncthreads();
-        buf[tid] += add;
-        __syncthreads();
-    }
-    int64_t r = buf[tid];
-    __syncthreads();
-    return r;
-}
-
+// One workgroup: per 1024 pairs, their segment counts are scanned (wave shuffles, then
+// the 16 wave totals), then all threads share the segments, each finding its
+// segment's pair by binary search among the scanned starts.  With one thread writing
+// all segments of a pair, a single user's list took up to 100 us (200 segments: 21).
 __global__ __launch_bounds__(kWorklistThreads) void worklist_kernel(
     const int64_t* __restrict__ offsets, int64_t B, int64_t T, int32_t H, int64_t C,
     int64_t n_ranges, int32_t* __restrict__ items, int64_t max_items,
     int32_t* __restrict__ wg_start, int32_t* __restrict__ pair_start,
     int64_t* __restrict__ n_items) {
-    __shared__ int64_t scan_buf[kWorklistThreads];
-    const int tid = threadIdx.x;
+    constexpr int kWaves = kWorklistThreads / 64;
+    __shared__ int64_t starts[kWorklistThreads + 1], wave_total[kWaves];
+    __shared__ int32_t los[kWorklistThreads], his[kWorklistThreads];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (wg_start) {
         for (int64_t i = tid; i <= n_ranges; i += kWorklistThreads) wg_start[i] = -1;
     }
-    __syncthreads();
     const int64_t npairs = (int64_t)H * B;
     int64_t carry = 0;
     for (int64_t base = 0; base < npairs; base += kWorklistThreads) {
         const int64_t p = base + tid;
-        int64_t n = 0, lo = 0, hi = 0, i0 = 0;
-        int32_t h = 0, b = 0;
+        int64_t n = 0, lo = 0, hi = 0;
         if (p < npairs) {
-            h = (int32_t)(p / B);
-            b = (int32_t)(p % B);
+            const int64_t h = p / B, b = p % B;
             lo = clamp64(offsets[b], 0, T);
             hi = clamp64(offsets[b + 1], 0, T);
-            if (hi > lo) {
-                const int64_t g0 = (int64_t)h * T + lo;
-                const int64_t g1 = (int64_t)h * T + hi - 1;
-                i0 = g0 / C;
-                n = g1 / C - i0 + 1;
-            }
+            if (hi > lo) n = (h * T + hi - 1) / C - (h * T + lo) / C + 1;
         }
-        const int64_t incl = block_inclusive_scan(n, scan_buf);
-        const int64_t start = carry + incl - n;
-        if (p < npairs && pair_start) pair_start[p] = (int32_t)(start < max_items ? start : max_items);
-        for (int64_t s = 0; s < n; ++s) {
-            const int64_t k = start + s;
-            if (k >= max_items) break;
-            const int64_t r = i0 + s;
-            const int64_t t0 = lo > r * C - (int64_t)h * T ? lo : r * C - (int64_t)h * T;
-            const int64_t t1 = hi < (r + 1) * C - (int64_t)h * T ? hi : (r + 1) * C - (int64_t)h * T;
+        int64_t incl = n;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t v = __shfl_up((long long)incl, o, 64);
+            if (lane >= o) incl += v;
+        }
+        if (lane == 63) wave_total[w] = incl;
+        __syncthreads();   // (also: wg_start is cleared)
+        for (int i = 0; i < w; ++i) incl += wave_total[i];
+        starts[tid + 1] = incl;
+        if (tid == 0) starts[0] = 0;
+        los[tid] = (int32_t)lo;
+        his[tid] = (int32_t)hi;
+        if (p < npairs && pair_start) pair_start[p] = (int32_t)(carry + incl - n < max_items ? carry + incl - n : max_items);
+        __syncthreads();
+        const int64_t total = starts[kWorklistThreads];
+        const int64_t here = total < max_items - carry ? total : max_items - carry;
+        for (int64_t j = tid; j < here; j += kWorklistThreads) {
+            int a = 0, z = kWorklistThreads - 1;   // the last pair with starts[pair] <= j
+            while (a < z) {
+                const int mid = (a + z + 1) >> 1;
+                if (starts[mid] <= j) a = mid; else z = mid - 1;
+            }
+            const int64_t h = (base + a) / B, b = (base + a) % B, hT = h * T;
+            const int64_t plo = los[a], phi = his[a], r = (hT + plo) / C + (j - starts[a]);
+            const int64_t t0 = plo > r * C - hT ? plo : r * C - hT;
+            const int64_t t1 = phi < (r + 1) * C - hT ? phi : (r + 1) * C - hT;
+            const int64_t k = carry + j;
             int32_t* it = items + k * IT_WORDS;
-            it[IT_B] = b;
-            it[IT_H] = h;
+            it[IT_B] = (int32_t)b;
+            it[IT_H] = (int32_t)h;
             it[IT_T0] = (int32_t)t0;
             it[IT_T1] = (int32_t)t1;
             it[IT_RANGE] = (int32_t)r;
-            it[IT_SPLIT] = n > 1 ? 1 : 0;
-            it[IT_PAIR_FIRST] = (int32_t)start;
+            it[IT_SPLIT] = starts[a + 1] - starts[a] > 1 ? 1 : 0;
+            it[IT_PAIR_FIRST] = (int32_t)(carry + starts[a]);
             it[7] = 0;
-            if (wg_start && r < n_ranges && (int64_t)h * T + t0 == r * C) wg_start[r] = (int32_t)k;
+            if (wg_start && r < n_ranges && hT + t0 == r * C) wg_start[r] = (int32_t)k;
         }
-        // the last thread's inclusive value is the block total
-        if (tid == kWorklistThreads - 1) scan_buf[0] = incl;
-        __syncthreads();
-        carry += scan_buf[0];
-        __syncthreads();
+        carry += total;
+        if (carry > max_items) carry = max_items;
+        __syncthreads();   // the next pairs overwrite the scan
     }
     if (tid == 0) {
-        const int64_t fin = carry < max_items ? carry : max_items;
-        if (pair_start) pair_start[npairs] = (int32_t)fin;
-        if (wg_start) wg_start[n_ranges] = (int32_t)fin;
-        *n_items = fin;
+        if (pair_start) pair_start[npairs] = (int32_t)carry;
+        if (wg_start) wg_start[n_ranges] = (int32_t)carry;
+        *n_items = carry;
     }
 }
 
