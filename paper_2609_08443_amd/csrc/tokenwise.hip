@@ -24,6 +24,8 @@
 //                       with the transposing LDS load).
 //   tw_merge_kernel     rescale-and-add of the partials of a split user, or zero /
 //                       -inf for an empty one.
+#include <type_traits>
+
 #include "sa_internal.h"
 #include "segments.h"
 #include "tile_ops.h"
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
         // past the range read its last token, threads past the tile's chunks
         // reload a chunk they do not store), so the wait before a store counts
         // exactly the newer set's loads.  Rows past the range need no zeros: their
-        // logits are masked to -inf, so their weights are 0 and their V is unused.
+        // weights are set to 0 (and their V is the last token's).
         struct Regs { u32x4 k[C::NCH], v[C::NCH]; };
         Regs ra, rb;
         auto fetch = [&](int ts, Regs& r) __attribute__((always_inline)) {
@@ -228,7 +230,8 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
         for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[jt][r] = 0.f;
-        float mu = -INFINITY;   // running max of this lane's prototype, log2 units
+        float mu = -INFINITY;   // reference of this lane's prototype's weights, log2 units: its
+                                // running max, or at most 8 below it
         float lsum = 0.f;       // running sum over this lane's 16 token rows per tile
         // Wait here for the held operands.  Otherwise the compiler's load-counter
         // waits for them inside the loop also wait for each iteration's prefetch
@@ -238,10 +241,13 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
         for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(pop[kk]));
 
         // tile at ts in LDS buffer buf; the next tile is in `nxt` (stored at the end
-        // of this step into the other buffer), the one after it fetched into `far`
-        auto step = [&](int ts, int buf, Regs& far, const Regs& nxt) __attribute__((always_inline)) {
+        // of this step into the other buffer), the one after it fetched into `far`.
+        // Only the last, ragged tile masks rows, in a copy of its own: left to the
+        // compiler, every tile paid for the masks (about 60 VALU instructions).
+        auto step = [&](int ts, int buf, Regs& far, const Regs& nxt, auto rag) __attribute__((always_inline)) {
+            constexpr bool ragged = decltype(rag)::value;
             const bool more = ts + 32 < t1;
-            fetch(ts + 64, far);
+            if constexpr (!ragged) fetch(ts + 64, far);
             const uint16_t* Ks = reinterpret_cast<const uint16_t*>(smem + C::OFF_K + buf * C::TILE);
             const uint16_t* Vs = reinterpret_cast<const uint16_t*>(smem + C::OFF_V + buf * C::TILE);
             // S[t, m]: lane = prototype, register r = token srow(r, hl)
@@ -251,19 +257,22 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk)
                 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_b128(Ks, swz<D>(l32, 2 * kk + hl)), pop[kk], s, 0, 0, 0);
-            float x[16];
-            float tmax = -INFINITY;
-            const bool ragged = ts + 32 > t1;
+            if constexpr (ragged) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                x[r] = s[r] * ks2;
-                if (ragged && ts + srow(r, hl) >= t1) x[r] = -INFINITY;   // past the user's end
-                tmax = fmaxf(tmax, x[r]);
+                for (int r = 0; r < 16; ++r)
+                    if (ts + srow(r, hl) >= t1) s[r] = -3.4028234664e38f;   // past the user's end
             }
-            tmax = xhalf_max(tmax);
+            // (scale >= 0: the largest logit is the largest product)
+            float tmax = s[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, s[r]);
+            tmax = xhalf_max(tmax) * ks2;
             const float mnew = fmaxf(mu, tmax);
-            // rescale the accumulator rows whose maximum rose (wave-uniform branch)
-            if (__builtin_amdgcn_ballot_w64(mnew > mu) != 0) {
+            // Rescale the accumulator when some prototype's maximum rose by more than 8
+            // (wave-uniform branch).  Until then its weights are relative to the older
+            // maximum, at most 2^8, with the same relative rounding: without the slack a
+            // quarter of the tiles of a long user rescale, with it hardly any but the first.
+            if (__builtin_amdgcn_ballot_w64(mnew > mu + 8.f) != 0) {
                 const float al = exp2f(mu - mnew);     // 0 when mu = -inf
                 lsum *= al;
                 float alr[16];
@@ -277,7 +286,10 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
             float e[16];
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                e[r] = __builtin_amdgcn_exp2f(x[r] - mu);
+                e[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], ks2, -mu));
+                if constexpr (ragged) {
+                    if (ts + srow(r, hl) >= t1) e[r] = 0.f;
+                }
                 lsum += e[r];
             }
             const bf16x8 e0 = pack8(e), e1 = pack8(e + 8);
@@ -287,18 +299,26 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
                 acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(e0, lds_tr_tokens<D>(Vs, lane, jt, 0), acc[jt], 0, 0, 0);
                 acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(e1, lds_tr_tokens<D>(Vs, lane, jt, 1), acc[jt], 0, 0, 0);
             }
-            if (more) store(buf ^ 1, nxt);
+            if (!ragged && more) store(buf ^ 1, nxt);
             __syncthreads();
         };
         // two tiles per trip; the exits sit after each step, so that the path back
         // to the top always comes from the second step (whose pending loads fill
         // the other register set)
-        for (int ts = t0;; ts += 64) {
-            step(ts, 0, ra, rb);
-            if (ts + 32 >= t1) break;
-            step(ts + 32, 1, rb, ra);
-            if (ts + 64 >= t1) break;
+        int ts = t0, last = 0;   // after the whole tiles: the ragged one and its buffer
+        if (t0 + 32 <= t1) {
+            for (;;) {
+                step(ts, 0, ra, rb, std::false_type{});
+                ts += 32;
+                last = 1;
+                if (ts + 32 > t1) break;
+                step(ts, 1, rb, ra, std::false_type{});
+                ts += 32;
+                last = 0;
+                if (ts + 32 > t1) break;
+            }
         }
+        if (ts < t1) step(ts, last, ra, rb, std::true_type{});
         const float ltot = xhalf_add(lsum);   // both halves hold the same prototype
         // rows of this wave: prototypes part*MP + w*32 + srow(r, hl), columns jt*32 + l32
         uint32_t lane_off = (uint32_t)((part * C::MP + w * 32 + 4 * hl) * D + l32);
