@@ -6,6 +6,7 @@
 // Forward (section 3.1), two passes over the keys as in fwd_split.hip:
 //   lse_f32_kernel      lse_t = log sum_m exp(scale <K_t, P_m>)
 //   agg_f32_kernel      sketch_m += exp(scale <K_t, P_m> - lse_t) V_t
+// (or in the second alone, when one workgroup holds all M <= 256 prototypes)
 // Backward (chain rule; the MRLB sum over R targets, section 4.2, is done first):
 //   bwd_token_f32_kernel, a block of 128 tokens against all prototypes, twice:
 //     sweep 1: A = exp(scale S - lse), dV = A^T dY;  then D_t = <V_t, dV_t>
@@ -27,10 +28,11 @@
 // An instruction takes 64 cycles for 4096 FLOPs; everything else (one 4-byte or a
 // quarter of a 16-byte LDS read per instruction, the exponentials) hides beside it.
 // Measured (fp32 VALU path before -> now): layer forward + backward on 9,619 tokens,
-// H = 2, M = 256, d = 64, 1366 -> 305 us; one user of 2,048 tokens, M = 64, d = 64,
-// forward, 44 -> 19 us; distance from float64 the same or smaller on every output.
+// H = 2, M = 256, d = 64, 1366 -> 247 us; one user of 2,048 tokens, M = 64, d = 64,
+// forward, 44 -> 15 us (18 with a log-sum-exp pass of its own); distance from float64 the same or smaller on every output.
 #include <algorithm>
 
+#include "reduce_ops.h"
 #include "sa_internal.h"
 #include "segments.h"
 #include "tile_ops.h"
@@ -248,9 +250,14 @@ struct AggF32Args {
     bool p_user;
     float* sketch;
     float* partials;
+    float* lse_out;   // (ONE) [T,H], or null
 };
 
-template <int D, int NW>
+// ONE: all M prototypes in the workgroup (one part): the log-sum-exp of a tile's
+// tokens comes from its own logits, the waves' (maximum, sum) of each token combined
+// through LDS, and no pass over the keys precedes (4 M d instead of 6 M d executed).
+// `lse` is then an output, or null.
+template <int D, int NW, bool ONE>
 __global__ __launch_bounds__(NW * 64) void agg_f32_kernel(AggF32Args a) {
     using TL = Tile32<D>;
     constexpr int JT = D / 32, THREADS = NW * 64;
@@ -258,6 +265,7 @@ __global__ __launch_bounds__(NW * 64) void agg_f32_kernel(AggF32Args a) {
     float* Kt = sm;                       // [2] tiles
     float* Vt = Kt + 2 * TL::FLOATS;      // [2] tiles
     float* shift = Vt + 2 * TL::FLOATS;   // [2][32]: -lse
+    float2* stats = reinterpret_cast<float2*>(shift + 64);   // (ONE) [NW][32]: a wave's maximum and sum
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l32 = lane & 31, hl = lane >> 5;
     int64_t range;
     int part;
@@ -277,12 +285,14 @@ __global__ __launch_bounds__(NW * 64) void agg_f32_kernel(AggF32Args a) {
             auto row = [&](int i) { return ((int64_t)min(ts + i, t1 - 1) * a.H + h) * D; };
             lk.fetch(a.K, tid, row);
             lv.fetch(a.V, tid, row);
-            ll = a.lse[(int64_t)min(ts + l32, t1 - 1) * a.H + h];
+            if constexpr (!ONE) ll = a.lse[(int64_t)min(ts + l32, t1 - 1) * a.H + h];
         };
         auto store = [&](int ts, int buf) {
             lk.store(Kt + buf * TL::FLOATS, tid, 32);
             lv.store(Vt + buf * TL::FLOATS, tid, t1 - ts);   // V of rows past the segment: zeros
-            if (tid < 32) shift[buf * 32 + tid] = -ll;
+            if constexpr (!ONE) {
+                if (tid < 32) shift[buf * 32 + tid] = -ll;
+            }
         };
         f32x16 acc[JT];
 #pragma unroll
@@ -294,8 +304,36 @@ __global__ __launch_bounds__(NW * 64) void agg_f32_kernel(AggF32Args a) {
         for (int ts = t0, buf = 0; ts < t1; ts += 32, buf ^= 1) {
             const bool more = ts + 32 < t1;
             if (more) fetch(ts + 32);
-            const f32x16 s = TL::rows_dot(Kt + buf * TL::FLOATS, l32, hl, pop);
+            f32x16 s = TL::rows_dot(Kt + buf * TL::FLOATS, l32, hl, pop);
             float e[16];
+            if constexpr (ONE) {
+                // per token: maximum and sum over this wave's prototypes (those past M
+                // count as -inf, and a wave without any as an empty sum)
+                const bool valid = m0 + l32 < a.M;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float x = valid ? s[r] * a.scale : -INFINITY;
+                    const float m = half_max(x);
+                    const float z = half_sum(exp_f32(x - m));
+                    if (l32 == 0) stats[w * 32 + srow(r, hl)] = m0 < a.M ? make_float2(m, z) : make_float2(-INFINITY, 0.f);
+                }
+                __syncthreads();
+                if (tid < 32) {
+                    float m = stats[tid].x;
+#pragma unroll
+                    for (int q = 1; q < NW; ++q) m = fmaxf(m, stats[q * 32 + tid].x);
+                    float z = 0.f;
+#pragma unroll
+                    for (int q = 0; q < NW; ++q) {
+                        const float2 o = stats[q * 32 + tid];
+                        z += o.y == 0.f ? 0.f : o.y * exp_f32(o.x - m);
+                    }
+                    const float l = __builtin_fmaf(__builtin_amdgcn_logf(z), kLn2, m);
+                    shift[buf * 32 + tid] = -l;
+                    if (a.lse_out && ts + tid < t1) a.lse_out[(int64_t)(ts + tid) * a.H + h] = l;
+                }
+                __syncthreads();
+            }
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 e[r] = exp_f32(__builtin_fmaf(s[r], a.scale, shift[buf * 32 + srow(r, hl)]));
@@ -618,6 +656,19 @@ template <int D>
 hipError_t fwd_impl(const SplitFwdArgs& f, hipStream_t stream) {
     const float *K = reinterpret_cast<const float*>(f.K), *V = reinterpret_cast<const float*>(f.V),
                 *P = reinterpret_cast<const float*>(f.P);
+    AggF32Args a{K, V, P, f.offsets, f.lse, f.B, f.T, f.C, f.n_ranges, f.H, f.M, 1, f.scale, f.p_user, f.sketch, f.partials,
+                 nullptr};
+    const int nw = part_waves(f.M);
+    if (f.M <= 32 * nw) {   // one part: no pass for the log-sum-exp
+        a.lse_out = f.lse;
+        const size_t lds = (4 * Tile32<D>::FLOATS + 64 + 64 * nw) * sizeof(float);
+        ProfScope ps("plain_fwd", stream);
+        switch (nw) {
+            case 2: return launch_parts(agg_f32_kernel<D, 2, true>, a, 2, lds, stream);
+            case 4: return launch_parts(agg_f32_kernel<D, 4, true>, a, 4, lds, stream);
+            default: return launch_parts(agg_f32_kernel<D, 8, true>, a, 8, lds, stream);
+        }
+    }
     const int64_t nblk = (f.T + 127) / 128;
     if (nblk * f.H > 0x7fffffff) return hipErrorInvalidValue;
     {
@@ -627,14 +678,10 @@ hipError_t fwd_impl(const SplitFwdArgs& f, hipStream_t stream) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    AggF32Args a{K, V, P, f.offsets, f.lse, f.B, f.T, f.C, f.n_ranges, f.H, f.M, 1, f.scale, f.p_user, f.sketch, f.partials};
     const size_t lds = (4 * Tile32<D>::FLOATS + 64) * sizeof(float);
     ProfScope ps("plain_agg", stream);
-    switch (part_waves(f.M)) {
-        case 2: return launch_parts(agg_f32_kernel<D, 2>, a, 2, lds, stream);
-        case 4: return launch_parts(agg_f32_kernel<D, 4>, a, 4, lds, stream);
-        default: return launch_parts(agg_f32_kernel<D, 8>, a, 8, lds, stream);
-    }
+    if (nw == 4) return launch_parts(agg_f32_kernel<D, 4, false>, a, 4, lds, stream);
+    return launch_parts(agg_f32_kernel<D, 8, false>, a, 8, lds, stream);
 }
 
 template <bool BF16, int D>

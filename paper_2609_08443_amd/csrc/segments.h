@@ -44,7 +44,7 @@ class SegmentWalk {
         const int64_t HT = (int64_t)H * T;
         g_ = range * C;
         end_ = g_ + C < HT ? g_ + C : HT;
-        h_ = T > 0 ? (int32_t)(g_ / T) : 0;
+        h_ = g_ < T || T <= 0 ? 0 : (int32_t)(g_ / T);
         b_ = first_user_after(off, B, T, g_ - (int64_t)h_ * T);
     }
     // the next non-empty segment, or false at the end of the range
@@ -71,7 +71,7 @@ class SegmentWalk {
             s.h = h_;
             s.t0 = (int32_t)t0;
             s.t1 = (int32_t)t1;
-            s.split = (base + lo) / C_ != (base + hi - 1) / C_;
+            s.split = base + lo < range_ * C_ || base + hi > (range_ + 1) * C_;
             s.slot = base + t0 == range_ * C_ ? range_ : n_ranges_ + h_ * B_ + b;
             g_ = base + t1;
             return true;

@@ -1,0 +1,60 @@
+"""Single-precision path (fp32 matrix cores) against the fp64 oracle: forward and
+backward of fp32 inputs, and the backward of bf16 inputs without a fused instance.
+
+Bounds (2-norm per output): every product and sum is fp32.  A weight's relative error is
+that of its logit, an fp32 sum of d products: sqrt(d) 2^-24 |s|, 7e-7 at d = 128 and unit
+logits; gradients chain two such sums.  The bounds are three times that, 2e-6 and 4e-6;
+one operand rounded to bf16 would give 1e-3.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_08443_amd import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sa():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_08443_amd import sa_sketch
+    sa_sketch.lib()
+    return sa_sketch
+
+
+def rel(g, r):
+    return np.linalg.norm(g.cpu().numpy().astype(np.float64) - r) / max(np.linalg.norm(r), 1e-30)
+
+
+# prototype counts around a wave's 32 and the workgroups' 64 / 128 / 256 (one part: no
+# log-sum-exp pass); users of one token, of whole tiles, empty, and split over ranges
+@pytest.mark.parametrize("lengths,H,M,d,dtype,R", [
+    ([33, 0, 1, 64], 2, 1, 64, "fp32", 1), ([40, 7], 1, 33, 128, "fp32", 2), ([31, 0, 65], 2, 64, 128, "fp32", 1),
+    ([70], 3, 65, 64, "fp32", 1), ([129, 2], 1, 127, 128, "fp32", 3), ([64, 64, 0], 2, 129, 64, "fp32", 1),
+    ([50, 300], 1, 255, 64, "fp32", 2), ([90, 33], 2, 257, 128, "fp32", 1), ([45, 0, 77], 1, 385, 64, "fp32", 1),
+    ([3000, 12, 4100, 0, 900], 2, 96, 64, "fp32", 2), ([2000, 5, 700], 1, 520, 64, "fp32", 1),
+    ([33, 0, 1, 64], 2, 33, 64, "bf16", 2), ([300, 7, 2000], 1, 200, 128, "bf16", 1), ([70, 41], 2, 300, 64, "bf16", 3)])
+@pytest.mark.parametrize("want_lse", [True, False])
+def test_forward_and_backward(sa, lengths, H, M, d, dtype, R, want_lse):
+    w = wl.custom(lengths, H, M, d, dtype, seed=sum(lengths) + M + d, R=R, bwd=True)
+    host = wl.host_tensors(w)
+    dev = wl.to_device(host, dtype)
+    print(f"case {w.name} R={R} lse={want_lse}", flush=True)
+    args = dev["K"], dev["V"], dev["P"], dev["offsets"]
+    sk, lse = sa.sketch_fwd(*args, w.scale, want_lse=want_lse)
+    rs, rl = oracle.fwd(host["K"], host["V"], host["P"], host["offsets"], w.scale)
+    assert rel(sk, rs) <= 2e-6
+    if not want_lse:
+        return
+    assert rel(lse, rl) <= 2e-7 * max(1.0, d ** 0.5 / 8) + 2e-7
+    got = sa.sketch_bwd(*args, dev["dsketch"], lse, w.scale)
+    ref = oracle.bwd(host["K"], host["V"], host["P"], host["offsets"], host["dsketch"], w.scale)
+    for name, g, r in zip(("dK", "dV", "dP"), got, ref):
+        # (M = 1: the weight is 1 whatever the logit; dK and dP are zero)
+        if M == 1 and name != "dV":
+            assert float(g.abs().max()) <= 1e-4 * float(got[1].abs().max())
+        else:
+            assert rel(g, r) <= 4e-6, name
