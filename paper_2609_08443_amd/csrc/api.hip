@@ -1462,11 +1462,10 @@ sa_status sa_stca_bwd(const void* Xs, const void* q, const void* Wq, const void*
     if (e == hipSuccess) {
         sa::ProfScope ps("stca_sketch_grads", stream);
         // dXs = alpha^T dC + (scale ds)^T U per user;  dU = (scale ds) Xs
-        e = sa::launch_gemm({Al, bf, Rhk, 1, k, dC, bf, RhD, D, 1, dXs, false, kD, D, k, D, Rh, (int32_t)B, 1.f, false},
-                            stream);
-        if (e == hipSuccess)
-            e = sa::launch_gemm({ds, bf, Rhk, 1, k, U, bf, RhD, D, 1, dXs, false, kD, D, k, D, Rh, (int32_t)B, 1.f,
-                                 true}, stream);
+        // (one product over both contractions: dXs is written once, not read back and
+        // added to: 479 -> 441 us for 32 users with 40 targets, k = 512, D = 1024, h = 16)
+        e = sa::launch_gemm_pair({Al, bf, Rhk, 1, k, dC, bf, RhD, D, 1, dXs, false, kD, D, k, D, Rh, (int32_t)B, 1.f,
+                                  false}, ds, U, stream);
         if (e == hipSuccess)
             e = sa::launch_gemm({ds, bf, Rhk, k, 1, Xs, bf, kD, D, 1, dU, bf, RhD, D, Rh, D, k, (int32_t)B, 1.f, false},
                                 stream);

@@ -44,6 +44,10 @@ struct MgArgs {
     float alpha;
     int32_t accumulate;
     int32_t c_rows16;   // N, c_m, c_z multiples of 8 and C 16-byte aligned
+    // a second pair of operands with the same strides, whose slabs follow the first
+    // pair's k1_slabs (bf16 kernel only): C = alpha (A B + A2 B2)
+    const void *A2 = nullptr, *B2 = nullptr;
+    int32_t k1_slabs = 0x7fffffff;
 };
 
 // One thread's share of a [128 rows][64 k] slab: four 16-byte pieces of 8 bf16,
@@ -343,13 +347,14 @@ struct LtOperand;
 template <int R>
 struct LtOperand<R, true> {
     static constexpr int Q = R / 32;
-    const char* base;
+    const char *base, *base2;   // base2: the second pair's, less the first pair's slabs
     int64_t step;   // bytes from one slab to the next
     uint32_t off[Q];
-    __device__ __forceinline__ void init(const uint16_t* b, int64_t s_row, int64_t /*s_k*/, int row0, int nrows,
-                                         int w, int lane) {
-        base = reinterpret_cast<const char*>(b);
+    __device__ __forceinline__ void init(const uint16_t* b, const uint16_t* b2, int k1, int64_t s_row, int64_t /*s_k*/,
+                                         int row0, int nrows, int w, int lane) {
         step = GBK * 2;
+        base = reinterpret_cast<const char*>(b);
+        base2 = reinterpret_cast<const char*>(b2) - k1 * step;
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             const int row = 8 * (w + 4 * i) + (lane >> 3);
@@ -358,8 +363,9 @@ struct LtOperand<R, true> {
             off[i] = (uint32_t)(((int64_t)gr * s_row + 8 * c) * 2);
         }
     }
-    __device__ __forceinline__ void issue(int kt, uint8_t* lds, int w) {
-        const char* p = base + kt * step;
+    template <bool PAIR>
+    __device__ __forceinline__ void issue(int kt, int k1, uint8_t* lds, int w) {
+        const char* p = (!PAIR || kt < k1 ? base : base2) + kt * step;
 #pragma unroll
         for (int i = 0; i < Q; ++i) lt_dma16(p, off[i], lds + (w + 4 * i) * 1024);
     }
@@ -388,13 +394,14 @@ struct LtOperand<R, false> {
     static constexpr int Q = R / 32, LPR = R / 8;   // loads per thread, lanes per row
     static_assert(64 % LPR == 0, "whole rows per load");
     static constexpr int RPL = 64 / LPR;            // rows per load
-    const char* base;
+    const char *base, *base2;
     int64_t step;
     uint32_t off[Q];
-    __device__ __forceinline__ void init(const uint16_t* b, int64_t /*s_row*/, int64_t s_k, int row0, int nrows,
-                                         int w, int lane) {
-        base = reinterpret_cast<const char*>(b);
+    __device__ __forceinline__ void init(const uint16_t* b, const uint16_t* b2, int k1, int64_t /*s_row*/, int64_t s_k,
+                                         int row0, int nrows, int w, int lane) {
         step = GBK * s_k * 2;
+        base = reinterpret_cast<const char*>(b);
+        base2 = reinterpret_cast<const char*>(b2) - k1 * step;
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             const int idx = (w + 4 * i) * 64 + lane;        // chunk index in the slab
@@ -402,8 +409,9 @@ struct LtOperand<R, false> {
             off[i] = (uint32_t)(((int64_t)k * s_k + col) * 2);
         }
     }
-    __device__ __forceinline__ void issue(int kt, uint8_t* lds, int w) {
-        const char* p = base + kt * step;
+    template <bool PAIR>
+    __device__ __forceinline__ void issue(int kt, int k1, uint8_t* lds, int w) {
+        const char* p = (!PAIR || kt < k1 ? base : base2) + kt * step;
 #pragma unroll
         for (int i = 0; i < Q; ++i) lt_dma16(p, off[i], lds + (w + 4 * i) * 1024);
     }
@@ -434,7 +442,8 @@ __device__ __forceinline__ bf16x8 lt_frag(const uint8_t* lds, int first, int ks,
     }
 }
 
-template <int FM, int FN, int PM, int PN, bool A_KC, bool B_KC, bool C_BF16, int NS>
+// PAIR: a second pair of operands follows the first (MgArgs)
+template <int FM, int FN, int PM, int PN, bool A_KC, bool B_KC, bool C_BF16, int NS, bool PAIR = false>
 __global__ __launch_bounds__(256, (LtCfg<FM, FN, PM, PN, NS>::OCC)) void mfma_gemm_lt_kernel(MgArgs g) {
     using C = LtCfg<FM, FN, PM, PN, NS>;
     __shared__ __attribute__((aligned(16))) uint8_t smem[C::LDS];
@@ -450,14 +459,16 @@ __global__ __launch_bounds__(256, (LtCfg<FM, FN, PM, PN, NS>::OCC)) void mfma_ge
     const int nk = g.K / GBK;
     LtOperand<C::BM, A_KC> opa;
     LtOperand<C::BN, B_KC> opb;
-    opa.init(Ab, g.a_m, g.a_k, m0, g.M, w, lane);
-    opb.init(Bb, g.b_n, g.b_k, n0, g.N, w, lane);
+    const uint16_t* Ab2 = PAIR ? reinterpret_cast<const uint16_t*>(g.A2) + z * g.a_z : Ab;
+    const uint16_t* Bb2 = PAIR ? reinterpret_cast<const uint16_t*>(g.B2) + (g.b_mod > 0 ? z % g.b_mod : z) * g.b_z : Bb;
+    opa.init(Ab, Ab2, g.k1_slabs, g.a_m, g.a_k, m0, g.M, w, lane);
+    opb.init(Bb, Bb2, g.k1_slabs, g.b_n, g.b_k, n0, g.N, w, lane);
     auto stage = [&](int s) { return smem + (s % C::NS) * C::STAGE; };
     // slab kt into the stage of slab position pos
     auto issue = [&](int kt, int pos) __attribute__((always_inline)) {
         uint8_t* st = stage(pos);
-        opa.issue(kt, st, w);
-        opb.issue(kt, st + C::A_BYTES, w);
+        opa.template issue<PAIR>(kt, g.k1_slabs, st, w);
+        opb.template issue<PAIR>(kt, g.k1_slabs, st + C::A_BYTES, w);
     };
 
     f32x16 acc[FM][FN];
@@ -594,6 +605,16 @@ hipError_t lt_launch(MgArgs g, bool c_bf16, int64_t batch, hipStream_t stream) {
     g.tm = (g.M + C::BM - 1) / C::BM;
     g.tn = (g.N + C::BN - 1) / C::BN;
     const int64_t blocks = (int64_t)g.tm * g.tn * batch;
+    if (g.A2) {
+        if constexpr (!A_KC && !B_KC && NS > 1) {
+            if (c_bf16) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((mfma_gemm_lt_kernel<FM, FN, PM, PN, false, false, false, NS, true>), dim3((unsigned)blocks),
+                               dim3(256), 0, stream, g);
+            return hipGetLastError();
+        } else {
+            return hipErrorInvalidValue;
+        }
+    }
     if (c_bf16)
         hipLaunchKernelGGL((mfma_gemm_lt_kernel<FM, FN, PM, PN, A_KC, B_KC, true, NS>), dim3((unsigned)blocks),
                            dim3(256), 0, stream, g);
@@ -769,6 +790,31 @@ hipError_t launch_gemm(const GemmDesc& d, hipStream_t stream) {
     if (a_kc) return mgemm_launch<true, false>(g, d.a_bf16, d.b_bf16, d.c_bf16, d.batch, stream);
     if (b_kc) return mgemm_launch<false, true>(g, d.a_bf16, d.b_bf16, d.c_bf16, d.batch, stream);
     return mgemm_launch<false, false>(g, d.a_bf16, d.b_bf16, d.c_bf16, d.batch, stream);
+}
+
+hipError_t launch_gemm_pair(const GemmDesc& d, const void* A2, const void* B2, hipStream_t stream) {
+    if (d.batch <= 0 || d.M <= 0 || d.N <= 0) return hipSuccess;
+    const bool a_kc = d.a_k == 1, b_kc = d.b_k == 1;
+    // (instances: both operands contiguous along their rows, fp32 results)
+    if (d.a_bf16 && d.b_bf16 && !a_kc && !b_kc && !d.c_bf16 && gemm_on_matrix_cores(d) && al16(A2) && al16(B2)) {
+        GemmDesc both = d;   // the shape for the whole contraction
+        both.K = 2 * d.K;
+        const int shape = choose_lt(both, a_kc, b_kc);
+        if (shape >= 0) {
+            MgArgs g = make_args(both);
+            g.A2 = A2;
+            g.B2 = B2;
+            g.k1_slabs = d.K / GBK;
+            return lt_run(shape, g, a_kc, b_kc, d.c_bf16, d.batch, stream);
+        }
+    }
+    hipError_t e = launch_gemm(d, stream);
+    if (e != hipSuccess) return e;
+    GemmDesc second = d;
+    second.A = A2;
+    second.B = B2;
+    second.accumulate = true;
+    return launch_gemm(second, stream);
 }
 
 int gemm_tile_shapes() { return (int)(sizeof(kLtShapes) / sizeof(kLtShapes[0])); }

@@ -196,6 +196,9 @@ int device_cus();
 int gemm_tile_shapes();
 hipError_t launch_gemm_tile_shape(const GemmDesc& d, int shape, hipStream_t stream);
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t stream);
+// C = alpha (A B + A2 B2) (+ C), A2 and B2 with the strides and types of A and B: one
+// product over both contractions where the bf16 kernel takes it, else two.
+hipError_t launch_gemm_pair(const GemmDesc& d, const void* A2, const void* B2, hipStream_t stream);
 hipError_t launch_small_gemm_general(const GemmDesc& d, hipStream_t stream);
 
 // Reordered single-query STCA rows (stca.hip), over [rows][k] fp32 logits already
