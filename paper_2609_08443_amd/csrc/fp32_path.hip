@@ -28,7 +28,7 @@
 // An instruction takes 64 cycles for 4096 FLOPs; everything else (one 4-byte or a
 // quarter of a 16-byte LDS read per instruction, the exponentials) hides beside it.
 // Measured (fp32 VALU path before -> now): layer forward + backward on 9,619 tokens,
-// H = 2, M = 256, d = 64, 1366 -> 247 us; one user of 2,048 tokens, M = 64, d = 64,
+// H = 2, M = 256, d = 64, 1366 -> 195 us; one user of 2,048 tokens, M = 64, d = 64,
 // forward, 44 -> 15 us (18 with a log-sum-exp pass of its own); distance from float64 the same or smaller on every output.
 #include <algorithm>
 
@@ -365,9 +365,16 @@ struct BwdF32Args {
     float* partials;       // [n_ranges + H B][M][d]
 };
 
-// Workgroup = 4 waves of 32 tokens of one (user, head) segment of a 128-token range;
-// P and dY tiles of 32 prototypes stream through LDS, twice.  Result tiles have
-// prototypes (or features) as rows and a token per lane.
+// Workgroup = 4 waves of 32 tokens: up to 128 tokens of one user, counted from the
+// user's first, and one head; P and dY tiles of 32 prototypes stream through LDS,
+// twice.  Result tiles have prototypes (or features) as rows and a token per lane.
+//
+// User b's blocks are numbers floor(off[b] / 128) + b on: floor(off[b+1] / 128) + b + 1
+// is at least ceil(length / 128) further, so floor(T / 128) + B numbers a head hold every
+// user's blocks, found by binary search.  With ranges of 128 tokens cut anywhere, the
+// ranges that held two users' tokens did two passes over the prototypes one after the
+// other and the launch waited for them (9,619 tokens of 8 users, H = 2, M = 256, d = 64:
+// 121 us, now 68).
 template <bool BF16, int D, bool XV>
 __global__ __launch_bounds__(256) void bwd_token_f32_kernel(BwdF32Args a) {
     using TL = Tile32<D>;
@@ -379,27 +386,43 @@ __global__ __launch_bounds__(256) void bwd_token_f32_kernel(BwdF32Args a) {
     const int64_t MD = (int64_t)a.M * D;
     const int ntiles = (a.M + 31) / 32;
 
-    // rows of this range that no user holds get zero gradients
-    const int64_t HT = (int64_t)a.H * a.T, g_end = min((blockIdx.x + 1) * a.C, HT);
-    int64_t g_done = blockIdx.x * a.C;
-    auto zero_rows = [&](int64_t g1) {
-        for (int64_t i = g_done * D + tid; i < g1 * D; i += 256) {
-            const int64_t g = i / D, row = (g % a.T) * a.H + g / a.T, o = row * D + i % D;
+    const int64_t nblk = a.T / 128 + a.B + 1, blk = blockIdx.x % nblk;
+    const int h = (int)(blockIdx.x / nblk);
+    const int64_t first = a.B > 0 ? seg_clamp(a.off[0], a.T) : 0, last = a.B > 0 ? seg_clamp(a.off[a.B], a.T) : 0;
+    // tokens before the first user's and after the last one's: zero gradients
+    for (int64_t t = blk; t < a.T; t += nblk) {
+        if (t >= first && t < last) {
+            t += (last - 1 - t) / nblk * nblk;   // this workgroup's next one is past the users'
+            continue;
+        }
+        for (int j = tid; j < D; j += 256) {
+            const int64_t o = (t * a.H + h) * D + j;
             if constexpr (XV) {
                 if (!a.dx_add) a.dX[o] = 0.f;
             } else {
                 a.dK[o] = 0.f;
                 a.dV[o] = 0.f;
             }
-            if (i % D == 0) a.Dbuf[row] = 0.f;
+            if (j == 0) a.Dbuf[t * a.H + h] = 0.f;
         }
-    };
-    SegmentWalk walk(a.off, a.B, a.T, a.H, a.C, 0, blockIdx.x);
+    }
+    // the last user whose first number is not past blk
+    int64_t ub = 0;
+    for (int64_t hi = a.B; ub + 1 < hi;) {
+        const int64_t mid = (ub + hi) >> 1;
+        if (seg_clamp(a.off[mid], a.T) / 128 + mid <= blk) ub = mid; else hi = mid;
+    }
+    if (a.B == 0) return;
     Segment sg;
-    while (walk.next(sg)) {
-        const int h = sg.h;
-        zero_rows((int64_t)h * a.T + sg.t0);
-        g_done = (int64_t)h * a.T + sg.t1;
+    {
+        const int64_t lo = seg_clamp(a.off[ub], a.T), hi = seg_clamp(a.off[ub + 1], a.T);
+        const int64_t t0 = lo + (blk - lo / 128 - ub) * 128;
+        if (t0 < lo || t0 >= hi) return;
+        sg.b = (int32_t)ub;
+        sg.t0 = (int32_t)t0;
+        sg.t1 = (int32_t)(t0 + 128 < hi ? t0 + 128 : hi);
+    }
+    {
         const int64_t pair = (int64_t)sg.b * a.H + h;
         const int tok = sg.t0 + w * 32 + l32;
         const bool live = tok < sg.t1;
@@ -516,7 +539,6 @@ __global__ __launch_bounds__(256) void bwd_token_f32_kernel(BwdF32Args a) {
                 }
         }
     }
-    zero_rows(g_end);
 }
 
 // ---------------------------------------------------------------- backward: prototype side
@@ -686,13 +708,14 @@ hipError_t fwd_impl(const SplitFwdArgs& f, hipStream_t stream) {
 
 template <bool BF16, int D>
 hipError_t bwd_impl(const PlainBwdArgs& f, hipStream_t stream) {
-    BwdF32Args a{f.K, f.V, f.P, f.offsets, f.dY, f.lse, f.B, f.T, 128, 0, f.H, f.M, 1, f.scale, f.p_user, f.dx_add,
+    BwdF32Args a{f.K, f.V, f.P, f.offsets, f.dY, f.lse, f.B, f.T, f.C, f.n_ranges, f.H, f.M, 1, f.scale, f.p_user, f.dx_add,
                  f.Dbuf, f.dK, f.dV, f.dX, f.dP, f.partials};
     const int64_t HT = (int64_t)f.H * f.T;
     if (HT > 0) {
         ProfScope ps("plain_bwd_token", stream);
         const size_t lds = 4 * Tile32<D>::FLOATS * sizeof(float);
-        const int64_t blocks = (HT + a.C - 1) / a.C;
+        const int64_t blocks = (f.T / 128 + f.B + 1) * f.H;
+        if (blocks > 0x7fffffff) return hipErrorInvalidValue;
         auto kern = f.dX ? bwd_token_f32_kernel<BF16, D, true> : bwd_token_f32_kernel<BF16, D, false>;
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)lds);
@@ -700,8 +723,6 @@ hipError_t bwd_impl(const PlainBwdArgs& f, hipStream_t stream) {
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, stream, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        a.C = f.C;
-        a.n_ranges = f.n_ranges;
         ProfScope ps2("plain_bwd_proto", stream);
         const size_t lds2 = (4 * Tile32<D>::FLOATS + 128) * sizeof(float);
         switch (proto_waves(f.M, D)) {
