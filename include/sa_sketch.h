@@ -120,8 +120,8 @@ sa_status sa_sketch_fwd(const void* K, const void* V, const void* P,
  * tight serving loops, harnesses that forbid hipMalloc.  Same operation,
  * arguments, kernels, results (bit for bit) and errors as sa_sketch_fwd, with
  * these differences:
- *  * the work list, the per-range partial sketches and (plain path, lse = NULL)
- *    the lse scratch live in a device array of SA_NOALLOC_SCRATCH_BYTES that the
+ *  * the per-range partial sketches and (two-pass paths, lse = NULL) the lse
+ *    scratch live in a device array of SA_NOALLOC_SCRATCH_BYTES that the
  *    library holds on every device it runs on until the process ends (looked up
  *    once per device, on the first call with that device current);
  *  * a shape whose scratch exceeds that size returns SA_ERR_WORKSPACE (the
@@ -423,7 +423,8 @@ sa_status sa_stca_bwd(const void* Xs, const void* q, const void* Wq, const void*
                       void* stream);
 
 /*
- * Work list used by the fused forward, exposed for exact testing.
+ * The forward's ranges as a list of segments (the fused backward's work list),
+ * exposed for exact testing.
  *
  * The (head, token) pairs are laid out head-major in one index space of
  * length H*T, cut into n_ranges = ceil(H*T / chunk_tokens) equal ranges (one

@@ -814,7 +814,7 @@ const char* sa_last_error(void) { return g_last_error; }
 size_t sa_sketch_fwd_workspace_size(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d,
                                     sa_dtype dtype) {
     if (check_common(B, T, H, M, d, 1.0f, dtype) != SA_OK) return 0;
-    // the plain path needs lse scratch only when the caller passes lse = NULL;
+    // the two-pass paths need lse scratch only when the caller passes lse = NULL;
     // size for that case so one query serves both
     return plan_fwd(B, T, H, M, d, dtype, true).total;
 }
