@@ -122,10 +122,13 @@ __global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __re
                 *reinterpret_cast<u32x4*>(dst + swz<D>(idx / C::KCH, idx % C::KCH)) = reg[i];
             }
         };
-        float mu[TT], z[TT];   // log2 units
+        // log2 units; the maximum starts at the lowest finite value, so that it stays
+        // finite while a lane has seen only masked rows (which the scale may take to
+        // -inf) or logits of -inf, and no difference of two maxima is a NaN
+        float mu[TT], z[TT];
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) {
-            mu[tt] = -INFINITY;
+            mu[tt] = -3.4028234664e38f;
             z[tt] = 0.f;
         }
         // a logits tile into the running maximum and sum; in the ragged one, rows past
@@ -142,7 +145,7 @@ __global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __re
 #pragma unroll
                 for (int r = 1; r < 16; ++r) t = fmaxf(t, s[tt][r]);
                 const float mn = fmaxf(mu[tt], t * ks2);
-                z[tt] *= __builtin_amdgcn_exp2f(mu[tt] - mn);   // 0 on the first tile
+                z[tt] *= __builtin_amdgcn_exp2f(mu[tt] - mn);   // z is 0 on the first tile
                 float sum[2] = {0.f, 0.f};
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {

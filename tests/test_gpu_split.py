@@ -76,3 +76,43 @@ def test_split_fwd_infinite_values(sa):
     for b, j in enumerate((5, 63, 0)):
         keep = [c for c in range(64) if c != j]
         assert np.linalg.norm(g[b, 0][:, keep] - ref[b, 0][:, keep]) <= 2e-6 * np.linalg.norm(ref[b, 0][:, keep])
+
+
+# A prototype tile with few valid rows (none in some lane) and scales that take a masked
+# row's value to -inf, on batches that reach one, two and four waves a token set (by the
+# number of 256-token workgroups a head: 256 CUs, 128 and fewer).  The logits are fp32
+# sums of size `scale`: sqrt(d) 2^-24 scale = 5e-7 scale each, three times that beside
+# the bound of unit scale.
+@pytest.mark.parametrize("lengths,H", [([40, 0, 31], 1), ([9000, 0, 24500], 1), ([9000, 33, 24500], 2)])
+@pytest.mark.parametrize("M", [1, 3, 4, 33, 36, 68, 100])
+@pytest.mark.parametrize("scale", [0.7, 1.0, 4.0])
+def test_split_fwd_few_valid_rows_large_scale(sa, lengths, H, M, scale):
+    w = wl.custom(lengths, H, M, 64, "bf16", seed=M)
+    host = wl.host_tensors(w)
+    dev = wl.to_device(host, "bf16")
+    print(f"case {w.name} scale={scale}", flush=True)
+    sk, lse = sa.sketch_fwd(dev["K"], dev["V"], dev["P"], dev["offsets"], scale)
+    ref, rlse = oracle.fwd(host["K"], host["V"], host["P"], host["offsets"], scale)
+    bound = 2e-6 + 1.5e-6 * scale
+    assert np.linalg.norm(sk.cpu().numpy() - ref) <= bound * np.linalg.norm(ref)
+    assert np.abs(lse.cpu().numpy() - rlse).max() <= bound * max(1.0, np.abs(rlse).max())
+
+
+@pytest.mark.parametrize("lengths,M,d", [([70, 33], 200, 64), ([33000], 100, 64), ([70, 33], 640, 128),
+                                         ([70, 33], 512, 128)])
+@pytest.mark.parametrize("scale", [0.125, 4.0])
+def test_split_fwd_prototypes_out_of_use(sa, lengths, M, d, scale):
+    """Logits of -inf (prototypes switched off) have weight 0, also where a wave has no other."""
+    w = wl.custom(lengths, 1, M, d, "bf16", seed=M)
+    host = wl.host_tensors(w)
+    host["K"][:, :, 0] = np.abs(host["K"][:, :, 0]) + 1.0
+    host["P"][:, 32:64, 0] = -np.inf
+    host["K"] = torch.from_numpy(host["K"]).bfloat16().float().numpy()
+    dev = wl.to_device(host, "bf16")
+    print(f"case {w.name} scale={scale}", flush=True)
+    sk, lse = sa.sketch_fwd(dev["K"], dev["V"], dev["P"], dev["offsets"], scale)
+    ref, rlse = oracle.fwd(host["K"], host["V"], host["P"], host["offsets"], scale)
+    assert np.all(np.isfinite(ref)) and not sk[:, :, 32:64].any()
+    bound = 2e-2 if (M, d) == (512, 128) else 2e-6 + 1.5e-6 * scale * (d / 64) ** 0.5
+    assert np.linalg.norm(sk.cpu().numpy() - ref) <= bound * np.linalg.norm(ref)
+    assert np.abs(lse.cpu().numpy() - rlse).max() <= (2e-6 + 3e-6 * scale) * max(1.0, np.abs(rlse).max())
