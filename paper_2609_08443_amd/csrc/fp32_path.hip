@@ -44,6 +44,7 @@ namespace {
 using namespace tile;
 
 constexpr float kLn2 = 0.6931471805599453f;
+constexpr float kFloatMax = 3.4028234664e38f;
 
 __device__ inline f32x16 mfma(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 __device__ inline f32x16 zero16() {
@@ -179,7 +180,8 @@ __global__ __launch_bounds__(256) void lse_f32_kernel(const float* __restrict__ 
         const float* Pg = P + (p_user ? b * H + h : (int64_t)h) * M * D;
         TileLoad<false, D, 256> ld;
         auto rows = [&](int t) { return [=](int i) { return (int64_t)min(t * 32 + i, M - 1) * D; }; };
-        float mu = -INFINITY, z = 0.f;   // log2 units
+        // log2 units; the maximum stays finite while all logits are -inf
+        float mu = -kFloatMax, z = 0.f;
         ld.fetch(Pg, tid, rows(0));
         __syncthreads();   // the previous round is done with the tiles
         ld.store(tile[0], tid, 32);
@@ -189,14 +191,14 @@ __global__ __launch_bounds__(256) void lse_f32_kernel(const float* __restrict__ 
             if (more) ld.fetch(Pg, tid, rows(t + 1));
             const f32x16 s = TL::rows_dot(tile[t & 1], l32, hl, kop);
             const bool ragged = t * 32 + 32 > M;   // rows past M: no part in the maximum or the sum
-            float x[16], m = -3.4028234664e38f;
+            float x[16], m = -kFloatMax;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 x[r] = s[r];
                 m = fmaxf(m, ragged && t * 32 + srow(r, hl) >= M ? m : x[r]);
             }
             const float mn = fmaxf(mu, m * ks2);
-            z *= __builtin_amdgcn_exp2f(mu - mn);   // 0 on the first tile
+            z *= __builtin_amdgcn_exp2f(mu - mn);   // z is 0 on the first tile
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], ks2, -mn));
@@ -324,12 +326,13 @@ __global__ __launch_bounds__(NW * 64) void agg_f32_kernel(AggF32Args a) {
             float e[16];
             if constexpr (ONE) {
                 // per token: maximum and sum over this wave's prototypes (those past M
-                // count as -inf, and a wave without any as an empty sum)
+                // count as -inf, and a wave without any as an empty sum; the maximum
+                // stays finite where all of a wave's logits are -inf)
                 const bool valid = m0 + l32 < a.M;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const float x = valid ? s[r] * a.scale : -INFINITY;
-                    const float m = half_max(x);
+                    const float m = fmaxf(half_max(x), -kFloatMax);
                     const float z = half_sum(exp_f32(x - m));
                     if (l32 == 0) stats[w * 32 + srow(r, hl)] = m0 < a.M ? make_float2(m, z) : make_float2(-INFINITY, 0.f);
                 }

@@ -58,3 +58,22 @@ def test_forward_and_backward(sa, lengths, H, M, d, dtype, R, want_lse):
             assert float(g.abs().max()) <= 1e-4 * float(got[1].abs().max())
         else:
             assert rel(g, r) <= 4e-6, name
+
+
+# one pass (M <= 256: per-wave maxima combined through LDS) and two (a lane's running maximum)
+@pytest.mark.parametrize("M,d", [(64, 64), (129, 64), (256, 128), (300, 64), (640, 64)])
+@pytest.mark.parametrize("scale", [0.125, 4.0])
+def test_prototypes_out_of_use(sa, M, d, scale):
+    """Logits of -inf (prototypes switched off) have weight 0, also where a wave has no
+    other.  The bound of unit logits plus that of logits of size scale: sqrt(d) 2^-24 scale
+    is 7e-7 scale at d = 128, three times that."""
+    w = wl.custom([70, 0, 33], 2, M, d, "fp32", seed=M)
+    host = wl.host_tensors(w)
+    host["K"][:, :, 0] = np.abs(host["K"][:, :, 0]) + 1.0
+    host["P"][:, :32, 0] = -np.inf
+    dev = wl.to_device(host, "fp32")
+    sk, lse = sa.sketch_fwd(dev["K"], dev["V"], dev["P"], dev["offsets"], scale)
+    rs, rl = oracle.fwd(host["K"], host["V"], host["P"], host["offsets"], scale)
+    assert np.all(np.isfinite(rs)) and not sk[:, :, :32].any()
+    assert rel(sk, rs) <= 2e-6 + 2e-6 * scale
+    assert rel(lse, rl) <= 2e-6 + 2e-6 * scale
