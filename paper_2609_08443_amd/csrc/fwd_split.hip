@@ -297,7 +297,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
     const float ks2 = a.scale * kLog2e;
     const float rks2 = ks2 > 0.f ? 1.0f / ks2 : 0.f;
     const int64_t MD = (int64_t)a.M * D;
-    const uint32_t row_stride = (uint32_t)a.H * D;
+    const int64_t row_stride = (int64_t)a.H * D;
     const int m0 = part * C::MP + w * 32;            // the wave's first prototype
     const int prow = min(m0 + l32, a.M - 1);         // this lane's (rows past M repeat the last)
 
@@ -316,19 +316,20 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
         // token), so the wait before a store counts exactly the newer set's loads.
         struct Regs { u32x4 k[C::NCH], v[C::NCH]; float l; };
         Regs ra, rb;
-        const char* Kb = reinterpret_cast<const char*>(a.K + ((int64_t)t0 * a.H + h) * D);
-        const char* Vb = reinterpret_cast<const char*>(a.V + ((int64_t)t0 * a.H + h) * D);
-        const float* Lb = a.lse + (int64_t)t0 * a.H + h;
+        // Rows are addressed in 64 bits: with many prototype parts the ranges are few and a
+        // segment may span more than 4 GB of K (one user of 1M tokens, 16 heads, d = 128).
         auto fetch = [&](int ts, Regs& r) __attribute__((always_inline)) {
+            const int64_t tb = __builtin_amdgcn_readfirstlane(min(ts, t1 - 1));
+            const int last = t1 - 1 - (int)tb;
+            const int64_t base = (tb * a.H + h) * D;
 #pragma unroll
             for (int c = 0; c < C::NCH; ++c) {
                 const int idx = (tid + c * C::THREADS) % C::LD_CHUNKS;
-                const int row = min(ts + idx / C::KCH, t1 - 1) - t0;
-                const uint32_t o = ((uint32_t)row * row_stride + (uint32_t)((idx % C::KCH) * 8)) * 2;
-                r.k[c] = *reinterpret_cast<const u32x4*>(Kb + o);
-                r.v[c] = *reinterpret_cast<const u32x4*>(Vb + o);
+                const int64_t o = base + min(idx / C::KCH, last) * row_stride + (idx % C::KCH) * 8;
+                r.k[c] = *reinterpret_cast<const u32x4*>(a.K + o);
+                r.v[c] = *reinterpret_cast<const u32x4*>(a.V + o);
             }
-            r.l = Lb[(uint32_t)(min(ts + l32, t1 - 1) - t0) * (uint32_t)a.H];
+            r.l = a.lse[(tb + min(l32, last)) * a.H + h];
         };
         auto store = [&](int ts, int buf, const Regs& r) __attribute__((always_inline)) {
             uint16_t* Kd = reinterpret_cast<uint16_t*>(smem + C::OFF_K + buf * C::TILE);

@@ -116,3 +116,22 @@ def test_split_fwd_prototypes_out_of_use(sa, lengths, M, d, scale):
     bound = 2e-2 if (M, d) == (512, 128) else 2e-6 + 1.5e-6 * scale * (d / 64) ** 0.5
     assert np.linalg.norm(sk.cpu().numpy() - ref) <= bound * np.linalg.norm(ref)
     assert np.abs(lse.cpu().numpy() - rlse).max() <= (2e-6 + 3e-6 * scale) * max(1.0, np.abs(rlse).max())
+
+
+def test_split_fwd_segment_beyond_4_gib(sa):
+    """A segment's last tokens lie more than 4 GiB behind its first one (16 ranges of M = 4096
+    prototypes hold whole users); float64 torch on the last head."""
+    H, M, d, T = 64, 4096, 128, 264_000
+    assert sa.fwd_chunk_tokens(1, T, H, M, d, sa.SA_BF16) >= T and T * H * d * 2 > 1 << 32
+    g = torch.Generator(device="cuda").manual_seed(4)
+    X = torch.empty((T, H, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    P = (torch.randn(H, M, d, generator=g, device="cuda") * d ** -0.5).to(torch.bfloat16)
+    sk, lse = sa.sketch_fwd(X, X, P, torch.tensor([0, T], device="cuda"))
+    x, p = X[:, -1].double(), P[-1].double()
+    ref, rl = torch.zeros(M, d, dtype=torch.float64, device="cuda"), []
+    for part in x.split(16384):
+        s = part @ p.t() * d ** -0.5
+        rl.append(torch.logsumexp(s, 1))
+        ref += torch.exp(s - rl[-1][:, None]).t() @ part
+    assert float((sk[0, -1].double() - ref).norm() / ref.norm()) <= 2e-6
+    assert float((lse[:, -1].double() - torch.cat(rl)).abs().max()) <= 2e-6 * float(lse.max())
