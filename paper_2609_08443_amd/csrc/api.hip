@@ -242,7 +242,9 @@ BwdPlan plan_bwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype
         set_ranges((int64_t)H * T, sa::plain_bwd_ranges(M, d), &p.C, &p.n_ranges);
         p.off_dY = carve(sizeof(float) * (size_t)B * H * M * d);
         p.off_D = carve(sizeof(float) * (size_t)T * H);
-        p.off_part = carve(sizeof(float) * (size_t)(p.n_ranges + H * B) * M * d);
+        // partial slots: a range's own, and one a pair (per-user prototypes) or a head
+        // (shared ones, whose heads' tokens are one run of ranges whatever B is)
+        p.off_part = carve(sizeof(float) * (size_t)(p.n_ranges + (p_user ? H * B : H)) * M * d);
     }
     p.total = off;
     return p;

@@ -377,7 +377,7 @@ struct BwdF32Args {
     float* Dbuf;
     float *dK, *dV, *dX;   // dX: K and V are one tensor, its gradient is written there
     float* dP;             // [H,M,d], or [B,H,M,d] with p_user
-    float* partials;       // [n_ranges + H B][M][d]
+    float* partials;       // [n_ranges + H, or n_ranges + H B with p_user][M][d]
 };
 
 // Workgroup = 4 waves of 32 tokens: up to 128 tokens of one user, counted from the

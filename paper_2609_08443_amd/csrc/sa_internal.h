@@ -263,7 +263,7 @@ struct PlainBwdArgs {
     bool dx_add;             // with dX: add to it
     float* Dbuf;             // [T,H]
     float *dK, *dV, *dX, *dP;   // dX non-null: K = V, its gradient goes there (dK, dV unused)
-    float* partials;         // [n_ranges + H B][M][d]
+    float* partials;         // [n_ranges + H, or n_ranges + H B with p_user][M][d]
 };
 hipError_t launch_plain_bwd(const PlainBwdArgs& f, bool bf16, hipStream_t stream);
 

@@ -260,3 +260,16 @@ def test_block_saved_offsets():
     assert offs[0, 3] - offs[0, 2] >= 2 * B * H * M * d       # P' (bf16) before lse
     for args in ((n, sa.SA_BF16, n, 1), (n, sa.SA_BF16, -1, 1), (n, sa.SA_BF16, 0, 4), (0, sa.SA_BF16, 0, 1)):
         assert L.sa_block_saved_offset(B, T, H, M, d, *args) == bad
+
+
+@pytest.mark.parametrize("dtype,H,M,d", [(sa.SA_FP32, 2, 128, 64), (sa.SA_FP32, 3, 33, 128), (sa.SA_BF16, 2, 200, 64)])
+def test_single_precision_backward_partials_do_not_depend_on_users(dtype, H, M, d):
+    """The partials of shared prototypes are one a range and one a head, also with B = 0: a user
+    adds its dY block (and nothing else) to the workspace."""
+    size = lambda B: sa.bwd_workspace_size(B, 1000, H, M, d, dtype, 1)
+    up = lambda n: (n + 255) // 256 * 256
+    block = 4 * H * M * d
+    assert size(1) - size(0) == up(block)
+    assert size(9) - size(1) == up(9 * block) - up(block)
+    # a range of tokens, at least two a head here, and a head's own slot
+    assert size(0) >= 4 * 1000 * H + 3 * block

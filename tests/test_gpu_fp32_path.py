@@ -77,3 +77,20 @@ def test_prototypes_out_of_use(sa, M, d, scale):
     assert np.all(np.isfinite(rs)) and not sk[:, :, :32].any()
     assert rel(sk, rs) <= 2e-6 + 2e-6 * scale
     assert rel(lse, rl) <= 2e-6 + 2e-6 * scale
+
+
+@pytest.mark.parametrize("dtype,H,M,d", [("fp32", 2, 128, 64), ("fp32", 3, 33, 128), ("bf16", 2, 200, 64)])
+def test_backward_without_users(sa, dtype, H, M, d):
+    """B = 0 with tokens: zero gradients, and nothing written past the workspace (heads begin
+    inside a range, so each head's slot is used)."""
+    T, code = 1000, sa.SA_FP32 if dtype == "fp32" else sa.SA_BF16
+    dt = dict(dtype=torch.float32 if dtype == "fp32" else torch.bfloat16, device="cuda")
+    K, V, P = torch.randn(T, H, d, **dt), torch.randn(T, H, d, **dt), torch.randn(H, M, d, **dt)
+    n = sa.bwd_workspace_size(0, T, H, M, d, code, 1)
+    ws = torch.full((n + 4 * M * d * H,), 77, dtype=torch.uint8, device="cuda")
+    out = sa.sketch_bwd(K, V, P, torch.zeros(1, dtype=torch.int64, device="cuda"),
+                        torch.empty((0, 1, H, M, d), device="cuda"), torch.zeros(T, H, device="cuda"),
+                        None, *(torch.full_like(x, 5.0, dtype=torch.float32) for x in (K, V, P)), workspace=ws)
+    for name, g in zip(("dK", "dV", "dP"), out):
+        assert not g.any(), name
+    assert bool((ws[n:] == 77).all())
