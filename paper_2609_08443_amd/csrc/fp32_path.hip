@@ -175,6 +175,7 @@ __global__ __launch_bounds__(256) void lse_f32_kernel(const float* __restrict__ 
             lo = seg_clamp(off[b], T);
             hi = seg_clamp(off[b + 1], T);
             if (lo >= blk1) break;
+            if (hi <= lo) b = next_user_after(off, b + 1, B, T, lo) - 1;   // no tokens: past those like it
             if (hi <= lo || hi <= blk0) continue;
         }
         const float* Pg = P + (p_user ? b * H + h : (int64_t)h) * M * D;

@@ -102,6 +102,7 @@ __global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __re
             lo = seg_clamp(off[b], T);
             hi = seg_clamp(off[b + 1], T);
             if (lo >= blk1) break;
+            if (hi <= lo) b = next_user_after(off, b + 1, B, T, lo) - 1;   // no tokens: past those like it
             if (hi <= lo || hi <= blk0) continue;
         }
         const uint16_t* Pg = P + (p_user ? b * H + h : (int64_t)h) * M * D;

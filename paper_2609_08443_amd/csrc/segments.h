@@ -30,6 +30,23 @@ __device__ inline int64_t first_user_after(const int64_t* off, int64_t B, int64_
     return lo;
 }
 
+// the same from user b on, in steps that double: a run of n users without tokens costs
+// about 2 log2 n reads (one at a time, 4,000 of them between two users took 1.1 ms)
+__device__ inline int64_t next_user_after(const int64_t* off, int64_t b, int64_t B, int64_t T, int64_t t) {
+    int64_t lo = b, hi = b, step = 1;
+    while (hi < B && seg_clamp(off[hi + 1], T) <= t) {
+        lo = hi + 1;
+        hi = lo + step;
+        step *= 2;
+    }
+    if (hi > B) hi = B;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (seg_clamp(off[mid + 1], T) > t) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+
 struct Segment {
     int32_t b, h;       // user and head
     int32_t t0, t1;     // tokens [t0, t1)
@@ -65,6 +82,7 @@ class SegmentWalk {
             const int32_t b = (int32_t)b_++;
             if (t1 <= t0) {
                 if (lo >= lim) g_ = end_;   // begins after this range
+                else b_ = next_user_after(off_, b_, B_, T_, t);
                 continue;
             }
             s.b = b;

@@ -135,3 +135,35 @@ def test_split_fwd_segment_beyond_4_gib(sa):
         ref += torch.exp(s - rl[-1][:, None]).t() @ part
     assert float((sk[0, -1].double() - ref).norm() / ref.norm()) <= 2e-6
     assert float((lse[:, -1].double() - torch.cat(rl)).abs().max()) <= 2e-6 * float(lse.max())
+
+
+@pytest.mark.parametrize("M,dtype", [(128, "bf16"), (200, "bf16"), (128, "fp32")])
+def test_users_without_tokens_cost_their_zeros(sa, M, dtype):
+    """4,000 users without tokens between others (and, in two heads, at each head's end): their zero
+    sketches are 0.13 GB a head and right, and the call stays within ten times that of the users with
+    tokens alone (a walk over them one at a time took 1.1 ms, 18 times as long)."""
+    few = [2000, 300, 1500, 2500, 700, 90, 1800, 1110]
+
+    def timed(lengths):
+        w = wl.custom(lengths, 2, M, 64, dtype, seed=1)
+        dev = wl.device_tensors(w)
+        args = dev["K"], dev["V"], dev["P"], dev["offsets"]
+        sk, lse = sa.sketch_fwd(*args)
+        ws = torch.empty(sa.fwd_workspace_size(len(lengths), sum(lengths), 2, M, 64, sa._dtype_code(dev["K"])), dtype=torch.uint8, device="cuda")
+        best = 1e9
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(5):
+                sa.sketch_fwd(*args, sketch=sk, lse=lse, workspace=ws)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return sk, best
+
+    sk0, t0 = timed(few)
+    lengths = few[:4] + [0] * 4000 + few[4:]
+    sk1, t1 = timed(lengths)
+    assert not sk1[4:4004].any()
+    assert float((sk1[:4] - sk0[:4]).norm()) <= 1e-5 * float(sk0[:4].norm())   # (partials added in other groups)
+    assert t1 <= 10 * t0, (t0, t1)
