@@ -195,7 +195,7 @@ TwPlan plan_tokenwise(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_
 // ---------------------------------------------------------------- backward plan
 struct BwdPlan {
     bool fused = false;
-    bool per_item = false;   // a workgroup a segment (fused)
+    bool per_item = false;   // workgroups share segments, not ranges (fused)
     int64_t C = 0, n_ranges = 0, max_items = 0;
     size_t off_dY = 0, off_D = 0, off_part = 0;
     size_t off_nitems = 0, off_wgstart = 0, off_pairstart = 0, off_items = 0, off_ymj = 0,
@@ -223,14 +223,16 @@ BwdPlan plan_bwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype
         p.C = C;
         p.n_ranges = (HT + C - 1) / C;
         p.max_items = p.n_ranges + (int64_t)H * B;
-        // Ranges of one token block: a workgroup for each segment rather than for each
-        // range.  A range with two users' tokens is two blocks, and the launch waited
-        // for the workgroup that did both (8 users, 7.6K tokens, H = 2, d = 128,
-        // M = 1024: 145 -> 83 us; 8 users, 25K, H = 1, d = 64, M = 512: 35 -> 26 us).  Longer
-        // ranges keep one workgroup each: their count is what fits on the CUs at once.
+        // Ranges of one token block: the workgroups share the segments, not the ranges.
+        // A range with two users' tokens is two blocks, and the launch waited for the
+        // workgroup that did both (8 users, 7.6K tokens, H = 2, d = 128, M = 1024:
+        // 145 -> 83 us; 8 users, 25K, H = 1, d = 64, M = 512: 35 -> 26 us).  The segments'
+        // number is known on the device only: dealing out the most there can be left
+        // whole XCDs idle where users end at range boundaries.  Longer ranges keep
+        // one workgroup each: their count is what fits on the CUs at once.
         p.per_item = C == 128;
         p.off_nitems = carve(sizeof(int64_t));
-        p.off_wgstart = carve(sizeof(int32_t) * (p.max_items + 1));
+        p.off_wgstart = carve(sizeof(int32_t) * (p.n_ranges + 1));
         p.off_pairstart = carve(sizeof(int32_t) * ((int64_t)H * B + 1));
         p.off_items = carve(sizeof(int32_t) * sa::IT_WORDS * p.max_items);
         p.off_ymj = carve(sizeof(uint16_t) * (size_t)B * H * M * d);
@@ -693,7 +695,8 @@ sa_status run_bwd(const void* K, const void* V, const void* P, const int64_t* of
         f.items = reinterpret_cast<int32_t*>(ws + plan.off_items);
         f.wg_start = reinterpret_cast<int32_t*>(ws + plan.off_wgstart);
         f.pair_start = reinterpret_cast<int32_t*>(ws + plan.off_pairstart);
-        f.n_ranges = plan.per_item && plan.n_ranges > 0 ? plan.max_items : plan.n_ranges;
+        f.n_items = plan.per_item ? reinterpret_cast<const int64_t*>(ws + plan.off_nitems) : nullptr;
+        f.n_ranges = plan.n_ranges;
         f.max_items = plan.max_items;
         f.B = B;
         f.T = T;
@@ -719,7 +722,7 @@ sa_status run_bwd(const void* K, const void* V, const void* P, const int64_t* of
                                     const_cast<int32_t*>(f.items), plan.max_items,
                                     const_cast<int32_t*>(f.wg_start),
                                     const_cast<int32_t*>(f.pair_start),
-                                    reinterpret_cast<int64_t*>(ws + plan.off_nitems), stream, plan.per_item);
+                                    reinterpret_cast<int64_t*>(ws + plan.off_nitems), stream);
         }
         if (e != hipSuccess) return hip_fail(e, "work list launch");
         e = sa::launch_fused_bwd(f, stream);

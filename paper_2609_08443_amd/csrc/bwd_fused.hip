@@ -29,6 +29,7 @@
 //          accumulates in registers with K^T read by the transposing LDS load;
 //          one partial per work-list segment, summed per head in segment order
 //          (deterministic).
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -342,7 +343,8 @@ struct TokArgs {
     const uint16_t* Yjm;
     const float* lse;
     const int32_t* items;
-    const int32_t* wg_start;
+    const int32_t* wg_start;   // (without n_items)
+    const int64_t* n_items;    // non-null: segments shared by their number
     int64_t max_items;
     int64_t T;
     int32_t B, H, M;
@@ -371,11 +373,19 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void bwd_token_kernel(TokArgs a) {
     // The workgroups of one XCD take the token blocks of that XCD's ranges in
     // turn (workgroup i of the XCD: blocks i, i + nx, i + 2 nx, ...), so that at
     // any time they work on neighbouring blocks, mostly of one (user, head),
-    // whose prototype-block stream then stays in that XCD's L2.
-    const int64_t nr = gridDim.x, xq = nr / 8, xrem = nr % 8, xcd = blockIdx.x % 8;
-    const int64_t lw = blockIdx.x / 8, nx = xq + (xcd < xrem ? 1 : 0);
-    const int64_t first_range = xcd * xq + (xcd < xrem ? xcd : xrem);
-    const int64_t k0 = a.wg_start[first_range], k1 = a.wg_start[first_range + nx];
+    // whose prototype-block stream then stays in that XCD's L2.  With n_items the
+    // XCDs share the segments evenly instead of the ranges (see launch_fused_bwd).
+    const int64_t xcd = blockIdx.x % 8, lw = blockIdx.x / 8, nx = share8(gridDim.x, xcd);
+    int64_t k0, k1;
+    if (a.n_items) {
+        const int64_t n = *a.n_items < a.max_items ? *a.n_items : a.max_items;
+        k0 = start8(n, xcd);
+        k1 = k0 + share8(n, xcd);
+    } else {
+        const int64_t first_range = start8(gridDim.x, xcd);
+        k0 = a.wg_start[first_range];
+        k1 = a.wg_start[first_range + nx];
+    }
     if (k0 < 0 || k1 < k0 || k1 > a.max_items) return;
     const float ks2 = a.scale * kLog2e;
     const int nblk = a.M / 32;   // >= 4
@@ -715,11 +725,18 @@ __global__ __launch_bounds__(256, 1) void bwd_token_held_kernel(TokArgs a) {
     float* stg = reinterpret_cast<float*>(smem + C::OFF_STG) + w * C::STG_FLOATS;
 
     // block assignment as in bwd_token_kernel: the workgroups of an XCD take the
-    // token blocks of that XCD's ranges in turn
-    const int64_t nr = gridDim.x, xq = nr / 8, xrem = nr % 8, xcd = blockIdx.x % 8;
-    const int64_t lw = blockIdx.x / 8, nx = xq + (xcd < xrem ? 1 : 0);
-    const int64_t first_range = xcd * xq + (xcd < xrem ? xcd : xrem);
-    const int64_t k0 = a.wg_start[first_range], k1 = a.wg_start[first_range + nx];
+    // token blocks of that XCD's ranges (or its share of the segments) in turn
+    const int64_t xcd = blockIdx.x % 8, lw = blockIdx.x / 8, nx = share8(gridDim.x, xcd);
+    int64_t k0, k1;
+    if (a.n_items) {
+        const int64_t n = *a.n_items < a.max_items ? *a.n_items : a.max_items;
+        k0 = start8(n, xcd);
+        k1 = k0 + share8(n, xcd);
+    } else {
+        const int64_t first_range = start8(gridDim.x, xcd);
+        k0 = a.wg_start[first_range];
+        k1 = a.wg_start[first_range + nx];
+    }
     if (k0 < 0 || k1 < k0 || k1 > a.max_items) return;
     const TokSeq<C::TB> seq{a.items, k1, a.T, a.B, a.H};
     const float ks2 = a.scale * kLog2e;
@@ -1043,7 +1060,8 @@ struct ProtoArgs {
     const float* lse;
     const float* Dbuf;
     const int32_t* items;
-    const int32_t* wg_start;
+    const int32_t* wg_start;   // (without n_items)
+    const int64_t* n_items;    // non-null: segments shared by their number
     int64_t max_items;
     int64_t T;
     int64_t n_ranges;
@@ -1071,17 +1089,26 @@ __global__ __launch_bounds__(NW * 64, 1) void bwd_proto_kernel(ProtoArgs a) {
     const int64_t xcd = blockIdx.x % 8, jx = blockIdx.x / 8;
     const int part = (int)(jx % a.parts);          // prototypes [part*MP, (part+1)*MP)
     const int64_t ix = jx / a.parts;
-    const int64_t q8 = a.n_ranges / 8, r8 = a.n_ranges % 8;
-    if (ix >= q8 + (xcd < r8 ? 1 : 0)) return;     // this XCD has fewer ranges
-    const int64_t range = xcd * q8 + (xcd < r8 ? xcd : r8) + ix;
-    const int64_t k0 = a.wg_start[range], k1 = a.wg_start[range + 1];
-    if (k0 < 0 || k1 < k0 || k1 > a.max_items) return;
+    int64_t k0, k1, kstep = 1;
+    if (a.n_items) {   // the XCD's share of the segments, its workgroups in turn
+        const int64_t n = *a.n_items < a.max_items ? *a.n_items : a.max_items;
+        k0 = start8(n, xcd) + ix;
+        k1 = start8(n, xcd) + share8(n, xcd);
+        kstep = gridDim.x / 8 / a.parts;
+        if (k0 < 0 || k1 > a.max_items) return;
+    } else {
+        if (ix >= share8(a.n_ranges, xcd)) return;     // this XCD has fewer ranges
+        const int64_t range = start8(a.n_ranges, xcd) + ix;
+        k0 = a.wg_start[range];
+        k1 = a.wg_start[range + 1];
+        if (k0 < 0 || k1 < k0 || k1 > a.max_items) return;
+    }
     const float ks2 = a.scale * kLog2e;
     const int64_t MD = (int64_t)a.M * D;
     const uint32_t row_stride = (uint32_t)a.H * D;
     int64_t cur_p = -1;
 
-    for (int64_t k = k0; k < k1; ++k) {
+    for (int64_t k = k0; k < k1; k += kstep) {
         const int32_t* it = a.items + k * IT_WORDS;
         const int b = it[IT_B], h = it[IT_H], t0 = it[IT_T0], t1 = it[IT_T1];
         if (b < 0 || b >= a.B || h < 0 || h >= a.H || t0 < 0 || t1 < t0 || t1 > a.T) continue;
@@ -1363,6 +1390,11 @@ __global__ __launch_bounds__(256) void dp_sum_kernel(const int32_t* __restrict__
     if (idx < MD) *reinterpret_cast<float4*>(dP + o * MD + idx) = acc;
 }
 
+// Most workgroups a part of the prototype side over segments shared by their number: two
+// a CU (training steps with 256 / 512 / 1024: 1,000 users of 16 tokens, M = 1024, d = 64
+// 662 / 671 / 684 us, M = 128 135 / 131 / 132; 200 of 100, M = 128, d = 64 77 / 73 / 73).
+constexpr int64_t kProtoWgs = 512;
+
 template <int D, int NW, bool XV>
 hipError_t launch_token(const TokArgs& a, int64_t n_ranges, hipStream_t stream) {
     using C = TokCfg<D, NW>;
@@ -1454,32 +1486,40 @@ hipError_t launch_fused_bwd(const FusedBwdArgs& f, hipStream_t stream) {
     if (f.n_ranges > 0) {
         TokArgs t;
         t.K = f.K; t.V = f.V; t.P = f.P; t.Pjm = f.Pjm; t.Ymj = f.Ymj; t.Yjm = f.Yjm;
-        t.lse = f.lse; t.items = f.items; t.wg_start = f.wg_start; t.max_items = f.max_items;
+        t.lse = f.lse; t.items = f.items; t.wg_start = f.wg_start; t.n_items = f.n_items; t.max_items = f.max_items;
         t.T = f.T; t.B = (int32_t)f.B; t.H = f.H; t.M = f.M; t.scale = f.scale;
         t.dK = f.dK; t.dV = f.dV; t.dX = f.dX; t.Dbuf = f.Dbuf; t.p_user = f.p_user; t.dx_add = f.dx_add;
         const bool xv = f.dX != nullptr;
+        // Segments shared by their number (n_items): at most the workgroups that fit on
+        // the CUs at once, which take an XCD's segments in turn; their number is device
+        // data, so the grid covers the most there can be.
+        int64_t wgs = f.n_ranges, pwgs = f.n_ranges;
+        if (f.n_items) {
+            wgs = std::min<int64_t>(f.max_items, (int64_t)device_cus() * fused_bwd_ranges_per_cu());
+            pwgs = std::min<int64_t>(f.max_items, kProtoWgs);
+        }
         hipError_t e;
         {
             ProfScope ps("bwd_token", stream);
-            e = f.d == 64 ? launch_token_d<64>(t, xv, f.n_ranges, stream)
-                          : launch_token_d<128>(t, xv, f.n_ranges, stream);
+            e = f.d == 64 ? launch_token_d<64>(t, xv, wgs, stream)
+                          : launch_token_d<128>(t, xv, wgs, stream);
         }
         if (e != hipSuccess) return e;
         ProtoArgs p;
         p.K = f.K; p.V = f.V; p.P = f.P; p.Ymj = f.Ymj; p.lse = f.lse; p.Dbuf = f.Dbuf;
-        p.items = f.items; p.wg_start = f.wg_start; p.max_items = f.max_items; p.T = f.T;
+        p.items = f.items; p.wg_start = f.wg_start; p.n_items = f.n_items; p.max_items = f.max_items; p.T = f.T;
         p.B = (int32_t)f.B; p.H = f.H; p.M = f.M; p.scale = f.scale; p.partials = f.partials;
         p.p_user = f.p_user;
         const int mp = fused_bwd_part(f.M, f.d);
         ProfScope ps("bwd_proto", stream);
         // eight waves (two per SIMD) when the part has at least 32 prototypes per wave
         if (f.d == 64) {
-            e = mp == 128 ? launch_proto<64, 32, 4>(p, xv, f.n_ranges, stream)
-              : mp == 256 ? launch_proto<64, 32, 8>(p, xv, f.n_ranges, stream)
-                          : launch_proto<64, 64, 8>(p, xv, f.n_ranges, stream);
+            e = mp == 128 ? launch_proto<64, 32, 4>(p, xv, pwgs, stream)
+              : mp == 256 ? launch_proto<64, 32, 8>(p, xv, pwgs, stream)
+                          : launch_proto<64, 64, 8>(p, xv, pwgs, stream);
         } else {
-            e = mp == 128 ? launch_proto<128, 32, 4>(p, xv, f.n_ranges, stream)
-                          : launch_proto<128, 32, 8>(p, xv, f.n_ranges, stream);
+            e = mp == 128 ? launch_proto<128, 32, 4>(p, xv, pwgs, stream)
+                          : launch_proto<128, 32, 8>(p, xv, pwgs, stream);
         }
         if (e != hipSuccess) return e;
     }

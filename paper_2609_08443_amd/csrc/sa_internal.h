@@ -40,12 +40,11 @@ class ProfScope {
 // ---------------------------------------------------------------------------
 
 // Work list over the head-major (h, t) index space cut into ranges of C tokens.
-// wg_start[n_ranges + 1] and pair_start[H*B + 1] may be null.  With per_item, wg_start
-// has max_items + 1 entries, one start a segment (and empty ones after the last).
+// wg_start[n_ranges + 1] and pair_start[H*B + 1] may be null.
 hipError_t launch_worklist(const int64_t* offsets, int64_t B, int64_t T, int32_t H,
                            int64_t C, int64_t n_ranges, int32_t* items, int64_t max_items,
                            int32_t* wg_start, int32_t* pair_start, int64_t* n_items,
-                           hipStream_t stream, bool per_item = false);
+                           hipStream_t stream);
 
 // Fused bf16 forward (matrix cores).  Returns hipErrorInvalidValue for a
 // (d, M) it has no instance for.
@@ -105,6 +104,7 @@ struct FusedBwdArgs {
     const int32_t* items;
     const int32_t* wg_start;
     const int32_t* pair_start;
+    const int64_t* n_items;   // non-null: workgroups share the segments by their number, not by ranges
     int64_t n_ranges;
     int64_t max_items;
     int64_t B, T;

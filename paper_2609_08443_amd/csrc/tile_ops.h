@@ -60,10 +60,9 @@ __device__ inline uint4 scale8(uint4 v, float f) {
 // the prototype and dY blocks they stream are shared in that L2.  XCD x takes
 // ranges [x*q + min(x, n%8), ...) with q = n/8, one more when x < n%8: a
 // bijection of [0, n).
-__device__ inline int64_t xcd_range(int64_t b, int64_t n) {
-    const int64_t q = n / 8, rem = n % 8, x = b % 8, i = b / 8;
-    return x * q + (x < rem ? x : rem) + i;
-}
+__device__ inline int64_t start8(int64_t n, int64_t x) { return x * (n / 8) + (x < n % 8 ? x : n % 8); }
+__device__ inline int64_t share8(int64_t n, int64_t x) { return n / 8 + (x < n % 8 ? 1 : 0); }
+__device__ inline int64_t xcd_range(int64_t b, int64_t n) { return start8(n, b % 8) + b / 8; }
 
 __device__ inline int perm16(int t) { return (t & ~12) | ((t & 4) << 1) | ((t & 8) >> 1); }
 

@@ -29,12 +29,12 @@ __global__ __launch_bounds__(kWorklistThreads) void worklist_kernel(
     const int64_t* __restrict__ offsets, int64_t B, int64_t T, int32_t H, int64_t C,
     int64_t n_ranges, int32_t* __restrict__ items, int64_t max_items,
     int32_t* __restrict__ wg_start, int32_t* __restrict__ pair_start,
-    int64_t* __restrict__ n_items, bool per_item) {
+    int64_t* __restrict__ n_items) {
     constexpr int kWaves = kWorklistThreads / 64;
     __shared__ int64_t starts[kWorklistThreads + 1], wave_total[kWaves];
     __shared__ int32_t los[kWorklistThreads], his[kWorklistThreads];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    if (wg_start && !per_item) {
+    if (wg_start) {
         for (int64_t i = tid; i <= n_ranges; i += kWorklistThreads) wg_start[i] = -1;
     }
     const int64_t npairs = (int64_t)H * B;
@@ -85,18 +85,15 @@ __global__ __launch_bounds__(kWorklistThreads) void worklist_kernel(
             it[IT_SPLIT] = starts[a + 1] - starts[a] > 1 ? 1 : 0;
             it[IT_PAIR_FIRST] = (int32_t)(carry + starts[a]);
             it[7] = 0;
-            if (wg_start && !per_item && r < n_ranges && hT + t0 == r * C) wg_start[r] = (int32_t)k;
+            if (wg_start && r < n_ranges && hT + t0 == r * C) wg_start[r] = (int32_t)k;
         }
         carry += total;
         if (carry > max_items) carry = max_items;
         __syncthreads();   // the next pairs overwrite the scan
     }
-    if (wg_start && per_item) {   // start k for segment k, empty after the last
-        for (int64_t i = tid; i <= max_items; i += kWorklistThreads) wg_start[i] = (int32_t)(i < carry ? i : carry);
-    }
     if (tid == 0) {
         if (pair_start) pair_start[npairs] = (int32_t)carry;
-        if (wg_start && !per_item) wg_start[n_ranges] = (int32_t)carry;
+        if (wg_start) wg_start[n_ranges] = (int32_t)carry;
         *n_items = carry;
     }
 }
@@ -153,9 +150,9 @@ __global__ __launch_bounds__(256) void merge_ranges_kernel(const int64_t* __rest
 hipError_t launch_worklist(const int64_t* offsets, int64_t B, int64_t T, int32_t H, int64_t C,
                            int64_t n_ranges, int32_t* items, int64_t max_items,
                            int32_t* wg_start, int32_t* pair_start, int64_t* n_items,
-                           hipStream_t stream, bool per_item) {
+                           hipStream_t stream) {
     hipLaunchKernelGGL(worklist_kernel, dim3(1), dim3(kWorklistThreads), 0, stream, offsets, B,
-                       T, H, C, n_ranges, items, max_items, wg_start, pair_start, n_items, per_item);
+                       T, H, C, n_ranges, items, max_items, wg_start, pair_start, n_items);
     return hipGetLastError();
 }
 
