@@ -532,13 +532,17 @@ int agg_waves(int32_t M) {
 
 }  // namespace
 
-int64_t split_fwd_ranges(int32_t M, bool bf16_weights, int64_t HT) {
+int64_t split_fwd_ranges(int32_t M, bool bf16_weights, int64_t HT, int64_t pairs) {
     // two waves per SIMD of every CU in one round of workgroups, at most two
     // workgroups per CU; ranges of at least 128 (bf16 weights) or 64 tokens, below
     // which a range's partial costs more than its tiles (M = 512, d = 128, 2K tokens,
-    // us: 16 ranges 23, 32 25, 63 27)
+    // us: 16 ranges 23, 32 25, 63 27).  Shorter ones, down to a tile, where the mean user
+    // is shorter: a range's users are done one after the other, a tile or more each
+    // (512 users of 8 tokens, M = 256, d = 128: ranges of 128 93 us, of 32 45; 64 users of
+    // 64: 128 23, 64 18).
     const int nw = agg_waves(M);
-    const int64_t parts = (M + 32 * nw - 1) / (32 * nw), least = bf16_weights ? 128 : 64;
+    const int64_t parts = (M + 32 * nw - 1) / (32 * nw);
+    const int64_t least = std::clamp<int64_t>(HT / std::max<int64_t>(pairs, 1), kTileTokens, bf16_weights ? 128 : 64);
     const int64_t r = std::min<int64_t>((int64_t)device_cus() * (nw == 8 ? 1 : 2) / parts, (HT + least - 1) / least);
     return r < 1 ? 1 : r;
 }

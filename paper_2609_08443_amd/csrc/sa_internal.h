@@ -84,8 +84,8 @@ struct SplitFwdArgs {
     float* lse;        // [T,H]
     float* partials;   // [n_ranges + H B][M][d]
 };
-// token ranges that fill the device once
-int64_t split_fwd_ranges(int32_t M, bool bf16_weights, int64_t HT);
+// token ranges that fill the device once, fewer for few tokens (HT in `pairs` = H B pairs)
+int64_t split_fwd_ranges(int32_t M, bool bf16_weights, int64_t HT, int64_t pairs);
 hipError_t launch_split_fwd(const SplitFwdArgs& f, hipStream_t stream);
 // sketch[b,h] = sum of the partial sketches of a split (user, head) pair, in
 // segment order; zero for empty pairs; untouched for single-segment pairs.  Without

@@ -273,3 +273,13 @@ def test_single_precision_backward_partials_do_not_depend_on_users(dtype, H, M, 
     assert size(9) - size(1) == up(9 * block) - up(block)
     # a range of tokens, at least two a head here, and a head's own slot
     assert size(0) >= 4 * 1000 * H + 3 * block
+
+
+@pytest.mark.parametrize("M,d,dtype", [(256, 128, sa.SA_BF16), (512, 64, sa.SA_BF16), (200, 64, sa.SA_BF16)])
+def test_two_pass_ranges_follow_the_mean_user(M, d, dtype):
+    """Short batches: a range's users are done one after the other, so ranges of many short users
+    go down to a token tile; those of longer users stay at 128 (64: fp32 weights) tokens."""
+    chunk = lambda B, n: sa.fwd_chunk_tokens(B, B * n, 1, M, d, dtype)
+    most = 64 if M % 128 else 128
+    assert chunk(512, 8) == 32 and chunk(64, 16) == 32 and chunk(64, 64) == 64
+    assert chunk(8, 512) == most and chunk(1, 4096) == most
