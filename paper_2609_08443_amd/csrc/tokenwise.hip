@@ -24,6 +24,7 @@
 //                       with the transposing LDS load).
 //   tw_merge_kernel     rescale-and-add of the partials of a split user, or zero /
 //                       -inf for an empty one.
+#include <algorithm>
 #include <type_traits>
 
 #include "sa_internal.h"
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(NW * 64, 1) void tw_fused_kernel(TwArgs a) {
     }
 }
 
-// A workgroup merges ROWS = 256 / (D / 4) prototype rows of a split pair, D / 4
+// A workgroup merges ROWS = 256 / (D / 4) prototype rows of a split pair at a time, D / 4
 // threads (four columns each) a row: the (max, sum) of the row's segments are read
 // once by the row's threads in turn, then every thread rescales and adds its columns,
 // several segments' loads in flight; the sums keep segment order.
@@ -363,31 +364,31 @@ __global__ __launch_bounds__(256) void tw_merge_kernel(const int64_t* __restrict
     const int64_t h = blockIdx.x / B, b = blockIdx.x % B;
     const PairSlots ps(seg_clamp(off[b], T), seg_clamp(off[b + 1], T), b, h, B, T, C, n_ranges);
     if (ps.count == 1) return;       // written directly by the fused kernel
-    const int64_t m = (int64_t)blockIdx.y * ROWS + threadIdx.x / TPR;
-    if (m >= M) return;
     const int j = (threadIdx.x % TPR) * 4;
     const int64_t MD = (int64_t)M * D;
-    float mx = -INFINITY;
-    for (int64_t i = threadIdx.x % TPR; i < ps.count; i += TPR) mx = fmaxf(mx, stats[ps.slot(i) * M + m].x);
+    for (int64_t m = (int64_t)blockIdx.y * ROWS + threadIdx.x / TPR; m < M; m += (int64_t)gridDim.y * ROWS) {
+        float mx = -INFINITY;
+        for (int64_t i = threadIdx.x % TPR; i < ps.count; i += TPR) mx = fmaxf(mx, stats[ps.slot(i) * M + m].x);
 #pragma unroll
-    for (int o = 1; o < TPR; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    float l = 0.f;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int o = 1; o < TPR; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        float l = 0.f;
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 8
-    for (int64_t i = 0; i < ps.count; ++i) {
-        const int64_t k = ps.slot(i);
-        const float2 st = stats[k * M + m];
-        const float4 x = *reinterpret_cast<const float4*>(partials + k * MD + m * D + j);
-        const float f = exp2f(st.x - mx);
-        l += f * st.y;
-        v.x += f * x.x;
-        v.y += f * x.y;
-        v.z += f * x.z;
-        v.w += f * x.w;
+        for (int64_t i = 0; i < ps.count; ++i) {
+            const int64_t k = ps.slot(i);
+            const float2 st = stats[k * M + m];
+            const float4 x = *reinterpret_cast<const float4*>(partials + k * MD + m * D + j);
+            const float f = exp2f(st.x - mx);
+            l += f * st.y;
+            v.x += f * x.x;
+            v.y += f * x.y;
+            v.z += f * x.z;
+            v.w += f * x.w;
+        }
+        const float rl = l > 0.f ? 1.0f / l : 0.f;
+        *reinterpret_cast<float4*>(sketch + (b * H + h) * MD + m * D + j) = make_float4(v.x * rl, v.y * rl, v.z * rl, v.w * rl);
+        if (lse_m && j == 0) lse_m[(b * H + h) * M + m] = l > 0.f ? mx * kLn2 + __logf(l) : -INFINITY;
     }
-    const float rl = l > 0.f ? 1.0f / l : 0.f;
-    *reinterpret_cast<float4*>(sketch + (b * H + h) * MD + m * D + j) = make_float4(v.x * rl, v.y * rl, v.z * rl, v.w * rl);
-    if (lse_m && j == 0) lse_m[(b * H + h) * M + m] = l > 0.f ? mx * kLn2 + __logf(l) : -INFINITY;
 }
 
 template <int D, int NW>
@@ -439,7 +440,8 @@ hipError_t launch_tokenwise_merge(const TokenwiseArgs& f, hipStream_t stream) {
     const int64_t npairs = (int64_t)f.H * f.B;
     if (npairs == 0) return hipSuccess;
     const int rows = 256 / (f.d / 4);
-    const dim3 grid((unsigned)npairs, (unsigned)((f.M + rows - 1) / rows));
+    // (few workgroups a pair where there are many pairs, as in launch_merge_ranges)
+    const dim3 grid((unsigned)npairs, (unsigned)std::min<int64_t>((f.M + rows - 1) / rows, std::max<int64_t>(4, kMergeWgs / npairs)));
     const float2* st = reinterpret_cast<const float2*>(f.stats);
     if (f.d == 64)
         hipLaunchKernelGGL(tw_merge_kernel<64>, grid, dim3(256), 0, stream, f.offsets, f.B, f.T, f.H, f.M, f.C,

@@ -10,6 +10,8 @@
 // over prototypes), the sketch of a user is a plain sum over its tokens, so
 // the partial sketches of a user cut across ranges merge by addition; there is
 // no rescaling step as in a token-wise softmax.
+#include <algorithm>
+
 #include "sa_internal.h"
 #include "segments.h"
 
@@ -101,48 +103,58 @@ __global__ __launch_bounds__(kWorklistThreads) void worklist_kernel(
 // ---------------------------------------------------------------- split-L merge
 // sketch[b,h] = the sum of a split pair's partials; zero for an empty one; a pair
 // held by one range is written by its own workgroup.  Without offsets there is one
-// user, of all T tokens.  A workgroup takes 1024 / G columns: G groups of threads add
-// G consecutive parts of the segments in token order, several loads in flight, and
-// the groups' sums are added in order.
+// user, of all T tokens.  A workgroup takes 1024 / G columns at a time: G groups of
+// threads add G consecutive parts of the segments in token order, several loads in
+// flight, and the groups' sums are added in order.
 template <int G>
 __global__ __launch_bounds__(256) void merge_ranges_kernel(const int64_t* __restrict__ off, int64_t B, int64_t T,
                                                            int32_t H, int64_t C, int64_t n_ranges,
                                                            const float* __restrict__ partials, int64_t MD,
                                                            float* __restrict__ sketch) {
-    constexpr int COLS = 256 / G;
+    constexpr int COLS = 256 / G, INFLIGHT = 8;
     __shared__ float4 part[G > 1 ? 256 : 1];
     const int64_t h = blockIdx.x / B, b = blockIdx.x % B;
     const PairSlots ps(off ? seg_clamp(off[b], T) : 0, off ? seg_clamp(off[b + 1], T) : T, b, h, B, T, C, n_ranges);
     if (ps.count == 1) return;
     const int g = threadIdx.x / COLS;
-    const int64_t idx = ((int64_t)blockIdx.y * COLS + threadIdx.x % COLS) * 4;
     const int64_t per = (ps.count + G - 1) / G;
     const int64_t i1 = min((g + 1) * per, ps.count);
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (idx < MD) {
-#pragma unroll 16
-        for (int64_t i = g * per; i < i1; ++i) {
-            const float4 v = *reinterpret_cast<const float4*>(partials + ps.slot(i) * MD + idx);
-            acc.x += v.x;
-            acc.y += v.y;
-            acc.z += v.z;
-            acc.w += v.w;
-        }
-    }
-    if constexpr (G > 1) {
-        part[threadIdx.x] = acc;
-        __syncthreads();
-        if (g > 0) return;
+    for (int64_t c0 = (int64_t)blockIdx.y * 4 * COLS; c0 < MD; c0 += (int64_t)gridDim.y * 4 * COLS) {
+        const int64_t idx = c0 + threadIdx.x % COLS * 4;
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (idx < MD) {
+            for (int64_t i = g * per; i < i1; i += INFLIGHT) {
+                float4 v[INFLIGHT];
 #pragma unroll
-        for (int q = 1; q < G; ++q) {
-            const float4 v = part[q * COLS + threadIdx.x];
-            acc.x += v.x;
-            acc.y += v.y;
-            acc.z += v.z;
-            acc.w += v.w;
+                for (int u = 0; u < INFLIGHT; ++u)   // (past the end: the last again, not added)
+                    v[u] = *reinterpret_cast<const float4*>(partials + ps.slot(min(i + u, i1 - 1)) * MD + idx);
+#pragma unroll
+                for (int u = 0; u < INFLIGHT; ++u) {
+                    if (i + u < i1) {
+                        acc.x += v[u].x;
+                        acc.y += v[u].y;
+                        acc.z += v[u].z;
+                        acc.w += v[u].w;
+                    }
+                }
+            }
         }
+        if constexpr (G > 1) {
+            __syncthreads();   // the previous columns are added up
+            part[threadIdx.x] = acc;
+            __syncthreads();
+            if (g > 0) continue;
+#pragma unroll
+            for (int q = 1; q < G; ++q) {
+                const float4 v = part[q * COLS + threadIdx.x];
+                acc.x += v.x;
+                acc.y += v.y;
+                acc.z += v.z;
+                acc.w += v.w;
+            }
+        }
+        if (idx < MD) *reinterpret_cast<float4*>(sketch + (b * H + h) * MD + idx) = acc;
     }
-    if (idx < MD) *reinterpret_cast<float4*>(sketch + (b * H + h) * MD + idx) = acc;
 }
 
 }  // namespace
@@ -167,7 +179,14 @@ hipError_t launch_merge_ranges(const int64_t* offsets, int64_t B, int64_t T, int
     // MD is a multiple of 4.
     const bool many = n_ranges >= 16 * pairs;
     const int64_t cols = many ? 128 : 1024;
-    const dim3 grid((unsigned)pairs, (unsigned)((MD + cols - 1) / cols));
+    // A workgroup works out its pair's slots before, with many pairs, it mostly finds
+    // nothing to add: about a microsecond, on 1,500 of them at once.  From 16K workgroups on
+    // a pair's columns are dealt to fewer (2,048 users of 16 tokens, M = 512, d = 64: merge
+    // with 65,536 workgroups 49 us, with 16,384 15), but not to less than four, or the
+    // pairs with many segments wait for theirs (8 users of 90 - 2,500 tokens and 16,000
+    // of none, M = 128, the call 167 us; with one 199).
+    const int64_t most = std::max<int64_t>(4, kMergeWgs / pairs);
+    const dim3 grid((unsigned)pairs, (unsigned)std::min<int64_t>((MD + cols - 1) / cols, most));
     if (many)
         hipLaunchKernelGGL(merge_ranges_kernel<8>, grid, dim3(256), 0, stream, offsets, B, T, H, C, n_ranges, partials, MD,
                            sketch);

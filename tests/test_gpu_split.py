@@ -167,3 +167,33 @@ def test_users_without_tokens_cost_their_zeros(sa, M, dtype):
     assert not sk1[4:4004].any()
     assert float((sk1[:4] - sk0[:4]).norm()) <= 1e-5 * float(sk0[:4].norm())   # (partials added in other groups)
     assert t1 <= 10 * t0, (t0, t1)
+
+
+# more (pair, column group)s than workgroups of the merge: each takes several column groups
+@pytest.mark.parametrize("M,d,dtype", [(1024, 64, "bf16"), (640, 128, "bf16"), (512, 64, "fp32")])
+def test_merge_of_many_pairs(sa, M, d, dtype):
+    lengths = [5] * 700 + [300, 0, 2500] + [3] * 300
+    w = wl.custom(lengths, 1, M, d, dtype, seed=M)
+    host = wl.host_tensors(w)
+    dev = wl.to_device(host, dtype)
+    args = dev["K"], dev["V"], dev["P"], dev["offsets"]
+    ref = oracle.fwd(host["K"], host["V"], host["P"], host["offsets"], w.scale)[0]
+    sk = sa.sketch_fwd(*args, w.scale)[0].cpu().numpy()
+    # 2-norm per user: single-precision sums, or weights rounded to bf16 (2^-9 each)
+    err = np.linalg.norm((sk - ref).reshape(len(lengths), -1), axis=1)
+    assert np.all(err <= (4e-3 if M == 1024 else 2e-6) * np.linalg.norm(ref.reshape(len(lengths), -1), axis=1))
+
+
+def test_merge_of_unsplit_pairs_is_short(sa):
+    """2,048 users none of whom is split: finding that out takes a small part of the aggregation's time
+    (a fifth; two thirds with a workgroup for every 1,024 columns)."""
+    dev = wl.device_tensors(wl.custom([16] * 2048, 1, 512, 64, "bf16", seed=1))
+    ratio = 1e9
+    for _ in range(10):
+        sa.profile_enable(True)
+        sa.sketch_fwd(dev["K"], dev["V"], dev["P"], dev["offsets"])
+        torch.cuda.synchronize()
+        t = sa.kernel_times()
+        sa.profile_enable(False)
+        ratio = min(ratio, t["splitL_merge"][1] / t["split_agg"][1])
+    assert ratio <= 0.4, ratio

@@ -118,3 +118,8 @@ def test_tokenwise_sums_to_one(sa):
     sk, _ = sa.sketch_fwd_tokenwise(dev["K"], dev["V"], dev["P"], dev["offsets"], w.scale)
     torch.cuda.synchronize()
     np.testing.assert_allclose(sk.cpu().numpy(), 1.0, rtol=0, atol=1e-2)
+
+
+def test_tokenwise_merge_of_many_pairs(sa):
+    # more (pair, row group)s than workgroups of the merge: each takes several row groups
+    run_case(sa, wl.custom([5] * 700 + [300, 0, 2500] + [3] * 300, 1, 1024, 64, "bf16", seed=9))
