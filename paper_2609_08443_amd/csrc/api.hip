@@ -786,6 +786,11 @@ int device_cus() {
     return g_cu_count[dev];
 }
 
+int64_t xcd_ranges(int64_t per_cu, int64_t parts) {
+    const int64_t each = (int64_t)device_cus() * per_cu / 8 / parts;
+    return each > 0 ? 8 * each : std::max<int64_t>(1, (int64_t)device_cus() * per_cu / parts);
+}
+
 ProfScope::ProfScope(const char* name, hipStream_t stream) : stream_(stream) {
     if (!g_prof_on) return;
     name_ = name;

@@ -674,7 +674,7 @@ int proto_waves(int32_t M, int32_t d) { return d == 64 ? part_waves(M) : (M <= 6
 // prototype side, by its registers), in at most two workgroups per CU
 int64_t ranges(int32_t M, int nw, bool one) {
     const int64_t parts = (M + 32 * nw - 1) / (32 * nw);
-    return std::max<int64_t>(1, (int64_t)device_cus() * (one || nw == 8 ? 1 : 2) / parts);
+    return xcd_ranges(one || nw == 8 ? 1 : 2, parts);
 }
 
 template <typename Kern, typename Args>

@@ -534,7 +534,9 @@ int agg_waves(int32_t M) {
 
 int64_t split_fwd_ranges(int32_t M, bool bf16_weights, int64_t HT, int64_t pairs) {
     // two waves per SIMD of every CU in one round of workgroups, at most two
-    // workgroups per CU; ranges of at least 128 (bf16 weights) or 64 tokens, below
+    // workgroups per CU and as many ranges on every XCD (256 / 3 ranges of three parts
+    // are 33 workgroups for some XCD's 32 CUs, a second round: 65 us against 49 at
+    // M = 768, d = 64, 16 users of 4K tokens); ranges of at least 128 (bf16 weights) or 64 tokens, below
     // which a range's partial costs more than its tiles (M = 512, d = 128, 2K tokens,
     // us: 16 ranges 23, 32 25, 63 27).  Shorter ones, down to a tile, where the mean user
     // is shorter: a range's users are done one after the other, a tile or more each
@@ -543,8 +545,7 @@ int64_t split_fwd_ranges(int32_t M, bool bf16_weights, int64_t HT, int64_t pairs
     const int nw = agg_waves(M);
     const int64_t parts = (M + 32 * nw - 1) / (32 * nw);
     const int64_t least = std::clamp<int64_t>(HT / std::max<int64_t>(pairs, 1), kTileTokens, bf16_weights ? 128 : 64);
-    const int64_t r = std::min<int64_t>((int64_t)device_cus() * (nw == 8 ? 1 : 2) / parts, (HT + least - 1) / least);
-    return r < 1 ? 1 : r;
+    return std::min(xcd_ranges(nw == 8 ? 1 : 2, parts), std::max<int64_t>(1, (HT + least - 1) / least));
 }
 
 hipError_t launch_split_fwd(const SplitFwdArgs& f, hipStream_t stream) {

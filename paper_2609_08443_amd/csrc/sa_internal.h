@@ -192,6 +192,9 @@ struct GemmDesc {
 bool gemm_on_matrix_cores(const GemmDesc& d);
 // number of compute units of the current device (read once per device)
 int device_cus();
+// token ranges of `parts` workgroups each that run in one round, per_cu workgroups on a CU:
+// the most that each XCD holds alike (the parts of a range run on one XCD), or one
+int64_t xcd_ranges(int64_t per_cu, int64_t parts);
 // The bf16-operand product on one given tile shape (0 .. gemm_tile_shapes() - 1,
 // the largest first) instead of the one launch_gemm picks (shape < 0: as
 // launch_gemm); hipErrorInvalidValue where that shape cannot take the product.

@@ -283,3 +283,17 @@ def test_two_pass_ranges_follow_the_mean_user(M, d, dtype):
     most = 64 if M % 128 else 128
     assert chunk(512, 8) == 32 and chunk(64, 16) == 32 and chunk(64, 64) == 64
     assert chunk(8, 512) == most and chunk(1, 4096) == most
+
+
+@pytest.mark.parametrize("M,d,dtype,waves", [(768, 64, sa.SA_BF16, 8), (384, 128, sa.SA_BF16, 4), (640, 128, sa.SA_BF16, 4),
+                                             (1536, 128, sa.SA_BF16, 8), (1152, 64, sa.SA_BF16, 4), (96, 64, sa.SA_BF16, 4),
+                                             (768, 64, sa.SA_FP32, 8), (640, 64, sa.SA_FP32, 4), (1792, 64, sa.SA_FP32, 8)])
+def test_two_pass_ranges_fit_each_xcd_once(M, d, dtype, waves):
+    """The aggregation's workgroups (ranges x parts of 32 `waves` prototypes, the parts of a range on
+    one of 8 XCDs) run in one round on 32 CUs an XCD: one workgroup of eight waves a CU, or two."""
+    HT = 32_000   # short enough for two passes everywhere
+    ranges = -(-HT // sa.fwd_chunk_tokens(1, HT, 1, M, d, dtype))
+    parts = -(-M // (32 * waves))
+    slots = 32 * (1 if waves == 8 else 2)
+    assert -(-ranges // 8) * parts <= slots, (ranges, parts)
+    assert ranges * parts >= 0.6 * 8 * slots or ranges >= HT // 128
