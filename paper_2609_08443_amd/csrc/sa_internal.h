@@ -18,7 +18,7 @@ enum : int { IT_B = 0, IT_H = 1, IT_T0 = 2, IT_T1 = 3, IT_RANGE = 4, IT_SPLIT = 
 
 constexpr int kTileTokens = 32;     // tokens per MFMA tile (rows of the 32x32 output)
 constexpr int kWorklistThreads = 1024;
-constexpr int64_t kMergeWgs = 16384;   // most workgroups of a split-L merge while pairs share them
+constexpr int64_t kMergeWgs = 8192;   // most workgroups of a split-L merge while pairs share them
 
 // Brackets the launches made in its scope with HIP events on `stream` when
 // kernel timing is enabled on the calling thread (sa_profile_enable).

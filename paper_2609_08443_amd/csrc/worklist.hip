@@ -180,11 +180,11 @@ hipError_t launch_merge_ranges(const int64_t* offsets, int64_t B, int64_t T, int
     const bool many = n_ranges >= 16 * pairs;
     const int64_t cols = many ? 128 : 1024;
     // A workgroup works out its pair's slots before, with many pairs, it mostly finds
-    // nothing to add: about a microsecond, on 1,500 of them at once.  From 16K workgroups on
+    // nothing to add: about a microsecond, on 2,000 of them at once.  From 8K workgroups on
     // a pair's columns are dealt to fewer (2,048 users of 16 tokens, M = 512, d = 64: merge
-    // with 65,536 workgroups 49 us, with 16,384 15), but not to less than four, or the
-    // pairs with many segments wait for theirs (8 users of 90 - 2,500 tokens and 16,000
-    // of none, M = 128, the call 167 us; with one 199).
+    // with 65,536 workgroups 49 us, with 16,384 15, with 8,192 9), but not to less than
+    // four, or the pairs with many segments wait for theirs (8 users of 90 - 2,500 tokens
+    // and 16,000 of none, M = 128: the call 135 us, 199 with one).
     const int64_t most = std::max<int64_t>(4, kMergeWgs / pairs);
     const dim3 grid((unsigned)pairs, (unsigned)std::min<int64_t>((MD + cols - 1) / cols, most));
     if (many)
