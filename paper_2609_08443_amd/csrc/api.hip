@@ -126,16 +126,22 @@ void set_ranges(int64_t HT, int64_t target, int64_t* C, int64_t* n) {
 // One pass gives every workgroup all M prototypes, so with few tokens a CU it spends
 // its time on the prototype load and the M x d partial of each short range; two
 // passes compute the logits twice but cut the ranges by the prototype parts.
-// Measured, one pass / two (us) at HT (head, token) pairs:
-//   M = 512, d = 128:  2K 49 / 28,  40K 67 / 47,  128K 92 / 76,  512K 227 / 243
-//   M = 256, d = 128:  8K 40 / 27,  40K 43 / 37,  160K 65 / 63,  640K 166 / 176
-//   M = 1024, d = 64:  4K 52 / 28,  40K 56 / 48,  80K 80 / 76,  128K 87 / 94
-//   M = 256, d = 64:   8K 25 / 20,  40K 33 / 27,  128K 37 / 39
-//   M = 128, d = 64:   2K 15 / 18,  8K 18 / 18,  40K 28 / 24,  128K 30 / 29
-//   M = 128, d = 128:  8K 26 / 22,  40K 34 / 31,  128K 39 / 42
+// Measured, one pass / two (us) at HT (head, token) pairs, users of 0.4 to 1.6 times
+// 1,024 tokens (of 4,096 and of 128 the line lies the same within 3%):
+//   HT            16K        32K        48K        64K        96K       128K
+//   128,  64   21.8/18.6  24.7/21.9  28.2/26.9  27.4/25.6  29.5/29.2  31.9/31.3
+//   512,  64   37.7/28.4  39.4/33.7  41.3/37.6  44.3/40.8  48.5/53.4  55.4/59.9
+//  1024,  64   57.1/34.5  60.7/45.4  67.3/54.5  71.0/63.4  80.1/86.2  90.0/98.3
+//   128, 128   30.5/24.8  32.8/27.4  33.3/36.8  36.5/42.5  39.8/47.3  43.8/51.2
+//   256, 128   37.9/32.0  38.3/35.2  41.5/40.7  44.9/43.6  50.1/50.2  57.3/56.4
+//   384, 128   46.7/35.3  48.7/43.9  53.6/54.5  56.7/60.1  63.5/76.6  71.5/89.6
+//   512, 128   57.1/36.5  59.8/42.6  66.3/50.7  69.5/58.3  77.6/76.2  87.2/88.2
+// (M, d).  At d = 128 the aggregation keeps up with one pass for longest with its
+// workgroups of eight waves, M a multiple of 256, and for least with those of four,
+// which read each token tile twice as often.  M = 128, d = 64 below 8K: 16/19 at 4K.
 bool two_pass_faster(int64_t HT, int32_t M, int32_t d) {
     if (M * d <= 8192 && HT < 8192) return false;
-    const int64_t per_cu = d == 128 && M >= 256 ? 512 : 256;
+    const int64_t per_cu = d == 64 ? 256 : M % 256 == 0 ? 512 : 128;
     return HT <= per_cu * device_cus();
 }
 

@@ -297,3 +297,13 @@ def test_two_pass_ranges_fit_each_xcd_once(M, d, dtype, waves):
     slots = 32 * (1 if waves == 8 else 2)
     assert -(-ranges // 8) * parts <= slots, (ranges, parts)
     assert ranges * parts >= 0.6 * 8 * slots or ranges >= HT // 128
+
+
+@pytest.mark.parametrize("M,d,line", [(128, 64, 65536), (768, 64, 65536), (128, 128, 32768), (384, 128, 32768),
+                                      (256, 128, 131072), (512, 128, 131072)])
+def test_line_between_one_and_two_passes(M, d, line):
+    """The workspace of one pass is its partials; two passes add an lse scratch (4 bytes a pair)."""
+    size = lambda HT: sa.fwd_workspace_size(1, HT, 1, M, d, sa.SA_BF16)
+    def has_lse(HT):   # the lse scratch: bytes beyond whole partials
+        return size(HT) % (4 * M * d) != 0
+    assert has_lse(line - 100) and not has_lse(line + 100)

@@ -85,3 +85,10 @@ def test_one_pass_loose_bound_exact_maximum(sa, M, d):
     err = (sk.double() - rs).abs().amax(dim=(2, 3)) / rs.abs().amax(dim=(2, 3))
     assert float(err.max()) <= 2e-2
     assert float((lse.double() - rl).abs().max()) <= 2e-2   # logits of several hundred
+
+
+@pytest.mark.parametrize("M", [128, 384])
+def test_both_sides_of_the_short_line(sa, M):
+    """d = 128 and M no multiple of 256: two passes up to 32,768 (head, token) pairs."""
+    for T in (4095, 4096, 4097):
+        check(sa, [T - 40, 40], 8, M, 128)
