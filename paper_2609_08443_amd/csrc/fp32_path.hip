@@ -148,20 +148,31 @@ struct TileLoad {
 };
 
 // ---------------------------------------------------------------- forward: log-sum-exp
-// Workgroup = 4 waves of 32 tokens (held as operands), prototypes streamed through
-// LDS 32 at a time; a token's running maximum and sum live in one lane per half-wave.
-template <int D>
+// Workgroup = 4 waves; WM of them hold the same 32 tokens as operands and take every
+// WM-th tile of 32 prototypes.  WM = 1: the tiles stream through LDS one at a time,
+// double-buffered; WM = 4: four at a time, a wave each.  The next are in registers.  A
+// token's running maximum and sum live in one lane per half-wave and wave.
+template <int D, int WM>
+struct LseF32Cfg {
+    static constexpr int TOKENS = 128 / WM;   // per workgroup
+    static constexpr int BUFS = WM == 1 ? 2 : 1;
+    static constexpr size_t LDS = (size_t)BUFS * WM * Tile32<D>::FLOATS * 4 + 4 * 32 * sizeof(float2);
+};
+template <int D, int WM>
 __global__ __launch_bounds__(256) void lse_f32_kernel(const float* __restrict__ K, const float* __restrict__ P,
                                                       const int64_t* __restrict__ off, int64_t B, int64_t T,
                                                       int32_t H, int32_t M, float scale, bool p_user,
                                                       float* __restrict__ lse) {
     using TL = Tile32<D>;
-    __shared__ __attribute__((aligned(16))) float tile[2][TL::FLOATS];
+    using C = LseF32Cfg<D, WM>;
+    extern __shared__ __attribute__((aligned(16))) float sm[];
+    float2* stats = reinterpret_cast<float2*>(sm + C::BUFS * WM * TL::FLOATS);   // [wave][32]: maximum and sum
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l32 = lane & 31, hl = lane >> 5;
-    const int64_t nblk = (T + 127) / 128;
+    const int wt = w / WM, wm = w % WM;
+    const int64_t nblk = (T + C::TOKENS - 1) / C::TOKENS;
     const int32_t h = (int32_t)(blockIdx.x / nblk);
-    const int64_t blk0 = (blockIdx.x % nblk) * 128, blk1 = blk0 + 128 < T ? blk0 + 128 : T;
-    const int64_t tok = blk0 + w * 32 + l32;
+    const int64_t blk0 = (blockIdx.x % nblk) * C::TOKENS, blk1 = blk0 + C::TOKENS < T ? blk0 + C::TOKENS : T;
+    const int64_t tok = blk0 + wt * 32 + l32;
     float kop[D / 2];
     load_operand<false, D>(K, ((tok < T ? tok : T - 1) * H + h) * D, hl, kop);
     const float ks2 = scale * kLog2e;
@@ -179,44 +190,92 @@ __global__ __launch_bounds__(256) void lse_f32_kernel(const float* __restrict__ 
             if (hi <= lo || hi <= blk0) continue;
         }
         const float* Pg = P + (p_user ? b * H + h : (int64_t)h) * M * D;
-        TileLoad<false, D, 256> ld;
-        auto rows = [&](int t) { return [=](int i) { return (int64_t)min(t * 32 + i, M - 1) * D; }; };
-        // log2 units; the maximum stays finite while all logits are -inf
+        TileLoad<false, D, 256> ld[WM];
+        auto fetch = [&](int t) {
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+                ld[i].fetch(Pg, tid, [=](int r) { return (int64_t)min((t + i) * 32 + r, M - 1) * D; });
+        };
+        auto store = [&](int buf) {
+#pragma unroll
+            for (int i = 0; i < WM; ++i) ld[i].store(sm + (buf * WM + i) * TL::FLOATS, tid, 32);
+        };
+        // log2 units; the maximum stays finite while all logits are -inf, or while a wave
+        // has no tile
         float mu = -kFloatMax, z = 0.f;
-        ld.fetch(Pg, tid, rows(0));
+        fetch(0);
         __syncthreads();   // the previous round is done with the tiles
-        ld.store(tile[0], tid, 32);
+        store(0);
         __syncthreads();
-        for (int t = 0; t < ntiles; ++t) {
-            const bool more = t + 1 < ntiles;
-            if (more) ld.fetch(Pg, tid, rows(t + 1));
-            const f32x16 s = TL::rows_dot(tile[t & 1], l32, hl, kop);
-            const bool ragged = t * 32 + 32 > M;   // rows past M: no part in the maximum or the sum
-            float x[16], m = -kFloatMax;
+        for (int t0 = 0, buf = 0; t0 < ntiles; t0 += WM) {
+            const bool more = t0 + WM < ntiles;
+            if (more) fetch(t0 + WM);
+            const int t = t0 + wm;
+            if (t < ntiles) {
+                const f32x16 s = TL::rows_dot(sm + (buf * WM + wm) * TL::FLOATS, l32, hl, kop);
+                const bool ragged = t * 32 + 32 > M;   // rows past M: no part in the maximum or the sum
+                float x[16], m = -kFloatMax;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                x[r] = s[r];
-                m = fmaxf(m, ragged && t * 32 + srow(r, hl) >= M ? m : x[r]);
-            }
-            const float mn = fmaxf(mu, m * ks2);
-            z *= __builtin_amdgcn_exp2f(mu - mn);   // z is 0 on the first tile
+                for (int r = 0; r < 16; ++r) {
+                    x[r] = s[r];
+                    m = fmaxf(m, ragged && t * 32 + srow(r, hl) >= M ? m : x[r]);
+                }
+                const float mn = fmaxf(mu, m * ks2);
+                z *= __builtin_amdgcn_exp2f(mu - mn);   // z is 0 on the first tile
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], ks2, -mn));
-                z += ragged && t * 32 + srow(r, hl) >= M ? 0.f : e;
+                for (int r = 0; r < 16; ++r) {
+                    const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], ks2, -mn));
+                    z += ragged && t * 32 + srow(r, hl) >= M ? 0.f : e;
+                }
+                mu = mn;
             }
-            mu = mn;
-            if (more) ld.store(tile[(t + 1) & 1], tid, 32);
+            if constexpr (C::BUFS == 1) __syncthreads();   // every wave is done with the tiles
+            else buf ^= 1;
+            if (more) store(buf);
             __syncthreads();
         }
-        // the two half-waves hold the token's other prototype rows
+        // the two half-waves, and the waves sharing the tokens, hold the token's other
+        // prototype rows
         const auto m2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(mu), __float_as_uint(mu), false, false);
         const auto z2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(z), __float_as_uint(z), false, false);
-        const float ma = __uint_as_float(m2[0]), mb = __uint_as_float(m2[1]), mx = fmaxf(ma, mb);
-        const float zz = __uint_as_float(z2[0]) * __builtin_amdgcn_exp2f(ma - mx) +
-                         __uint_as_float(z2[1]) * __builtin_amdgcn_exp2f(mb - mx);
-        if (hl == 0 && tok >= lo && tok < hi) lse[tok * H + h] = __builtin_fmaf(mx, kLn2, __builtin_amdgcn_logf(zz) * kLn2);
+        const float ma = __uint_as_float(m2[0]), mb = __uint_as_float(m2[1]);
+        float mx = fmaxf(ma, mb);
+        float zz = __uint_as_float(z2[0]) * __builtin_amdgcn_exp2f(ma - mx) +
+                   __uint_as_float(z2[1]) * __builtin_amdgcn_exp2f(mb - mx);
+        if constexpr (WM > 1) {
+            if (hl == 0) stats[w * 32 + l32] = make_float2(mx, zz);
+            __syncthreads();
+            if (wm == 0) {
+#pragma unroll
+                for (int q = 1; q < WM; ++q) mx = fmaxf(mx, stats[(w + q) * 32 + l32].x);
+                zz = 0.f;
+#pragma unroll
+                for (int q = 0; q < WM; ++q) {
+                    const float2 o = stats[(w + q) * 32 + l32];
+                    zz += o.y * __builtin_amdgcn_exp2f(o.x - mx);
+                }
+            }
+        }
+        if (wm == 0 && hl == 0 && tok >= lo && tok < hi)
+            lse[tok * H + h] = __builtin_fmaf(mx, kLn2, __builtin_amdgcn_logf(zz) * kLn2);
     }
+}
+
+// Waves sharing a workgroup's tokens: four where workgroups of 128 tokens leave CUs idle
+// (M = 4096, d = 64, one user of 64 tokens, the call: 217 us with one, 82 with four; M = 512,
+// d = 128, one of 2,048: 79 and 52).
+template <int D, int WM>
+hipError_t launch_lse_f32(const SplitFwdArgs& f, hipStream_t stream) {
+    using C = LseF32Cfg<D, WM>;
+    const int64_t nblk = (f.T + C::TOKENS - 1) / C::TOKENS;
+    if (nblk * f.H > 0x7fffffff) return hipErrorInvalidValue;
+    auto kern = lse_f32_kernel<D, WM>;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)C::LDS);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(nblk * f.H)), dim3(256), C::LDS, stream, reinterpret_cast<const float*>(f.K),
+                       reinterpret_cast<const float*>(f.P), f.offsets, f.B, f.T, f.H, f.M, f.scale, f.p_user, f.lse);
+    return hipGetLastError();
 }
 
 // workgroup -> (token range, part of the prototypes), the parts of a range back to
@@ -704,13 +763,9 @@ hipError_t fwd_impl(const SplitFwdArgs& f, hipStream_t stream) {
             default: return launch_parts(agg_f32_kernel<D, 8, true>, a, 8, lds, stream);
         }
     }
-    const int64_t nblk = (f.T + 127) / 128;
-    if (nblk * f.H > 0x7fffffff) return hipErrorInvalidValue;
     {
         ProfScope ps("plain_lse", stream);
-        hipLaunchKernelGGL((lse_f32_kernel<D>), dim3((unsigned)(nblk * f.H)), dim3(256), 0, stream, K, P, f.offsets, f.B,
-                           f.T, f.H, f.M, f.scale, f.p_user, f.lse);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e = (f.T + 127) / 128 * f.H < device_cus() ? launch_lse_f32<D, 4>(f, stream) : launch_lse_f32<D, 1>(f, stream);
         if (e != hipSuccess) return e;
     }
     const size_t lds = (4 * Tile32<D>::FLOATS + 64) * sizeof(float);

@@ -94,3 +94,31 @@ def test_backward_without_users(sa, dtype, H, M, d):
     for name, g in zip(("dK", "dV", "dP"), out):
         assert not g.any(), name
     assert bool((ws[n:] == 77).all())
+
+
+# log-sum-exp workgroups of 128 tokens (enough of them for every CU), and of 32 tokens shared by
+# four waves, which take tiles of 32 prototypes in turn: some or all idle in the last round
+@pytest.mark.parametrize("lengths,H,M,d", [([20000, 3, 0, 13000], 1, 300, 64), ([9000, 7500], 2, 264, 128),
+                                           ([70, 0, 33], 2, 288, 64), ([1], 1, 416, 128), ([31, 65], 1, 449, 64)])
+def test_log_sum_exp_waves(sa, lengths, H, M, d):
+    w = wl.custom(lengths, H, M, d, "fp32", seed=M)
+    host = wl.host_tensors(w)
+    dev = wl.to_device(host, "fp32")
+    sk, lse = sa.sketch_fwd(dev["K"], dev["V"], dev["P"], dev["offsets"], w.scale)
+    rs, rl = oracle.fwd(host["K"], host["V"], host["P"], host["offsets"], w.scale)
+    assert rel(sk, rs) <= 2e-6 and rel(lse, rl) <= 4.9e-7
+
+
+def test_few_tokens_against_many_prototypes(sa):
+    """The log-sum-exp of 64 tokens against 4,096 prototypes is shared by the waves of a workgroup: five
+    times as long as the aggregation (15 times with a wave for 32 tokens)."""
+    dev = wl.device_tensors(wl.custom([64], 1, 4096, 64, "fp32", seed=1))
+    ratio = 1e9
+    for _ in range(10):
+        sa.profile_enable(True)
+        sa.sketch_fwd(dev["K"], dev["V"], dev["P"], dev["offsets"])
+        torch.cuda.synchronize()
+        t = sa.kernel_times()
+        sa.profile_enable(False)
+        ratio = min(ratio, t["plain_lse"][1] / t["plain_agg"][1])
+    assert ratio <= 7.0, ratio
