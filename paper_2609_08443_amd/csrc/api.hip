@@ -164,7 +164,7 @@ FwdPlan plan_fwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype
         p.C = fused_chunk_tokens(T, H, M, d);
         p.n_ranges = (HT + p.C - 1) / p.C;
     } else {
-        set_ranges(HT, dtype == SA_BF16 ? sa::split_fwd_ranges(M, p.bf16_weights, HT, H * B) : sa::plain_fwd_ranges(M),
+        set_ranges(HT, dtype == SA_BF16 ? sa::split_fwd_ranges(M, p.bf16_weights, HT, H * B) : sa::plain_fwd_ranges(M, d),
                    &p.C, &p.n_ranges);
     }
     p.off_partials = carve(sizeof(float) * (size_t)(p.n_ranges + H * B) * M * d);

@@ -724,13 +724,21 @@ __global__ __launch_bounds__(256) void dy_kernel(const float4* __restrict__ ds, 
     dY[i] = s;
 }
 
-// waves of 32 prototypes per workgroup: as many as M fills, up to eight
+// Waves of 32 prototypes per workgroup: as many as M fills, up to eight.  At d = 128 eight
+// waves, two a SIMD with 256 registers each, spill: none on the prototype side of the
+// backward, and in the forward only for M <= 256, where one pass takes all prototypes
+// (61 registers spilled; in two passes with four waves 8 users of 1,200 tokens take 51
+// instead of 70 us, one of 50K 118 instead of 116, but lse is 1.2 times as far from 64 bits).
+// Forward with eight waves (53 spilled) / four: M = 512, 8 users of 1,200 tokens 103 / 73 us,
+// one of 50K 229 / 212.  (At d = 64 the prototype side's eight waves spill 14 registers
+// and are still ahead on long batches: M = 1024, 50K tokens, training step 786, with four 834.)
 int part_waves(int32_t M) { return M <= 64 ? 2 : (M % 256 > 0 && M % 256 <= 128 ? 4 : 8); }
-
+int fwd_waves(int32_t M, int32_t d) { return d == 128 && M > 256 ? 4 : part_waves(M); }
 int proto_waves(int32_t M, int32_t d) { return d == 64 ? part_waves(M) : (M <= 64 ? 2 : 4); }
 
-// ranges that give every CU its two waves per SIMD once (one at d = 128 on the
-// prototype side, by its registers), in at most two workgroups per CU
+// ranges that give every CU its two waves per SIMD once, in at most two workgroups per
+// CU; one wave (by its registers) with `one`: four waves at d = 128, any number there on
+// the prototype side
 int64_t ranges(int32_t M, int nw, bool one) {
     const int64_t parts = (M + 32 * nw - 1) / (32 * nw);
     return xcd_ranges(one || nw == 8 ? 1 : 2, parts);
@@ -752,7 +760,7 @@ hipError_t fwd_impl(const SplitFwdArgs& f, hipStream_t stream) {
                 *P = reinterpret_cast<const float*>(f.P);
     AggF32Args a{K, V, P, f.offsets, f.lse, f.B, f.T, f.C, f.n_ranges, f.H, f.M, 1, f.scale, f.p_user, f.sketch, f.partials,
                  nullptr};
-    const int nw = part_waves(f.M);
+    const int nw = fwd_waves(f.M, D);
     if (f.M <= 32 * nw) {   // one part: no pass for the log-sum-exp
         a.lse_out = f.lse;
         const size_t lds = (4 * Tile32<D>::FLOATS + 64 + 64 * nw) * sizeof(float);
@@ -770,8 +778,10 @@ hipError_t fwd_impl(const SplitFwdArgs& f, hipStream_t stream) {
     }
     const size_t lds = (4 * Tile32<D>::FLOATS + 64) * sizeof(float);
     ProfScope ps("plain_agg", stream);
-    if (nw == 4) return launch_parts(agg_f32_kernel<D, 4, false>, a, 4, lds, stream);
-    return launch_parts(agg_f32_kernel<D, 8, false>, a, 8, lds, stream);
+    if constexpr (D == 64) {
+        if (nw == 8) return launch_parts(agg_f32_kernel<D, 8, false>, a, 8, lds, stream);
+    }
+    return launch_parts(agg_f32_kernel<D, 4, false>, a, 4, lds, stream);
 }
 
 template <bool BF16, int D>
@@ -810,7 +820,9 @@ hipError_t bwd_impl(const PlainBwdArgs& f, hipStream_t stream) {
 
 }  // namespace
 
-int64_t plain_fwd_ranges(int32_t M) { return ranges(M, part_waves(M), false); }
+int64_t plain_fwd_ranges(int32_t M, int32_t d) {
+    return ranges(M, fwd_waves(M, d), d == 128 && fwd_waves(M, d) == 4);
+}
 int64_t plain_bwd_ranges(int32_t M, int32_t d) { return ranges(M, proto_waves(M, d), d == 128); }
 
 hipError_t launch_plain_fwd(const SplitFwdArgs& f, hipStream_t stream) {

@@ -248,7 +248,7 @@ hipError_t launch_sum_users(const float* part, int64_t B, int32_t H, int64_t n, 
 // fp32 inputs (K, V, P of SplitFwdArgs point to fp32 values), and the backward of
 // fp32 inputs and of the bf16 shapes without a fused instance.
 // token ranges that fill the device once (forward; backward, prototype side)
-int64_t plain_fwd_ranges(int32_t M);
+int64_t plain_fwd_ranges(int32_t M, int32_t d);
 int64_t plain_bwd_ranges(int32_t M, int32_t d);
 hipError_t launch_plain_fwd(const SplitFwdArgs& f, hipStream_t stream);
 
