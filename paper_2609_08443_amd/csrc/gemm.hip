@@ -636,21 +636,20 @@ hipError_t lt_dispatch(const MgArgs& g, bool a_kc, bool b_kc, bool c_bf16, int64
 }
 
 // Tile shapes: rows, columns, relative speed per tile element (fewer LDS and L2
-// bytes per product for bigger tiles), workgroups per CU, whether the A operand
-// may be m-contiguous (160 rows do not split into whole loads of rows), and
-// whether the shape is a one-slab (K = 64) variant.
+// bytes per product for bigger tiles), whether the A operand may be m-contiguous
+// (160 rows do not split into whole loads of rows), and whether the shape is a
+// one-slab (K = 64) variant.
 struct LtShape {
     int bm, bn;
     double eff;
-    int occ;
     bool a_mc_ok;
     bool one_slab;   // K = 64 only
 };
 constexpr LtShape kLtShapes[] = {
-    {160, 256, 1.0, 1, false, false}, {128, 256, 0.85, 1, true, false}, {256, 128, 0.85, 1, true, false},
-    {128, 128, 0.7, 1, true, false},  {64, 128, 0.55, 2, true, false},  {128, 64, 0.6, 2, true, false},
-    {64, 64, 0.62, 3, true, false},   {160, 256, 1.0, 2, false, true},  {128, 128, 0.7, 4, true, true},
-    {128, 64, 0.6, 4, true, true},    {64, 64, 0.5, 4, true, true}};
+    {160, 256, 1.0, false, false}, {128, 256, 0.85, true, false}, {256, 128, 0.85, true, false},
+    {128, 128, 0.7, true, false},  {64, 128, 0.55, true, false},  {128, 64, 0.6, true, false},
+    {64, 64, 0.62, true, false},   {160, 256, 1.0, false, true},  {128, 128, 0.7, true, true},
+    {128, 64, 0.6, true, true},    {64, 64, 0.5, true, true}};
 
 // The per-lane load offsets of an operand are 32-bit byte offsets from the slab's
 // base: a k-contiguous operand's reach over its rows and K, an m- (n-)
@@ -664,12 +663,14 @@ bool lt_offsets_fit(const GemmDesc& d, bool a_kc, bool b_kc) {
 }
 
 // The shape with the least estimated time: the most tiles one compute unit gets
-// (resident workgroups split its matrix cores, so `occ` of them take as long as one
+// (workgroups resident together split its matrix cores, so they take as long as one
 // after the other), each the tile's work over its speed; small tiles win where big
-// ones leave compute units idle.  Counting whole rounds of `occ` tiles instead made
+// ones leave compute units idle.  Counting whole rounds of resident tiles instead made
 // 1,200 tiles of 64 x 64 look like six a CU, not five, and 4800 x 1024 x 1024 took
-// 128 x 256 tiles: 21.4 us (23.8 with B n-contiguous) against 18.7 (19.6).  -1 if no
-// shape applies (byte offsets of a k-contiguous operand beyond 32 bits).
+// 128 x 256 tiles: 21.4 us (23.8 with B n-contiguous) against 18.7 (19.6).  Over 970
+// products (up to 5,800 x 2,000 x 2,000 and 64 batches) the choice is 3.9% behind the fastest
+// shape in the mean and more than 10% behind for 118, counting rounds 4.0% and for 124.
+// -1 if no shape applies (byte offsets of a k-contiguous operand beyond 32 bits).
 int choose_lt(const GemmDesc& d, bool a_kc, bool b_kc) {
     if (!lt_offsets_fit(d, a_kc, b_kc)) return -1;
     const int64_t cus = device_cus();
@@ -677,7 +678,7 @@ int choose_lt(const GemmDesc& d, bool a_kc, bool b_kc) {
     double best_cost = 0;
     for (int i = 0; i < (int)(sizeof(kLtShapes) / sizeof(kLtShapes[0])); ++i) {
         const LtShape& t = kLtShapes[i];
-        // one-slab products take the one-slab shapes (same tiles, more of them per CU)
+        // one-slab products take the one-slab shapes
         if ((!a_kc && !t.a_mc_ok) || t.one_slab != (d.K == GBK)) continue;
         const int64_t tiles = (int64_t)((d.M + t.bm - 1) / t.bm) * ((d.N + t.bn - 1) / t.bn) * d.batch;
         if (tiles >= (int64_t(1) << 31)) continue;
