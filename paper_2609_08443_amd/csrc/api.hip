@@ -147,30 +147,43 @@ bool two_pass_faster(int64_t HT, int32_t M, int32_t d) {
 
 FwdPlan plan_fwd(int64_t B, int64_t T, int32_t H, int32_t M, int32_t d, sa_dtype dtype,
                  bool need_lse_scratch) {
-    FwdPlan p;
-    p.bf16_weights = dtype == SA_BF16 && sa::fused_fwd_supported(M, d);
-    p.fused = p.bf16_weights && !two_pass_faster((int64_t)H * T, M, d);
-    size_t off = 0;
-    auto carve = [&](size_t bytes) {
-        const size_t o = off;
-        off = align_up(off + bytes, 256);
-        return o;
-    };
     const int64_t HT = (int64_t)H * T;
     // the head-major token space in equal ranges: one per workgroup slot of the
     // one-pass kernel, or as many as fill the device with the aggregation's
     // prototype parts; partial slots as in segments.h
-    if (p.fused) {
-        p.C = fused_chunk_tokens(T, H, M, d);
-        p.n_ranges = (HT + p.C - 1) / p.C;
-    } else {
-        set_ranges(HT, dtype == SA_BF16 ? sa::split_fwd_ranges(M, p.bf16_weights, HT, H * B) : sa::plain_fwd_ranges(M, d),
-                   &p.C, &p.n_ranges);
+    auto plan = [&](bool fused, bool lse_scratch) {
+        FwdPlan p;
+        p.bf16_weights = dtype == SA_BF16 && sa::fused_fwd_supported(M, d);
+        p.fused = fused;
+        size_t off = 0;
+        auto carve = [&](size_t bytes) {
+            const size_t o = off;
+            off = align_up(off + bytes, 256);
+            return o;
+        };
+        if (fused) {
+            p.C = fused_chunk_tokens(T, H, M, d);
+            p.n_ranges = (HT + p.C - 1) / p.C;
+        } else {
+            set_ranges(HT, dtype == SA_BF16 ? sa::split_fwd_ranges(M, p.bf16_weights, HT, H * B) : sa::plain_fwd_ranges(M, d),
+                       &p.C, &p.n_ranges);
+        }
+        p.off_partials = carve(sizeof(float) * (size_t)(p.n_ranges + H * B) * M * d);
+        if (!fused && lse_scratch) p.off_lse = carve(sizeof(float) * (size_t)T * H);
+        p.total = off;
+        return p;
+    };
+    if (dtype != SA_BF16 || !sa::fused_fwd_supported(M, d)) return plan(false, need_lse_scratch);
+    if (!two_pass_faster(HT, M, d)) return plan(true, need_lse_scratch);
+    // Two passes have more ranges than one at M = 128, and an lse scratch: a shape whose
+    // one pass fits the scratch of the no-allocation entry stays within it (in every
+    // entry, whether or not lse is asked for, so that they agree bit for bit).
+    const size_t limit = SA_NOALLOC_SCRATCH_BYTES;
+    if (plan(false, true).total > limit) {
+        const FwdPlan one = plan(true, need_lse_scratch);
+        if (one.total <= limit) return one;
     }
-    p.off_partials = carve(sizeof(float) * (size_t)(p.n_ranges + H * B) * M * d);
-    if (!p.fused && need_lse_scratch) p.off_lse = carve(sizeof(float) * (size_t)T * H);
-    p.total = off;
-    return p;
+    return plan(false, need_lse_scratch);
 }
 
 // ---------------------------------------------------------------- token-wise plan

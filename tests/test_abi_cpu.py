@@ -307,3 +307,14 @@ def test_line_between_one_and_two_passes(M, d, line):
     def has_lse(HT):   # the lse scratch: bytes beyond whole partials
         return size(HT) % (4 * M * d) != 0
     assert has_lse(line - 100) and not has_lse(line + 100)
+
+
+@pytest.mark.parametrize("B,T,H,M,d", [(112, 1366, 16, 128, 128), (464, 2804, 4, 128, 128), (1900, 5039, 2, 128, 64),
+                                       (1831, 11152, 1, 128, 128)])
+def test_short_batches_stay_within_the_no_allocation_scratch(B, T, H, M, d):
+    """One pass over these fits the scratch (256 ranges of whole tiles and a slot a pair);
+    two passes, with more ranges and an lse scratch, do not."""
+    chunk = -(-(-(-H * T // 256)) // 32) * 32
+    ranges = -(-H * T // chunk)
+    assert 4 * (ranges + H * B) * M * d <= sa.NOALLOC_SCRATCH_BYTES
+    assert 0 < sa.fwd_workspace_size(B, T, H, M, d, sa.SA_BF16) <= sa.NOALLOC_SCRATCH_BYTES
