@@ -790,24 +790,26 @@ hipError_t bwd_impl(const PlainBwdArgs& f, hipStream_t stream) {
                  f.Dbuf, f.dK, f.dV, f.dX, f.dP, f.partials};
     const int64_t HT = (int64_t)f.H * f.T;
     if (HT > 0) {
-        ProfScope ps("plain_bwd_token", stream);
-        const size_t lds = 4 * Tile32<D>::FLOATS * sizeof(float);
-        const int64_t blocks = (f.T / 128 + f.B + 1) * f.H;
-        if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-        auto kern = f.dX ? bwd_token_f32_kernel<BF16, D, true> : bwd_token_f32_kernel<BF16, D, false>;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds);
+        hipError_t e;
+        {
+            ProfScope ps("plain_bwd_token", stream);
+            const size_t lds = 4 * Tile32<D>::FLOATS * sizeof(float);
+            const int64_t blocks = (f.T / 128 + f.B + 1) * f.H;
+            if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+            auto kern = f.dX ? bwd_token_f32_kernel<BF16, D, true> : bwd_token_f32_kernel<BF16, D, false>;
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, stream, a);
+            e = hipGetLastError();
+        }
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, stream, a);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        ProfScope ps2("plain_bwd_proto", stream);
-        const size_t lds2 = (4 * Tile32<D>::FLOATS + 128) * sizeof(float);
+        ProfScope ps("plain_bwd_proto", stream);
+        const size_t lds = (4 * Tile32<D>::FLOATS + 128) * sizeof(float);
         switch (proto_waves(f.M, D)) {
-            case 2: e = launch_parts(bwd_proto_f32_kernel<BF16, D, 2>, a, 2, lds2, stream); break;
-            case 4: e = launch_parts(bwd_proto_f32_kernel<BF16, D, 4>, a, 4, lds2, stream); break;
+            case 2: e = launch_parts(bwd_proto_f32_kernel<BF16, D, 2>, a, 2, lds, stream); break;
+            case 4: e = launch_parts(bwd_proto_f32_kernel<BF16, D, 4>, a, 4, lds, stream); break;
             default:   // (d = 64 only: at d = 128 eight waves do not fit the registers)
-                if constexpr (D == 64) e = launch_parts(bwd_proto_f32_kernel<BF16, D, 8>, a, 8, lds2, stream);
+                if constexpr (D == 64) e = launch_parts(bwd_proto_f32_kernel<BF16, D, 8>, a, 8, lds, stream);
                 else e = hipErrorInvalidValue;
         }
         if (e != hipSuccess) return e;

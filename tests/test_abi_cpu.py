@@ -310,7 +310,8 @@ def test_line_between_one_and_two_passes(M, d, line):
 
 
 @pytest.mark.parametrize("B,T,H,M,d", [(112, 1366, 16, 128, 128), (464, 2804, 4, 128, 128), (1900, 5039, 2, 128, 64),
-                                       (1831, 11152, 1, 128, 128)])
+                                       (1831, 11152, 1, 128, 128), (1925, 17613, 2, 128, 64), (111, 3218, 16, 128, 128),
+                                       (1658, 65132, 1, 128, 128)])
 def test_short_batches_stay_within_the_no_allocation_scratch(B, T, H, M, d):
     """One pass over these fits the scratch (256 ranges of whole tiles and a slot a pair);
     two passes, with more ranges and an lse scratch, do not."""
