@@ -296,7 +296,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(2, 2
     const int64_t range = xcd * q8 + (xcd < r8 ? xcd : r8) + ix;
 
     const float ks2 = a.scale * kLog2e;
-    const float rks2 = ks2 > 0.f ? 1.0f / ks2 : 0.f;
+    const float rks2 = ks2 > 1e-37f ? 1.0f / ks2 : 0.f;   // (finite; below that the logits are zero)
     const int64_t MD = (int64_t)a.M * D;
     const int64_t row_stride = (int64_t)a.H * D;
     const int m0 = part * C::MP + w * 32;            // the wave's first prototype

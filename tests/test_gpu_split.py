@@ -197,3 +197,17 @@ def test_merge_of_unsplit_pairs_is_short(sa):
         sa.profile_enable(False)
         ratio = min(ratio, t["splitL_merge"][1] / t["split_agg"][1])
     assert ratio <= 0.4, ratio
+
+
+@pytest.mark.parametrize("M", [200, 256])
+@pytest.mark.parametrize("scale", [0.0, 1e-39, 1e-38, 1e-30])
+def test_split_fwd_vanishing_scale(sa, M, scale):
+    """Logits of nothing: every weight 1 / M, also where 1 / scale has no fp32 value.  Bounds as at
+    unit scale (bf16 weights of 1 / 200 and 1 / 256: 2^-9)."""
+    w = wl.custom([70, 0, 33], 1, M, 64, "bf16", seed=M)
+    host = wl.host_tensors(w)
+    dev = wl.to_device(host, "bf16")
+    sk, lse = sa.sketch_fwd(dev["K"], dev["V"], dev["P"], dev["offsets"], scale)
+    ref, rlse = oracle.fwd(host["K"], host["V"], host["P"], host["offsets"], scale)
+    assert np.linalg.norm(sk.cpu().numpy() - ref) <= (2e-6 if M == 200 else 2e-3) * np.linalg.norm(ref)
+    assert np.abs(lse.cpu().numpy() - rlse).max() <= 2e-6 * np.abs(rlse).max()
