@@ -11,6 +11,7 @@
 // the partial sketches of a user cut across ranges merge by addition; there is
 // no rescaling step as in a token-wise softmax.
 #include <algorithm>
+#include <type_traits>
 
 #include "sa_internal.h"
 #include "segments.h"
@@ -123,21 +124,27 @@ __global__ __launch_bounds__(256) void merge_ranges_kernel(const int64_t* __rest
         const int64_t idx = c0 + threadIdx.x % COLS * 4;
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
         if (idx < MD) {
-            for (int64_t i = g * per; i < i1; i += INFLIGHT) {
+            const float* p0 = partials + ps.first * MD + idx;   // slot 0; slot i at p + i MD
+            const float* p = partials + ps.rest * MD + idx;
+            auto add = [&](int64_t i, int n, auto whole) __attribute__((always_inline)) {
+                const float* q = p + i * MD;
                 float4 v[INFLIGHT];
 #pragma unroll
                 for (int u = 0; u < INFLIGHT; ++u)   // (past the end: the last again, not added)
-                    v[u] = *reinterpret_cast<const float4*>(partials + ps.slot(min(i + u, i1 - 1)) * MD + idx);
+                    v[u] = *reinterpret_cast<const float4*>(u == 0 && i == 0 ? p0 : q + (whole.value ? u : min(u, n - 1)) * MD);
 #pragma unroll
                 for (int u = 0; u < INFLIGHT; ++u) {
-                    if (i + u < i1) {
+                    if (whole.value || u < n) {
                         acc.x += v[u].x;
                         acc.y += v[u].y;
                         acc.z += v[u].z;
                         acc.w += v[u].w;
                     }
                 }
-            }
+            };
+            int64_t i = g * per;
+            for (; i + INFLIGHT <= i1; i += INFLIGHT) add(i, INFLIGHT, std::true_type{});
+            if (i < i1) add(i, (int)(i1 - i), std::false_type{});
         }
         if constexpr (G > 1) {
             __syncthreads();   // the previous columns are added up
