@@ -62,11 +62,13 @@ struct LseCfg {
     static constexpr int TOKENS = 4 / WM * 32 * TT;       // tokens per workgroup
 };
 
-template <int D, int WM>
+// PU: P is [B,H,M,d], one prototype block per user: a round for every user with tokens here
+// (an instance of its own: the walk over users in the other's code cost 2 of 45 us).
+template <int D, int WM, bool PU>
 __global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __restrict__ K,
                                                             const uint16_t* __restrict__ P,
                                                             const int64_t* __restrict__ off, int64_t B, int64_t T,
-                                                            int32_t H, int32_t M, float scale, bool p_user,
+                                                            int32_t H, int32_t M, float scale,
                                                             float* __restrict__ lse) {
     using C = LseCfg<D, WM>;
     constexpr int KS = C::KS, TT = C::TT;
@@ -94,18 +96,17 @@ __global__ __launch_bounds__(256, 2) void lse_tokens_kernel(const uint16_t* __re
     const float ks2 = scale * kLog2e;
     const int ntiles = (M + C::ROWS - 1) / C::ROWS;
 
-    // with one prototype block per user, one round per user that has tokens here
     int64_t b = 0, lo = 0, hi = T;
-    if (p_user) b = first_user_after(off, B, T, blk0);
-    for (; p_user ? b < B : b < 1; ++b) {
-        if (p_user) {
+    if constexpr (PU) b = first_user_after(off, B, T, blk0);
+    for (; PU ? b < B : b < 1; ++b) {
+        if constexpr (PU) {
             lo = seg_clamp(off[b], T);
             hi = seg_clamp(off[b + 1], T);
             if (lo >= blk1) break;
             if (hi <= lo) b = next_user_after(off, b + 1, B, T, lo) - 1;   // no tokens: past those like it
             if (hi <= lo || hi <= blk0) continue;
         }
-        const uint16_t* Pg = P + (p_user ? b * H + h : (int64_t)h) * M * D;
+        const uint16_t* Pg = P + (PU ? b * H + h : (int64_t)h) * M * D;
         u32x4 reg[C::NLD];
         auto fetch = [&](int tile) __attribute__((always_inline)) {
 #pragma unroll
@@ -506,8 +507,9 @@ template <int D, int WM>
 hipError_t launch_lse_inst(const SplitFwdArgs& f, hipStream_t stream) {
     const int64_t nblk = (f.T + LseCfg<D, WM>::TOKENS - 1) / LseCfg<D, WM>::TOKENS;
     if (nblk * f.H > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((lse_tokens_kernel<D, WM>), dim3((unsigned)(nblk * f.H)), dim3(256), 0, stream, f.K, f.P,
-                       f.offsets, f.B, f.T, f.H, f.M, f.scale, f.p_user, f.lse);
+    auto kern = f.p_user ? lse_tokens_kernel<D, WM, true> : lse_tokens_kernel<D, WM, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(nblk * f.H)), dim3(256), 0, stream, f.K, f.P, f.offsets, f.B, f.T, f.H, f.M,
+                       f.scale, f.lse);
     return hipGetLastError();
 }
 // Waves sharing a workgroup's tokens: none while 256-token workgroups give every CU
