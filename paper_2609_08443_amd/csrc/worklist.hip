@@ -105,14 +105,14 @@ __global__ __launch_bounds__(kWorklistThreads) void worklist_kernel(
 // sketch[b,h] = the sum of a split pair's partials; zero for an empty one; a pair
 // held by one range is written by its own workgroup.  Without offsets there is one
 // user, of all T tokens.  A workgroup takes 1024 / G columns at a time: G groups of
-// threads add G consecutive parts of the segments in token order, several loads in
+// threads add G consecutive parts of the segments in token order, INFLIGHT loads in
 // flight, and the groups' sums are added in order.
-template <int G>
+template <int G, int INFLIGHT>
 __global__ __launch_bounds__(256) void merge_ranges_kernel(const int64_t* __restrict__ off, int64_t B, int64_t T,
                                                            int32_t H, int64_t C, int64_t n_ranges,
                                                            const float* __restrict__ partials, int64_t MD,
                                                            float* __restrict__ sketch) {
-    constexpr int COLS = 256 / G, INFLIGHT = 8;
+    constexpr int COLS = 256 / G;
     __shared__ float4 part[G > 1 ? 256 : 1];
     const int64_t h = blockIdx.x / B, b = blockIdx.x % B;
     const PairSlots ps(off ? seg_clamp(off[b], T) : 0, off ? seg_clamp(off[b + 1], T) : T, b, h, B, T, C, n_ranges);
@@ -194,12 +194,12 @@ hipError_t launch_merge_ranges(const int64_t* offsets, int64_t B, int64_t T, int
     // and 16,000 of none, M = 128: the call 135 us, 199 with one).
     const int64_t most = std::max<int64_t>(4, kMergeWgs / pairs);
     const dim3 grid((unsigned)pairs, (unsigned)std::min<int64_t>((MD + cols - 1) / cols, most));
-    if (many)
-        hipLaunchKernelGGL(merge_ranges_kernel<8>, grid, dim3(256), 0, stream, offsets, B, T, H, C, n_ranges, partials, MD,
-                           sketch);
-    else
-        hipLaunchKernelGGL(merge_ranges_kernel<1>, grid, dim3(256), 0, stream, offsets, B, T, H, C, n_ranges, partials, MD,
-                           sketch);
+    // eight loads in flight a thread, three where four workgroups a CU have eight groups
+    // each (one user of 100K tokens in 64 segments: M = 1024, d = 128, 1,024 workgroups, with
+    // eight 11.7 us, with three 9.9; M = 128, d = 64, 64 of them, the call 26.8, with three 31.7)
+    auto kern = !many ? merge_ranges_kernel<1, 8>
+                : (int64_t)grid.x * grid.y >= 4 * (int64_t)device_cus() ? merge_ranges_kernel<8, 3> : merge_ranges_kernel<8, 8>;
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, stream, offsets, B, T, H, C, n_ranges, partials, MD, sketch);
     return hipGetLastError();
 }
 
