@@ -186,8 +186,11 @@ __global__ __launch_bounds__(256) void lse_f32_kernel(const float* __restrict__ 
             lo = seg_clamp(off[b], T);
             hi = seg_clamp(off[b + 1], T);
             if (lo >= blk1) break;
-            if (hi <= lo) b = next_user_after(off, b + 1, B, T, lo) - 1;   // no tokens: past those like it
-            if (hi <= lo || hi <= blk0) continue;
+            if (__builtin_expect(hi <= lo, 0)) {   // no tokens: past those like it
+                b = next_user_after(off, b + 1, B, T, lo) - 1;
+                continue;
+            }
+            if (hi <= blk0) continue;
         }
         const float* Pg = P + (p_user ? b * H + h : (int64_t)h) * M * D;
         TileLoad<false, D, 256> ld[WM];

@@ -80,7 +80,7 @@ class SegmentWalk {
             const int64_t lim = end_ - base;
             const int64_t t1 = hi < lim ? hi : lim;
             const int32_t b = (int32_t)b_++;
-            if (t1 <= t0) {
+            if (__builtin_expect(t1 <= t0, 0)) {
                 if (lo >= lim) g_ = end_;   // begins after this range
                 else b_ = next_user_after(off_, b_, B_, T_, t);
                 continue;
