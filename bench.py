@@ -4,7 +4,7 @@
                     [--no-configs] [--no-variants]
 
 A step is one pass of the whole hot path over one batch: sa_sketch_fwd
-(work list, fused forward, split-L merge) then sa_sketch_bwd (MRLB target sum,
+(fused forward, split-L merge) then sa_sketch_bwd (MRLB target sum, work list,
 backward kernels).  The default workload is the ragged 100K batch trained with
 4 target instances per user (32 users, log-uniform lengths in [1e3, 1e5],
 H = 4, d = 128, M = 512, bf16, R = 4).  Inputs are synthetic, drawn on the
@@ -56,13 +56,13 @@ WORKLOADS = {"c1": 1, "c2": 2, "c3": 3, "c4": 4, "c5": 5}
 # Source: profiles/hbm_bytes_c5_ragged100k_fwd_bwd.md
 MEASURED_TRAFFIC = {
     "fused_fwd": ("paper_2609_08443_amd/csrc/fwd_fused.hip",
-                  "d95d57d9a73986256ac7444c7b95b5d25f6e592308de1aca4d0b37338b5712e8",
-                  1.115e9 + 0.145e9),
+                  "8e070f04d038a57cb2ccdd6a53e1d61004a2c968a2d2ba3f2122806b9c19aa18",
+                  1.115e9 + 0.146e9),
     "bwd_token": ("paper_2609_08443_amd/csrc/bwd_fused.hip",
-                  "04c2f979ec2709a93a48939f23c469eddc2e712161f692aa703e9002acbfd291",
-                  1.362e9 + 2.250e9),
+                  "95371f8ec362101eebdfa0e2e7a8ea098eca7f51948f75f5bd83c7e595d0c43d",
+                  1.364e9 + 2.250e9),
     "bwd_proto": ("paper_2609_08443_amd/csrc/bwd_fused.hip",
-                  "04c2f979ec2709a93a48939f23c469eddc2e712161f692aa703e9002acbfd291",
+                  "95371f8ec362101eebdfa0e2e7a8ea098eca7f51948f75f5bd83c7e595d0c43d",
                   1.220e9 + 0.100e9),
 }
 
