@@ -80,10 +80,11 @@ typedef enum {
 /*
  * Supported shapes (SA_ERR_UNSUPPORTED otherwise): 1 <= H, 1 <= M <= 4096,
  * d in {64, 128}, T < 2^31, B >= 0.  bf16 with d = 64 and M a multiple of 128
- * up to 1024, or d = 128 and M a multiple of 128 up to 512, runs the fused
- * matrix-core kernels; the forward of other bf16 shapes runs in two matrix-core
- * passes with fp32 weights; other supported shapes and SA_FP32 run a plain fp32
- * path with the same ABI and the same results up to rounding.
+ * up to 1024, or d = 128 and M a multiple of 128 up to 512, runs the one-pass
+ * forward, or for short batches two passes; other bf16 shapes run the forward in
+ * two passes with fp32 weights.  The backward of bf16 with M a multiple of 128 is
+ * fused; of other M, and SA_FP32 throughout, on the fp32 matrix cores, with the
+ * same ABI and the same results up to rounding.
  */
 
 /* Bytes of workspace that sa_sketch_fwd needs for this shape (0 is possible). */
@@ -463,8 +464,8 @@ int64_t sa_sketch_fwd_chunk_tokens(int64_t B, int64_t T, int32_t H, int32_t M,
  * elements), C[z](m, n) = C[z c_z + m c_m + n] fp32 (c_bf16 = 0) or bf16, fp32
  * accumulation.  A is contiguous along k (a_k = 1) or along m (a_m = 1), B along k
  * (b_k = 1) or along n (b_n = 1).  tile_shape < 0 lets the library pick the
- * shape (as it does for its own products, including the register-tiled fp32
- * product when the matrix cores cannot take it); 0 .. sa_gemm_tile_shapes() - 1
+ * shape (as it does for its own products, including the fp32
+ * matrix-core product when the bf16 one cannot take it); 0 .. sa_gemm_tile_shapes() - 1
  * forces one shape and returns SA_ERR_UNSUPPORTED where that shape cannot take
  * the product (K not a multiple of 64, strides or bases not on 16 bytes, an
  * m-contiguous A on the 160-row shape, byte offsets beyond 32 bits).  Operands

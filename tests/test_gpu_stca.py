@@ -7,8 +7,8 @@ column block for dW_Q, dW_K, dW_V.  lse absolute error: fp32 1e-4; bf16 mode
 rounds q W_Q, u = (q W_Q) W_K^T and the logits themselves to bf16 once each, so a
 logit of magnitude |s| moves by up to about 3 * 2^-9 |s|; the bound is
 2^-7 max(1, max |s|).
-The cases mix products that run on the matrix cores (every contraction length
-a multiple of 64) with ones that do not (the register-tiled fallback).
+The cases mix products that run on the bf16 matrix cores (every contraction length
+a multiple of 64) with ones that do not (the fp32 matrix-core product).
 """
 import numpy as np
 import pytest
